@@ -99,10 +99,11 @@ int bp_rule(int n, int quad, double *x, double *w);
  * then the shared nodes in the order the elements first reach them. The
  * operator kernels then read and write the interior nodes as contiguous
  * blocks, with plain stores in place of atomic additions. Every entry point
- * still takes and returns vectors in the caller's numbering: the vectors
- * are permuted on entry and exit (one gather pass each, and a solve keeps
- * its iteration in the internal order), and the results are the same up to
- * the rounding order of the assembly sums.
+ * still takes and returns vectors in the caller's numbering: the solves
+ * permute b and x on entry and exit (one gather pass each) and iterate in the
+ * internal order; single applications, diagonals and gradients go through a
+ * second gather map in the caller's ids (int32, nelem p1^3). The results are
+ * the same up to the rounding order of the assembly sums.
  * With GL quadrature (and nelem p1^3 < 2^31) the operator also holds the
  * transposed gather map (int32, nglobal + 1 offsets and nelem p1^3 slots) and
  * an element-local output buffer of ncomp nelem p1^3 words (per precision):

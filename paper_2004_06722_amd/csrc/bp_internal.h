@@ -97,6 +97,7 @@ struct bp_op_s {
   bp::Basis basis;
   // device buffers (owned)
   int32_t *idx = nullptr;    // [E][p1^3]; Dirichlet node g stored as -1-g
+  int32_t *idx_c = nullptr;  // the same map in the caller's ids (idx itself without renumbering)
   double *G = nullptr;       // [E][6][q^3] geometric factors
   double *Gk = nullptr;      // kappa_q * G (allocated by bp_set_coeff)
   double *Bt = nullptr;      // [E][q^3]

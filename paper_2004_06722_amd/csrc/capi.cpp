@@ -58,7 +58,9 @@ void dfree(T *&p) {
 void release(bp_op op) {
   if (!op) return;
   (void)hipDeviceSynchronize();
+  if (op->idx_c == op->idx) op->idx_c = nullptr;
   dfree(op->idx);
+  dfree(op->idx_c);
   dfree(op->G);
   dfree(op->Gk);
   dfree(op->Bt);
@@ -164,7 +166,7 @@ int ensure_dinv(bp_op op, int which, hipStream_t s) {
   if (op->dinv_valid[slot]) return BP_OK;
   if (!op->dinv[slot]) return set_error(BP_ERR_ARG, "inverse diagonal not allocated");
   fill_f64(op->tmp, op->nglobal, 0.0, s);
-  int rc = launch_diag(op, which, op->tmp, op->has_dirichlet, s);
+  int rc = launch_diag(op, which, internal_map(op), op->tmp, op->has_dirichlet, s);
   if (rc) return rc;
   invert_diag(op->tmp, op->dinv[slot], (slot == 1 && op->fp32) ? op->dinv32 : nullptr,
               op->nglobal, s);
@@ -282,7 +284,7 @@ int pcg_run(bp_op op, const CgWork &ws, int which, bool f32, const T *b, T *x, c
     else
       fill_f32((float *)w, nv, 0.0f, s);
     if (!x0_zero) {
-      rc = launch_apply(op, which, f32, x, w, masked, nullptr, nullptr, s);
+      rc = launch_apply(op, which, f32, internal_map(op), x, w, masked, nullptr, nullptr, s);
       if (rc) return rc;
     }
     cg_init<T>(nc, n, b, r, w, p, dinv, part, sc, s);
@@ -349,8 +351,8 @@ int pcg_run(bp_op op, const CgWork &ws, int which, bool f32, const T *b, T *x, c
         }
       }
       if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed], s));
-      rc = mass_wl ? launch_mass_wl(op, f32, p, masked, part, done, s)
-                   : launch_apply(op, which, f32, p, w, masked, part, done, s);
+      rc = mass_wl ? launch_mass_wl(op, f32, internal_map(op), p, masked, part, done, s)
+                   : launch_apply(op, which, f32, internal_map(op), p, w, masked, part, done, s);
       if (rc) return rc;
       if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed++ + 1], s));
       if constexpr (sizeof(T) == 8) {
@@ -422,11 +424,11 @@ int pcg_run_sr(bp_op op, int which, const double *b, double *x, const double *di
   if (rc) return rc;
   fill_f64(w, nv, 0.0, s);
   if (!x0_zero) {
-    rc = launch_apply(op, which, false, x, w, masked, nullptr, nullptr, s);
+    rc = launch_apply(op, which, false, internal_map(op), x, w, masked, nullptr, nullptr, s);
     if (rc) return rc;
   }
   sr_init<double>(nc, n, b, r, w, u, p, sv, dinv, pv, s);
-  rc = launch_apply(op, which, false, u, w, masked, pa, nullptr, s);
+  rc = launch_apply(op, which, false, internal_map(op), u, w, masked, pa, nullptr, s);
   if (rc) return rc;
   sr_fin(true, nc, pv, nbv, pa, nba, op->sc, s);
   BP_HIP(hipGetLastError());
@@ -447,7 +449,7 @@ int pcg_run_sr(bp_op op, int which, const double *b, double *x, const double *di
       if (fixed && it + c == maxit - 1) break;
       const bool tm = op->time_apply && timed < kMaxTimedApplies;
       if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed], s));
-      rc = launch_apply(op, which, false, u, w, masked, pa, done, s);
+      rc = launch_apply(op, which, false, internal_map(op), u, w, masked, pa, done, s);
       if (rc) return rc;
       if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed++ + 1], s));
       sr_fin(false, nc, pv, nbv, pa, nba, op->sc, s);
@@ -489,7 +491,8 @@ int true_residual(bp_op op, const double *b, const double *x, double *worst, hip
   const int nc = op->ncomp;
   const int64_t n = op->nglobal;
   fill_f64(op->w, n * nc, 0.0, s);
-  int rc = launch_apply(op, BP_STIFF, false, x, op->w, op->has_dirichlet, nullptr, nullptr, s);
+  int rc = launch_apply(op, BP_STIFF, false, internal_map(op), x, op->w, op->has_dirichlet, nullptr,
+                        nullptr, s);
   if (rc) return rc;
   dc_residual(nc, n, b, op->r, op->w, op->dinv[1], op->part, op->sc, s);
   rc = download_scalars(op, s);
@@ -648,13 +651,11 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   const bool renum = !(flags & BP_SETUP_CALLER_ORDER) &&
                      interior_first_order(p1, nelem, nglobal, elem_dofs, new_of_old, old_of_new,
                                           &n_owned);
-  // gather map in internal ids with the Dirichlet sign encoding
+  // gather map in the caller's ids with the Dirichlet sign encoding
   std::vector<int32_t> idx((size_t)(nelem * n3));
   for (int64_t k = 0; k < nelem * n3; ++k) {
-    const int64_t g = elem_dofs[k];
-    const int32_t v = renum ? new_of_old[(size_t)g] : (int32_t)g;
-    const bool dir = dirichlet && dirichlet[g];
-    idx[k] = dir ? -1 - v : v;
+    const int32_t g = (int32_t)elem_dofs[k];
+    idx[k] = dirichlet && dirichlet[g] ? -1 - g : g;
   }
 
   bp_op op = new bp_op_s();
@@ -697,8 +698,10 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   } while (0)
 
   const int64_t nv = nglobal * ncomp;
-  TRY(dmalloc(&op->idx, idx.size()));
-  TRYHIP(hipMemcpyAsync(op->idx, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+  TRY(dmalloc(&op->idx_c, idx.size()));
+  op->idx = op->idx_c;
+  TRYHIP(hipMemcpyAsync(op->idx_c, idx.data(), idx.size() * sizeof(int32_t),
+                        hipMemcpyHostToDevice, s));
   TRYHIP(hipStreamSynchronize(s));
   if (renum) {
     op->n_owned = n_owned;
@@ -708,6 +711,10 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
                           hipMemcpyHostToDevice, s));
     TRYHIP(hipMemcpyAsync(op->iperm, new_of_old.data(), new_of_old.size() * sizeof(int32_t),
                           hipMemcpyHostToDevice, s));
+    op->idx = nullptr;
+    TRY(dmalloc(&op->idx, idx.size()));
+    map_internal(op->idx_c, op->iperm, op->idx, nelem * n3, s);
+    TRYHIP(hipGetLastError());
     TRYHIP(hipStreamSynchronize(s));
     TRY(dmalloc(&op->bi, nv));
     TRY(dmalloc(&op->xi, nv));
@@ -717,7 +724,10 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   // mass operator's fixed-order assembly, and its element-local output
   const int64_t nl = nelem * n3;
   if (!op->colloc && nl < (int64_t(1) << 31)) {
-    auto node = [&](int64_t k) -> size_t { return (size_t)(idx[k] >= 0 ? idx[k] : -1 - idx[k]); };
+    auto node = [&](int64_t k) -> size_t {
+      const size_t g = (size_t)elem_dofs[k];
+      return renum ? (size_t)new_of_old[g] : g;
+    };
     std::vector<int32_t> off((size_t)nglobal + 1, 0), pos((size_t)nl);
     for (int64_t k = 0; k < nl; ++k) ++off[node(k) + 1];
     for (int64_t g = 0; g < nglobal; ++g) off[(size_t)g + 1] += off[(size_t)g];
@@ -883,32 +893,15 @@ int bp_apply(bp_op op, int which, int prec, const void *u, void *w, unsigned fla
   if (u == w) return set_error(BP_ERR_ARG, "bp_apply: w must not alias u");
   if (flags & ~BP_MASKED) return set_error(BP_ERR_ARG, "bp_apply: unknown flag");
   hipStream_t s = (hipStream_t)stream;
-  const int nc = op->ncomp;
-  const int64_t n = op->nglobal, nv = n * nc;
+  const int64_t nv = op->nglobal * op->ncomp;
   const bool f32 = prec == BP_FP32, masked = (flags & BP_MASKED) != 0;
-  if (!op->perm) {
-    if (f32)
-      fill_f32((float *)w, nv, 0.0f, s);
-    else
-      fill_f64((double *)w, nv, 0.0, s);
-    return launch_apply(op, which, f32, u, w, masked, nullptr, nullptr, s);
-  }
-  // internal order: u in, the operator on the operator's work vectors, w out
-  if (f32) {
-    permute_in<float>(nc, n, op->perm, (const float *)u, op->r32, s);
-    fill_f32(op->w32, nv, 0.0f, s);
-    rc = launch_apply(op, which, true, op->r32, op->w32, masked, nullptr, nullptr, s);
-    if (rc) return rc;
-    permute_out<float>(nc, n, op->iperm, op->w32, (float *)w, s);
-  } else {
-    permute_in<double>(nc, n, op->perm, (const double *)u, op->r, s);
-    fill_f64(op->w, nv, 0.0, s);
-    rc = launch_apply(op, which, false, op->r, op->w, masked, nullptr, nullptr, s);
-    if (rc) return rc;
-    permute_out<double>(nc, n, op->iperm, op->w, (double *)w, s);
-  }
-  BP_HIP(hipGetLastError());
-  return BP_OK;
+  if (which == BP_MASS && op->tr_off)
+    ;  // overwrites w
+  else if (f32)
+    fill_f32((float *)w, nv, 0.0f, s);
+  else
+    fill_f64((double *)w, nv, 0.0, s);
+  return launch_apply(op, which, f32, caller_map(op), u, w, masked, nullptr, nullptr, s);
 }
 
 int bp_apply_local(bp_op op, int which, int prec, const void *uL, void *wL, void *stream) {
@@ -930,13 +923,8 @@ int bp_diag(bp_op op, int which, double *d, unsigned flags, void *stream) {
   if (!d) return set_error(BP_ERR_ARG, "bp_diag: NULL output");
   if (flags & ~BP_MASKED) return set_error(BP_ERR_ARG, "bp_diag: unknown flag");
   hipStream_t s = (hipStream_t)stream;
-  double *dd = op->perm ? op->tmp : d;  // internal order: through op->tmp
-  fill_f64(dd, op->nglobal, 0.0, s);
-  rc = launch_diag(op, which, dd, (flags & BP_MASKED) != 0, s);
-  if (rc || !op->perm) return rc;
-  permute_out<double>(1, op->nglobal, op->iperm, dd, d, s);
-  BP_HIP(hipGetLastError());
-  return BP_OK;
+  fill_f64(d, op->nglobal, 0.0, s);
+  return launch_diag(op, which, caller_map(op), d, (flags & BP_MASKED) != 0, s);
 }
 
 int bp_pcg_solve(bp_op op, int which, const double *b, double *x, double rtol, int maxit,
@@ -1051,7 +1039,7 @@ int bp_pcg_solve_mixed(bp_op op, const double *b, double *x_out, double outer_rt
                         &outer, s);
   } else for (;;) {
     fill_f64(op->w, nv, 0.0, s);
-    rc = launch_apply(op, BP_STIFF, false, x, op->w, masked, nullptr, nullptr, s);
+    rc = launch_apply(op, BP_STIFF, false, internal_map(op), x, op->w, masked, nullptr, nullptr, s);
     if (rc) break;
     dc_residual(nc, n, b, op->r, op->w, op->dinv[1], op->part, op->sc, s);
     rc = download_scalars(op, s);
@@ -1101,12 +1089,6 @@ int bp_grad_kappa(bp_op op, const double *lam, const double *u, double *g, void 
   if (rc) return rc;
   if (!lam || !u || !g) return set_error(BP_ERR_ARG, "bp_grad_kappa: NULL pointer");
   hipStream_t s = (hipStream_t)stream;
-  if (op->perm) {  // internal order: lam and u through the operator's work vectors
-    permute_in<double>(op->ncomp, op->nglobal, op->perm, lam, op->r, s);
-    permute_in<double>(op->ncomp, op->nglobal, op->perm, u, op->pv, s);
-    lam = op->r;
-    u = op->pv;
-  }
   return launch_grad_kappa(op, lam, u, g, s);
 }
 
@@ -1120,27 +1102,16 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
   hipStream_t s = (hipStream_t)stream;
   const int nc = op->ncomp;
   const int64_t n = op->nglobal, nv = n * nc;
-  // d = u - u_target in the internal order, in the operator's work vector r
-  if (op->perm) {
-    permute_in<double>(nc, n, op->perm, u, op->r, s);
-    permute_in<double>(nc, n, op->perm, u_target, op->pv, s);
-    difference(op->r, op->pv, op->r, nv, s);
-  } else {
-    difference(u, u_target, op->r, nv, s);
-  }
+  // d = u - u_target in the operator's work vector r
+  difference(u, u_target, op->r, nv, s);
   // M d (unmasked) with the element energies d_L^T B_L d_L per work-group
   // and component, whose sum is d^T M d
   double *pa = op->part + (vec_blocks(n) + kStage2Rows) * 3 * nc;
-  fill_f64(op->w, nv, 0.0, s);
-  rc = launch_apply(op, BP_MASS, false, op->r, op->w, false, pa, nullptr, s);
+  double *Md = grad ? grad : op->w;
+  fill_f64(Md, nv, 0.0, s);
+  rc = launch_apply(op, BP_MASS, false, caller_map(op), op->r, Md, false, pa, nullptr, s);
   if (rc) return rc;
   operator_energies(nc, pa, apply_rows(op, BP_MASS), op->sc, s);
-  if (grad) {
-    if (op->perm)
-      permute_out<double>(nc, n, op->iperm, op->w, grad, s);
-    else
-      BP_HIP(hipMemcpyAsync(grad, op->w, nv * sizeof(double), hipMemcpyDeviceToDevice, s));
-  }
   BP_HIP(hipGetLastError());
   BP_HIP(hipMemcpyAsync(op->sc_host, op->sc, sizeof(DevScalars), hipMemcpyDeviceToHost, s));
   BP_HIP(hipStreamSynchronize(s));

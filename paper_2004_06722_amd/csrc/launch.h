@@ -14,19 +14,35 @@ int64_t apply_rows(const bp_op_s *op, int which);
 int64_t apply_blocks(const bp_op_s *op);
 // partial rows that any one operator application may write (buffer sizing)
 int64_t max_partial_rows(const bp_op_s *op);
-int launch_apply(const bp_op_s *op, int which, bool f32, const void *u, void *w, bool masked,
-                 double *part, const int *done, hipStream_t s);
+// The node order of the vectors a launch reads and writes. Internal: the
+// solves' own, element-interior nodes stored by their element (own). Caller's:
+// the vectors of bp_apply, bp_diag, bp_grad_kappa and bp_mass_misfit as they
+// come, every node added. An operator launch alone is about 10% slower so, but
+// permuting u in and w out is two launches and 2 x 147 us more at p = 8,
+// E = 47,520 (bp_apply 789 -> 562 us; 17.6 -> 12 us at E = 120, p = 5).
+struct NodeMap {
+  const int32_t *idx;
+  int own;
+};
+inline NodeMap internal_map(const bp_op_s *op) { return {op->idx, op->n_owned > 0 ? 1 : 0}; }
+inline NodeMap caller_map(const bp_op_s *op) {
+  return {op->idx_c, op->idx_c == op->idx && op->n_owned > 0 ? 1 : 0};
+}
+// w, in the order of m, is clear before (the Gauss-Legendre mass overwrites it)
+int launch_apply(const bp_op_s *op, int which, bool f32, const NodeMap &m, const void *u, void *w,
+                 bool masked, double *part, const int *done, hipStream_t s);
 // mass element kernel with element-local output: op->wl (op->wl32 if f32)
 // [ncomp][nelem][p1^3] = B_L (Q u), zero at masked nodes; needs op->tr_off
 // (Gauss-Legendre operators). launch_apply(BP_MASS) runs it and then
 // gather_local; the PCG iteration fuses the gather into the residual update.
-int launch_mass_wl(const bp_op_s *op, bool f32, const void *u, bool masked, double *part,
-                   const int *done, hipStream_t s);
+int launch_mass_wl(const bp_op_s *op, bool f32, const NodeMap &m, const void *u, bool masked,
+                   double *part, const int *done, hipStream_t s);
 // w_L = A_L u_L (or B_L u_L) per element, no gather or scatter; uL and wL are
 // [ncomp][nelem][p1^3] in the precision of f32
 int launch_apply_local(const bp_op_s *op, int which, bool f32, const void *uL, void *wL,
                        hipStream_t s);
-int launch_diag(const bp_op_s *op, int which, double *d, bool masked, hipStream_t s);
+int launch_diag(const bp_op_s *op, int which, const NodeMap &m, double *d, bool masked,
+                hipStream_t s);
 // G [E][6][q^3] and Bt [E][q^3] from the node coordinates X [E][p1^3][3] (device);
 // *bad (device, preset to INT_MAX) gets the smallest element with det J <= 0
 int launch_geometry(const bp_op_s *op, const double *X, double *G, double *Bt, int *bad,
@@ -128,12 +144,12 @@ void cg_update_rxp(int64_t n, double *x, double *p, double *z, double *w, const 
                    double *part, DevScalars *sc, hipStream_t s, bool check, bool first,
                    int64_t n_own);
 
-// transposed gather Q^T w_L: w[c][g] += sum of wl[c][pos[k]] for k in
-// [off[g], off[g+1]) in ascending order (wl is [nc][nl]); skipped while
-// *done (done may be NULL)
+// transposed gather Q^T w_L: w[c][g] = sum of wl[c][pos[k]] for k in
+// [off[v], off[v+1]) in ascending order (wl is [nc][nl]), v = iperm[g] or g;
+// skipped while *done (done may be NULL)
 template <typename T>
 void gather_local(int nc, int64_t n, int64_t nl, const int32_t *off, const int32_t *pos,
-                  const T *wl, T *w, const int *done, hipStream_t s);
+                  const int32_t *iperm, const T *wl, T *w, const int *done, hipStream_t s);
 // cg_update_r with w = Q^T w_L gathered per node (no w vector is read,
 // written or cleared)
 template <typename T>
@@ -159,6 +175,9 @@ template <typename T>
 void permute_in(int nc, int64_t n, const int32_t *perm, const T *src, T *dst, hipStream_t s);
 template <typename T>
 void permute_out(int nc, int64_t n, const int32_t *iperm, const T *src, T *dst, hipStream_t s);
+// the gather map in internal ids: idx = idx_c through iperm, Dirichlet signs kept
+void map_internal(const int32_t *idx_c, const int32_t *iperm, int32_t *idx, int64_t count,
+                  hipStream_t s);
 void sr_fin(bool first, int nc, double *pv, int64_t nbv, double *pa, int64_t nba,
             DevScalars *sc, hipStream_t s);
 

@@ -838,16 +838,19 @@ __global__ __launch_bounds__(kFinThreads) void k_fin_rxp_fused(const double *__r
   }
 }
 
-// w[c][v] += Q^T w_L at node v (fixed order as above), one node per thread
+// w[c][g] = Q^T w_L at node v = iperm[g] (g itself without iperm; fixed order
+// as above), one node per thread
 template <typename T>
 __global__ __launch_bounds__(kVecThreads) void k_gather_local(
     int64_t n, int64_t nl, const int32_t *__restrict__ off, const int32_t *__restrict__ pos,
-    const T *__restrict__ wl, T *__restrict__ w, const int *__restrict__ done) {
+    const int32_t *__restrict__ iperm, const T *__restrict__ wl, T *__restrict__ w,
+    const int *__restrict__ done) {
   if (done && *done) return;
-  const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
-  if (v >= n) return;
+  const int64_t g = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  if (g >= n) return;
+  const int64_t v = iperm ? iperm[g] : g;
   const T *wc = wl + blockIdx.y * nl;
-  w[blockIdx.y * n + v] += gather_node(wc, pos, off[v], off[v + 1], (int32_t)(nl - 1));
+  w[blockIdx.y * n + g] = gather_node(wc, pos, off[v], off[v + 1], (int32_t)(nl - 1));
 }
 
 template <int NC>
@@ -1209,6 +1212,18 @@ __global__ __launch_bounds__(kVecThreads) void k_scale_mass(const double *__rest
   }
 }
 
+// idx = idx_c in internal ids (the Dirichlet sign kept)
+__global__ __launch_bounds__(kVecThreads) void k_map_internal(const int32_t *__restrict__ idx_c,
+                                                              const int32_t *__restrict__ iperm,
+                                                              int32_t *__restrict__ idx,
+                                                              int64_t count) {
+  for (int64_t k = (int64_t)blockIdx.x * kVecThreads + threadIdx.x; k < count;
+       k += (int64_t)gridDim.x * kVecThreads) {
+    const int32_t g = idx_c[k];
+    idx[k] = g >= 0 ? iperm[g] : -1 - iperm[-1 - g];
+  }
+}
+
 // Between the caller's node order and the internal one, per component, as a
 // gather (contiguous stores): dst[c][v] = src[c][map[v]].
 template <typename T>
@@ -1235,12 +1250,14 @@ void permute_out(int nc, int64_t n, const int32_t *iperm, const T *src, T *dst, 
 }
 template void permute_in<double>(int, int64_t, const int32_t *, const double *, double *,
                                  hipStream_t);
-template void permute_in<float>(int, int64_t, const int32_t *, const float *, float *,
-                                hipStream_t);
 template void permute_out<double>(int, int64_t, const int32_t *, const double *, double *,
                                   hipStream_t);
-template void permute_out<float>(int, int64_t, const int32_t *, const float *, float *,
-                                 hipStream_t);
+
+void map_internal(const int32_t *idx_c, const int32_t *iperm, int32_t *idx, int64_t count,
+                  hipStream_t s) {
+  hipLaunchKernelGGL(k_map_internal, dim3(grid_blocks(count)), dim3(kVecThreads), 0, s, idx_c,
+                     iperm, idx, count);
+}
 
 int64_t vec_blocks(int64_t n) {
   const int64_t b = (n + kVecThreads - 1) / kVecThreads;
@@ -1558,9 +1575,9 @@ void cg_update_xp(int nc, int64_t n, T *x, T *p, const T *z, DevScalars *sc, hip
 
 template <typename T>
 void gather_local(int nc, int64_t n, int64_t nl, const int32_t *off, const int32_t *pos,
-                  const T *wl, T *w, const int *done, hipStream_t s) {
+                  const int32_t *iperm, const T *wl, T *w, const int *done, hipStream_t s) {
   hipLaunchKernelGGL((k_gather_local<T>), dim3(vec_blocks(n), nc), dim3(kVecThreads), 0, s, n, nl,
-                     off, pos, wl, w, done);
+                     off, pos, iperm, wl, w, done);
 }
 
 template <typename T, bool NT, int NC>
@@ -1717,9 +1734,9 @@ template void cg_update_xp<double>(int, int64_t, double *, double *, const doubl
 template void cg_update_xp<float>(int, int64_t, float *, float *, const float *, DevScalars *,
                                   hipStream_t, bool);
 template void gather_local<double>(int, int64_t, int64_t, const int32_t *, const int32_t *,
-                                   const double *, double *, const int *, hipStream_t);
+                                   const int32_t *, const double *, double *, const int *, hipStream_t);
 template void gather_local<float>(int, int64_t, int64_t, const int32_t *, const int32_t *,
-                                  const float *, float *, const int *, hipStream_t);
+                                  const int32_t *, const float *, float *, const int *, hipStream_t);
 template void cg_update_r_gather<double>(int, int64_t, int64_t, double *, const double *,
                                          const int32_t *, const int32_t *, const double *,
                                          double *, DevScalars *, hipStream_t, bool);
