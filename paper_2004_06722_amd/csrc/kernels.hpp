@@ -3,10 +3,9 @@
 // Operator application w = Q^T A_L Q u (section 4) with the element operator
 // of section 5: eq. (bk5x) for the stiffness matrix and eq. (mass) for the
 // mass matrix, applied by sum factorisation (eq. (tens1)). One work-group
-// owns one element (or, for small p, a slab of elements); each thread owns
-// one (i, j) column of the element and walks the k direction in registers,
-// so the k-derivatives never leave the thread while the i- and
-// j-derivatives are taken through LDS tiles. The scatter w = Q^T w_L uses
+// owns one element (or, for small p, a slab of elements); each thread holds
+// whole pencils of the element in registers, its (i, j) column along k first,
+// and hands them over through LDS tiles. The scatter w = Q^T w_L uses
 // hardware FP64/FP32 atomic adds into a zeroed w; the local energy
 // sum_e u_L^T w_L (Appendix A1: rho = w^T u before assembly) is reduced per
 // work-group into a partial sum.
@@ -159,9 +158,118 @@ __device__ __forceinline__ int decode_index(int v, bool live, int masked) {
   return masked ? -1 : -1 - v;
 }
 
+// Even-odd tables of an NO x NI matrix M with M[NO-1-a][NI-1-i] = S M[a][i]:
+// row a < (NO+1)/2 holds E[a][i] = (M[a][i] + M[a][NI-1-i]) / 2 and
+// O[a][i] = (M[a][i] - M[a][NI-1-i]) / 2 for i < NI/2, then M[a][NI/2] when
+// NI is odd. Then for a < NO/2, with e_i = x_i + x_{NI-1-i} and
+// o_i = x_i - x_{NI-1-i}: y_a = E e + O o (+ middle term), and
+// y_{NO-1-a} = S (E e - O o (+ middle term)).
+template <int NO, int NI>
+struct EvenOdd {
+  static constexpr int H = NI / 2, HO = NO / 2, ROWS = (NO + 1) / 2, SIZE = ROWS * NI;
+  static constexpr bool MI = (NI & 1) != 0, MO = (NO & 1) != 0;
+};
+
+// Folded input pencil: mirrored sums and differences, and the middle entry.
+template <int NI, typename T>
+struct Folded {
+  T e[NI / 2 > 0 ? NI / 2 : 1], o[NI / 2 > 0 ? NI / 2 : 1], m;
+};
+
+template <int NI, typename T>
+__device__ __forceinline__ Folded<NI, T> fold(const T (&x)[NI]) {
+  Folded<NI, T> f;
+#pragma unroll
+  for (int i = 0; i < NI / 2; ++i) {
+    f.e[i] = x[i] + x[NI - 1 - i];
+    f.o[i] = x[i] - x[NI - 1 - i];
+  }
+  f.m = (NI & 1) ? x[NI / 2] : T(0);
+  return f;
+}
+
+// Outputs a and NO-1-a of y = M x (only ya for the middle row of odd NO,
+// where one half is zero by symmetry).
+template <int NO, int NI, int S, typename T>
+__device__ __forceinline__ void eo_row(const T *__restrict__ tab, int a, const Folded<NI, T> &x,
+                                       T &ya, T &yb) {
+  using E = EvenOdd<NO, NI>;
+  const T *r = tab + a * NI;
+  const bool mid = E::MO && a == E::HO;
+  T ye = 0, yo = 0;
+  if (!mid || S > 0) {
+#pragma unroll
+    for (int i = 0; i < E::H; ++i) ye += r[i] * x.e[i];
+    if constexpr (E::MI) ye += r[2 * E::H] * x.m;
+  }
+  if (!mid || S < 0) {
+#pragma unroll
+    for (int i = 0; i < E::H; ++i) yo += r[E::H + i] * x.o[i];
+  }
+  ya = ye + yo;
+  yb = S > 0 ? ye - yo : yo - ye;
+}
+
+// z = M^T v accumulated input pair by input pair: p[i] = (z_i + z_{NI-1-i})/2,
+// m[i] = (z_i - z_{NI-1-i})/2, c = z_{NI/2} (odd NI).
+template <int NI, typename T>
+struct Unfold {
+  T p[NI / 2 > 0 ? NI / 2 : 1], m[NI / 2 > 0 ? NI / 2 : 1], c;
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int i = 0; i < NI / 2; ++i) p[i] = m[i] = T(0);
+    c = T(0);
+  }
+  // inputs a and NO-1-a (a < NO/2), or the middle input alone
+  template <int NO, int S>
+  __device__ __forceinline__ void add(const T *__restrict__ tab, int a, T va, T vb) {
+    using E = EvenOdd<NO, NI>;
+    const T *r = tab + a * NI;
+    const bool mid = E::MO && a == E::HO;
+    const T sp = mid ? va : (S > 0 ? va + vb : va - vb);
+    const T sm = mid ? va : (S > 0 ? va - vb : va + vb);
+    if (!mid || S > 0) {
+#pragma unroll
+      for (int i = 0; i < E::H; ++i) p[i] += r[i] * sp;
+      if constexpr (E::MI) c += r[2 * E::H] * sp;
+    }
+    if (!mid || S < 0) {
+#pragma unroll
+      for (int i = 0; i < E::H; ++i) m[i] += r[E::H + i] * sm;
+    }
+  }
+  __device__ __forceinline__ void get(T (&z)[NI]) const {
+#pragma unroll
+    for (int i = 0; i < NI / 2; ++i) {
+      z[i] = p[i] + m[i];
+      z[NI - 1 - i] = p[i] - m[i];
+    }
+    if constexpr ((NI & 1) != 0) z[NI / 2] = c;
+  }
+};
+
+// y = M x for the NO x NI matrix of an even-odd table.
+template <int NO, int NI, int S, typename T>
+__device__ __forceinline__ void eo_apply(const T *__restrict__ tab, const T (&x)[NI],
+                                         T (&y)[NO]) {
+  const Folded<NI, T> f = fold(x);
+#pragma unroll
+  for (int a = 0; a < (NO + 1) / 2; ++a) {
+    T ya, yb;
+    eo_row<NO, NI, S>(tab, a, f, ya, yb);
+    y[a] = ya;
+    if (a < NO / 2) y[NO - 1 - a] = yb;
+  }
+}
+
+// k-planes of G that a lane holds ahead of their use: the whole column up to
+// p1 = 8, where it fits beside a component's working set; beyond, chunks, one
+// loaded while the one before is applied (see below).
+constexpr int colloc_chunk(int p1) { return p1 <= 8 ? p1 : p1 <= 11 ? 4 : 2; }
+
 // Body of the collocated stiffness kernels (described below): with MULTI
-// every component of u and w ([ncomp][cs]) runs through one work-group, G and
-// the map loaded once; otherwise the one component that u and w point at
+// every component of u and w ([ncomp][cs]) runs through one work-group, the
+// map loaded once; otherwise the one component that u and w point at
 // (energy column c0).
 template <int P1, typename T, bool LOCAL, bool HELM, bool MULTI, bool PZ = false>
 __device__ __forceinline__ void stiff_colloc_body(
@@ -169,11 +277,11 @@ __device__ __forceinline__ void stiff_colloc_body(
     const T *__restrict__ Bb, const T *__restrict__ u, T *__restrict__ w, int64_t cs, int ncomp,
     int c0, int masked, double *__restrict__ part, const int *__restrict__ done, int own,
     PZIter pz = {}) {
-  constexpr int NC = 1;  // LDS tiles of one component at a time
-  static constexpr GLLDeriv<P1, T> kD{};  // D^, compile-time constants
-  const T *const Dg = kD.D;
+  static constexpr GLLTables<P1, T> kD{};  // D^ and its transpose, compile-time constants
+  const T *const tD = kD.D, *const tDt = kD.Dt;
   using PL = Plane<P1, P1>;
-  constexpr int N3 = P1 * P1 * P1, PP = P1 * P1, PAD = P1 + 1;
+  constexpr int N3 = P1 * P1 * P1, PP = P1 * P1, RS = P1 | 1, PS = P1 * RS;
+  constexpr int KC = colloc_chunk(P1), NCH = (P1 + KC - 1) / KC;
   if (done && *done) return;
   const int t = threadIdx.x;
   const bool act = t < PL::USED;
@@ -184,12 +292,11 @@ __device__ __forceinline__ void stiff_colloc_body(
   if (PL::EPB == 1 && e >= nelem) return;  // uniform over the work-group
   const bool live = act && e < nelem;
   const int64_t ec = live ? e : nelem - 1;  // element whose data a lane reads
-
-  __shared__ T sD[P1][PAD];   // sD[a][m]  = D^[a][m]
-  __shared__ T sDt[P1][PAD];  // sDt[m][a] = D^[a][m]
-  __shared__ T su[PL::EPB][NC][P1][P1][PAD];
-  __shared__ T sr[PL::EPB][NC][P1][P1][PAD];
-  __shared__ T ss[PL::EPB][NC][P1][P1][PAD];
+  // two tiles [k][j][i] with odd rows; the lane's column, row and s-pencil in them
+  __shared__ T sx[PL::EPB][P1 * PS];
+  __shared__ T sy[PL::EPB][P1 * PS];
+  T *const X = sx[slot], *const Y = sy[slot];
+  const int oc = j * RS + i, orow = j * PS + i * RS, os = j * PS + i;
   // two-launch iteration (PZIter, one component): the scalars and the
   // partial rows of r_k.z_k and r_k.r_k are requested first
   RowPairSums<PL::THREADS> pzs;
@@ -210,7 +317,7 @@ __device__ __forceinline__ void stiff_colloc_body(
       }
     }
   }
-  // one round trip: the column of the gather map and of G
+  // one round trip: the column of the gather map and the first chunk of G
   const int32_t *ie = idx + ec * N3 + ij;
   const T *Ge = G + ec * 6 * N3 + ij;
   int gk[P1];
@@ -218,40 +325,49 @@ __device__ __forceinline__ void stiff_colloc_body(
 #pragma unroll
   for (int k = 0; k < P1; ++k)
     gk[k] = LOCAL ? (int)(ec * N3) + ij + k * PP : __builtin_nontemporal_load(ie + k * PP);
+  auto load_chunk = [&](int ch) {
 #pragma unroll
-  for (int k = 0; k < P1; ++k)
+    for (int n = 0; n < 6; ++n)
 #pragma unroll
-    for (int n = 0; n < 6; ++n) g[n][k] = __builtin_nontemporal_load(Ge + n * N3 + k * PP);
-  // Helmholtz: beta B~ at the lane's nodes (B_beta is diagonal with GLL)
+      for (int k = ch * KC; k < (ch + 1) * KC && k < P1; ++k)
+        g[n][k] = MULTI && NCH > 1 ? Ge[n * N3 + k * PP]
+                                   : __builtin_nontemporal_load(Ge + n * N3 + k * PP);
+  };
+  T un[P1];
+  if constexpr (LOCAL)  // no map to wait for: u before G
+#pragma unroll
+    for (int k = 0; k < P1; ++k) un[k] = u[gk[k]];
+  if (!(MULTI && NCH > 1)) load_chunk(0);
   T bb[HELM ? P1 : 1];
   if constexpr (HELM) {
 #pragma unroll
     for (int k = 0; k < P1; ++k) bb[k] = __builtin_nontemporal_load(Bb + ec * N3 + ij + k * PP);
   }
-
-  // decode: global id, and bit k of mb set when node k is gathered and
-  // scattered (clear for dead slots and masked Dirichlet nodes)
-  unsigned mb = 0;
+  unsigned mb = 0;  // bit k: node k is gathered and scattered
 #pragma unroll
   for (int k = 0; k < P1; ++k) {
     const int v = gk[k];
     if (live && (LOCAL || v >= 0 || !masked)) mb |= 1u << k;
     if (!LOCAL) gk[k] = v >= 0 ? v : -1 - v;
   }
-
+  // several components: the next one's column of u is requested before the
+  // current result is written, and has arrived by then, so that its wait is
+  // not queued behind those stores (loads and stores retire in one order)
+  const int nrun = MULTI ? ncomp : 1;
+  if constexpr (!LOCAL)
+#pragma unroll
+    for (int k = 0; k < P1; ++k) un[k] = u[gk[k]];
   // two-launch iteration (PZIter): z_k and p_{k-1} gathered before the
   // partial sums are finished (their loads in flight meanwhile); r_k.z_k and
   // r_k.r_k, the same in every work-group; the stopping test on r_k ends the
-  // launch in all of them at once; p_k = z_k + beta p_{k-1} at the nodes
-  T pzp[PZ ? P1 : 1], pzz[PZ ? P1 : 1];
+  // launch in all of them at once; p_k = z_k + beta p_{k-1} at the nodes, as
+  // the vector kernel forms it
   __shared__ double pzr[2];
   if constexpr (PZ) {
     static_assert(!MULTI, "the two-launch iteration runs one component");
+    T pzz[P1];
 #pragma unroll
-    for (int k = 0; k < P1; ++k) {
-      pzp[k] = u[gk[k]];
-      pzz[k] = pz.first ? T(0) : pz.z[gk[k]];
-    }
+    for (int k = 0; k < P1; ++k) pzz[k] = pz.first ? T(0) : pz.z[gk[k]];
     if (!pz.first && pz.fused) {
       pzs.finish(pz.pr, pz.nbv, pzr);
       const double bb = pz_bb > 0.0 ? pz_bb : 1.0;
@@ -272,109 +388,107 @@ __device__ __forceinline__ void stiff_colloc_body(
     }
     if (!pz.first)
 #pragma unroll
-      for (int k = 0; k < P1; ++k) pzp[k] = __builtin_fma(pz_beta, pzp[k], pzz[k]);
+      for (int k = 0; k < P1; ++k) un[k] = __builtin_fma(pz_beta, un[k], pzz[k]);
   }
-
-  const int nrun = MULTI ? ncomp : 1;
 #pragma unroll 1
   for (int cc = 0; cc < nrun; ++cc) {
-    const T *uc = u + (MULTI ? cc * cs : 0);
     T *wc = w + (MULTI ? cc * cs : 0);
-    // gather u (PZ: p_k, formed above as the vector kernel forms it)
-    T ru[NC][P1];
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int k = 0; k < P1; ++k) {
-        const T v = PZ ? pzp[PZ ? k : 0] : uc[gk[k]];
-        ru[c][k] = (mb >> k & 1u) ? v : T(0);
-      }
-    if (cc == 0) {
-      // D^ staged after the first gather is requested, so both wait together
-      for (int x = t; x < PP; x += PL::THREADS) {
-        sD[x / P1][x % P1] = Dg[x];
-        sDt[x % P1][x / P1] = Dg[x];
-      }
-    } else {
-      __syncthreads();  // the tiles of the previous component have been read
-    }
-
-    // u into LDS; derivative along t (k) in registers
-    T rt[NC][P1];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
+    T rt[P1], h[HELM ? P1 : 1];
+    double en = 0.0;
+    if (MULTI && NCH > 1) load_chunk(0);
+    {
+      T ru[P1];
 #pragma unroll
       for (int k = 0; k < P1; ++k) {
-        if (act) su[slot][c][k][j][i] = ru[c][k];
-        T s = 0;
-#pragma unroll
-        for (int m = 0; m < P1; ++m) s += Dg[k * P1 + m] * ru[c][m];
-        rt[c][k] = s;
+        ru[k] = (mb >> k & 1u) ? un[k] : T(0);
+        if (act) X[oc + k * PS] = ru[k];
+        if constexpr (HELM) {
+          h[k] = bb[k] * ru[k];
+          if (act) en += (double)ru[k] * (double)h[k];
+        }
       }
+      eo_apply<P1, P1, -1>(tD, ru, rt);  // along t (k)
     }
     __syncthreads();
-
-    // derivatives along r, s through LDS; apply G; energy at the points
-    double en[NC];
+    {  // along r (rows into Y) and along s (in place of u, once every row is read)
+      T x[P1], y[P1];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) en[c] = 0.0;
-    if constexpr (HELM) {
-      if (act)
+      for (int m = 0; m < P1; ++m) x[m] = X[orow + m];
+      eo_apply<P1, P1, -1>(tD, x, y);
 #pragma unroll
-        for (int k = 0; k < P1; ++k) en[0] += (double)ru[0][k] * (double)(bb[k] * ru[0][k]);
+      for (int m = 0; m < P1; ++m)
+        if (act) Y[orow + m] = y[m];
+#pragma unroll
+      for (int m = 0; m < P1; ++m) x[m] = X[os + m * RS];
+      eo_apply<P1, P1, -1>(tD, x, y);
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < P1; ++m)
+        if (act) X[os + m * RS] = y[m];
     }
+    if constexpr (MULTI) {  // unconditional (the last component re-reads its own)
+      const T *up = u + (cc + 1 < nrun ? cc + 1 : cc) * cs;
 #pragma unroll
-    for (int k = 0; k < P1; ++k) {
+      for (int k = 0; k < P1; ++k) un[k] = up[gk[k]];
+    }
+    __syncthreads();
+    // G at the points of the column; energy
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        T ur = 0, us = 0;
+    for (int ch = 0; ch < NCH; ++ch) {
+      if (ch + 1 < NCH) load_chunk(ch + 1);
 #pragma unroll
-        for (int m = 0; m < P1; ++m) {
-          ur += sD[i][m] * su[slot][c][k][j][m];
-          us += sD[j][m] * su[slot][c][k][m][i];
-        }
-        const T ut = rt[c][k];
+      for (int k = ch * KC; k < (ch + 1) * KC && k < P1; ++k) {
+        const T ur = Y[oc + k * PS], us = X[oc + k * PS], ut = rt[k];
         const T vr = g[0][k] * ur + g[1][k] * us + g[2][k] * ut;
         const T vs = g[1][k] * ur + g[3][k] * us + g[4][k] * ut;
         const T vt = g[2][k] * ur + g[4][k] * us + g[5][k] * ut;
         // idle lanes of a partly used wave read another element's tile: no energy
-        if (act)
-          en[c] += (double)ur * (double)vr + (double)us * (double)vs + (double)ut * (double)vt;
-        rt[c][k] = vt;
         if (act) {
-          sr[slot][c][k][j][i] = vr;
-          ss[slot][c][k][j][i] = vs;
+          en += (double)ur * (double)vr + (double)us * (double)vs + (double)ut * (double)vt;
+          Y[oc + k * PS] = vr;
+          X[oc + k * PS] = vs;
         }
+        rt[k] = vt;
       }
     }
     __syncthreads();
-
-    // transposed derivatives and scatter
+    {  // transposed derivatives along r and s, in place
+      T x[P1], y[P1];
+#pragma unroll
+      for (int m = 0; m < P1; ++m) x[m] = Y[orow + m];
+      eo_apply<P1, P1, -1>(tDt, x, y);
+#pragma unroll
+      for (int m = 0; m < P1; ++m)
+        if (act) Y[orow + m] = y[m];
+#pragma unroll
+      for (int m = 0; m < P1; ++m) x[m] = X[os + m * RS];
+      eo_apply<P1, P1, -1>(tDt, x, y);
+#pragma unroll
+      for (int m = 0; m < P1; ++m)
+        if (act) X[os + m * RS] = y[m];
+    }
+    T wt[P1];
+    eo_apply<P1, P1, -1>(tDt, rt, wt);  // along t
+    __syncthreads();
+    if constexpr (MULTI)
+#pragma unroll
+      for (int k = 0; k < P1; ++k) asm volatile("" : "+v"(un[k]));  // waited for here
 #pragma unroll
     for (int k = 0; k < P1; ++k) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        T acc = 0;
-        if constexpr (HELM) acc = bb[k] * su[slot][c][k][j][i];
-#pragma unroll
-        for (int m = 0; m < P1; ++m) {
-          acc += Dg[m * P1 + k] * rt[c][m];
-          acc += sDt[i][m] * sr[slot][c][k][j][m];
-          acc += sDt[j][m] * ss[slot][c][k][m][i];
-        }
-        if (mb >> k & 1u) {
-          if (LOCAL || (own && interior_node<P1>(i, j, k)))
-            // element-local output, or a node of this element alone (streamed:
-            // nothing reads it again in this launch)
-            __builtin_nontemporal_store(acc, wc + gk[k]);
-          else
-            atomic_add(wc + gk[k], acc);
-        }
+      T acc = wt[k] + Y[oc + k * PS] + X[oc + k * PS];
+      if constexpr (HELM) acc += h[k];
+      if (mb >> k & 1u) {
+        if (LOCAL || (own && interior_node<P1>(i, j, k)))
+          __builtin_nontemporal_store(acc, wc + gk[k]);
+        else
+          atomic_add(wc + gk[k], acc);
       }
     }
-    if (part)
-      block_sum_store<NC, PL::THREADS>(en, part + (int64_t)blockIdx.x * ncomp +
-                                               (MULTI ? cc : c0), 1);
+    if (part) {
+      double ev[1] = {en};
+      block_sum_store<1, PL::THREADS>(ev, part + (int64_t)blockIdx.x * ncomp + (MULTI ? cc : c0),
+                                      1);
+    }
   }
 }
 
@@ -388,29 +502,36 @@ __device__ __forceinline__ void stiff_colloc_body(
 // one after the other (BK6 and the vector problems), with at most 256
 // registers per lane so that two waves share each SIMD.
 //
-// Arithmetic is not the limit (HBM traffic and the rate of the atomic
-// scatter are), so the kernel is laid out to need few dependent round trips:
-// each lane requests its whole column of G (6 x p1 values) and of the gather
-// map at entry, then gathers u, then computes from registers and LDS. The k direction stays in registers; the r and s contractions go
-// through LDS tiles. Loads are branch-free: an element slot past the end
-// reads the last element and a Dirichlet node reads its (valid) global
-// entry, both masked. D^ is a compile-time table (rules1d.hpp): entries
-// with compile-time indices are immediates, which the compiler rematerialises
-// in each component of the loop instead of keeping them in scalar registers;
-// the lane-dependent rows come from LDS. The local energy u_L^T A_L u_L is
-// accumulated at the quadrature points as (D u)^T G (D u) = u_L^T w_L.
+// What bounds it: HBM traffic at p1 = 7, 8 and E large; below, the atomic
+// scatter; above, with one thread per node and rows read through LDS (3 + 4 p1
+// accesses per node), the LDS pipe and two waves per SIMD did. So each lane
+// takes whole pencils of the element in registers instead, as the
+// Gauss-Legendre kernels do: the column (i, j) along t, the row (j, k) along r,
+// the pencil (i, k) along s, with the even-odd splitting (D^ is
+// centro-antisymmetric), and two LDS tiles hand the pencils over: 15 accesses
+// per node. Loads come in few dependent round trips: the map and the first
+// chunk of G at entry, then u, then the further chunks one ahead of their use.
+// Chunks of 4 planes leave registers for three waves per SIMD at p1 = 9..11,
+// chunks of 2 (p1 >= 12, two waves) for no spills. Loads are branch-free: an
+// element slot past the end reads the last element and a Dirichlet node reads
+// its (valid) global entry, both masked. D^ is a compile-time table
+// (rules1d.hpp). The local energy u_L^T A_L u_L is accumulated at the
+// quadrature points as (D u)^T G (D u) = u_L^T w_L.
+// Several components: the next one's column of u is requested before the
+// current result is written and waited for there, so that its wait is not
+// queued behind those stores (loads and stores retire in one order). G stays in
+// registers up to p1 = 8 and is read again per component at p1 = 9..11.
 // HELM adds the Helmholtz term of eq. (hm2): with collocated GLL points the
 // mass matrix is diagonal, so w_L += (beta B~) u_L node by node, with the
 // beta-scaled B~ read beside G (one more word per point). With the internal
 // node order (own) the element-interior nodes are stored, not added.
+// Measured (us, FP64, operator alone, one thread per node -> pencils): p1 = 7
+// E = 52^3 710 -> 651, p1 = 8 E = 41x37x29 259 -> 245, p1 = 9 E = 36x36x33 416 ->
+// 378, p1 = 10 E = 24^3 214 -> 177, p1 = 12 E = 6120 239 -> 131, p1 = 14
+// E = 3584 290 -> 131, p1 = 16 E = 2352 254 -> 118; element-local p1 = 12 189 -> 112;
+// three components p1 = 8 E = 41x37x29 597 -> 520, p1 = 10 E = 24^3 641 -> 370.
+// At least two waves per SIMD are asked for (it binds from p1 = 12 in FP64).
 // ---------------------------------------------------------------------------
-// Two waves per SIMD requested: it binds only from p1 = 11 in FP64 (the
-// p1 <= 10 and FP32 instances compile to the same code with or without it),
-// where the compiler otherwise let the register count pass 256 (p1 = 14) or
-// scheduled the same 252 registers differently (p1 = 13) (BK5 alone, N = 12:
-// 7.2 -> 10.0 TFLOP/s, N = 13: 7.3 -> 8.6;
-// BP5 iteration at N = 11: 2.09 -> 1.69 ms, N = 12: 2.53 -> 2.46 ms, E = 2^15),
-// at the cost of a few spilled registers at p1 = 13, 14.
 template <int P1, typename T, bool LOCAL = false, bool HELM = false>
 __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) __attribute__((amdgpu_waves_per_eu(2))) void k_stiff_colloc(
     int64_t nelem, const int32_t *__restrict__ idx, const T *__restrict__ G,
@@ -527,96 +648,6 @@ __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) void k_mass_colloc(
 // a gather kernel after the launch).
 // ---------------------------------------------------------------------------
 enum GLMode { kGLMass = 0, kGLStiff = 1, kGLHelm = 2 };
-
-// Even-odd tables of an NO x NI matrix M with M[NO-1-a][NI-1-i] = S M[a][i]:
-// row a < (NO+1)/2 holds E[a][i] = (M[a][i] + M[a][NI-1-i]) / 2 and
-// O[a][i] = (M[a][i] - M[a][NI-1-i]) / 2 for i < NI/2, then M[a][NI/2] when
-// NI is odd. Then for a < NO/2, with e_i = x_i + x_{NI-1-i} and
-// o_i = x_i - x_{NI-1-i}: y_a = E e + O o (+ middle term), and
-// y_{NO-1-a} = S (E e - O o (+ middle term)).
-template <int NO, int NI>
-struct EvenOdd {
-  static constexpr int H = NI / 2, HO = NO / 2, ROWS = (NO + 1) / 2, SIZE = ROWS * NI;
-  static constexpr bool MI = (NI & 1) != 0, MO = (NO & 1) != 0;
-};
-
-// Folded input pencil: mirrored sums and differences, and the middle entry.
-template <int NI, typename T>
-struct Folded {
-  T e[NI / 2 > 0 ? NI / 2 : 1], o[NI / 2 > 0 ? NI / 2 : 1], m;
-};
-
-template <int NI, typename T>
-__device__ __forceinline__ Folded<NI, T> fold(const T (&x)[NI]) {
-  Folded<NI, T> f;
-#pragma unroll
-  for (int i = 0; i < NI / 2; ++i) {
-    f.e[i] = x[i] + x[NI - 1 - i];
-    f.o[i] = x[i] - x[NI - 1 - i];
-  }
-  f.m = (NI & 1) ? x[NI / 2] : T(0);
-  return f;
-}
-
-// Outputs a and NO-1-a of y = M x (only ya for the middle row of odd NO,
-// where one half is zero by symmetry).
-template <int NO, int NI, int S, typename T>
-__device__ __forceinline__ void eo_row(const T *__restrict__ tab, int a, const Folded<NI, T> &x,
-                                       T &ya, T &yb) {
-  using E = EvenOdd<NO, NI>;
-  const T *r = tab + a * NI;
-  const bool mid = E::MO && a == E::HO;
-  T ye = 0, yo = 0;
-  if (!mid || S > 0) {
-#pragma unroll
-    for (int i = 0; i < E::H; ++i) ye += r[i] * x.e[i];
-    if constexpr (E::MI) ye += r[2 * E::H] * x.m;
-  }
-  if (!mid || S < 0) {
-#pragma unroll
-    for (int i = 0; i < E::H; ++i) yo += r[E::H + i] * x.o[i];
-  }
-  ya = ye + yo;
-  yb = S > 0 ? ye - yo : yo - ye;
-}
-
-// z = M^T v accumulated input pair by input pair: p[i] = (z_i + z_{NI-1-i})/2,
-// m[i] = (z_i - z_{NI-1-i})/2, c = z_{NI/2} (odd NI).
-template <int NI, typename T>
-struct Unfold {
-  T p[NI / 2 > 0 ? NI / 2 : 1], m[NI / 2 > 0 ? NI / 2 : 1], c;
-  __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int i = 0; i < NI / 2; ++i) p[i] = m[i] = T(0);
-    c = T(0);
-  }
-  // inputs a and NO-1-a (a < NO/2), or the middle input alone
-  template <int NO, int S>
-  __device__ __forceinline__ void add(const T *__restrict__ tab, int a, T va, T vb) {
-    using E = EvenOdd<NO, NI>;
-    const T *r = tab + a * NI;
-    const bool mid = E::MO && a == E::HO;
-    const T sp = mid ? va : (S > 0 ? va + vb : va - vb);
-    const T sm = mid ? va : (S > 0 ? va - vb : va + vb);
-    if (!mid || S > 0) {
-#pragma unroll
-      for (int i = 0; i < E::H; ++i) p[i] += r[i] * sp;
-      if constexpr (E::MI) c += r[2 * E::H] * sp;
-    }
-    if (!mid || S < 0) {
-#pragma unroll
-      for (int i = 0; i < E::H; ++i) m[i] += r[E::H + i] * sm;
-    }
-  }
-  __device__ __forceinline__ void get(T (&z)[NI]) const {
-#pragma unroll
-    for (int i = 0; i < NI / 2; ++i) {
-      z[i] = p[i] + m[i];
-      z[NI - 1 - i] = p[i] - m[i];
-    }
-    if constexpr ((NI & 1) != 0) z[NI / 2] = c;
-  }
-};
 
 // LDS layout and elements per work-group of the Gauss-Legendre kernels: up
 // to 256 threads (q^2 per element) and at most 80 KB of LDS per work-group,

@@ -37,17 +37,17 @@ int64_t vec_stride(const bp_op_s *op) {
   return LOCAL ? op->nelem * op->p1 * op->p1 * op->p1 : op->nglobal;
 }
 
-// Several components up to p = 7 (p = 6 with the Helmholtz term): one launch
-// of k_stiff_colloc_nc (G and the map read once per element for all of
-// them). Beyond, G beside a component's working set no longer fits 256
-// registers (the multi-component kernel spills), so each component gets its
+// Several components up to p = 10 (p = 8 with the Helmholtz term): one launch
+// of k_stiff_colloc_nc (the map read once per element for all of them, G from
+// HBM once). Beyond, the multi-component kernel spills (p1 = 12, three
+// components, E = 6120: 444 us against 3 x 131), so each component gets its
 // own launch.
 template <int P1, typename T, bool LOCAL, bool HELM>
 int stiff_colloc(const bp_op_s *op, const NodeMap &m, const T *G, const T *Bb, const T *u, T *w,
                  int masked, double *part, const int *done, hipStream_t s) {
   using PL = Plane<P1, P1>;
   const int64_t cs = vec_stride<LOCAL>(op);
-  if constexpr (P1 <= (HELM ? 7 : 8)) {
+  if constexpr (P1 <= (HELM ? 9 : 11)) {
     if (op->ncomp > 1) {
       hipLaunchKernelGGL((k_stiff_colloc_nc<P1, T, LOCAL, HELM>), dim3(apply_blocks(op)),
                          dim3(PL::THREADS), 0, s, op->nelem, m.idx, G, Bb, u, w, cs,

@@ -215,6 +215,25 @@ struct GLTables {
   }
 };
 
+// Compile-time even-odd tables of D^ on the p1 GLL nodes and of its transpose
+// (collocated quadrature; both are centro-antisymmetric), in the type T.
+template <int P1, typename T>
+struct GLLTables {
+  static constexpr int SIZE = ((P1 + 1) / 2) * P1;
+  T D[SIZE], Dt[SIZE];
+  constexpr GLLTables() : D(), Dt() {
+    double xi[P1] = {}, M[P1 * P1] = {}, Mt[P1 * P1] = {}, t[SIZE] = {};
+    gll_rule(P1, xi, nullptr);
+    lagrange_deriv(P1, xi, P1, xi, M);
+    for (int a = 0; a < P1; ++a)
+      for (int m = 0; m < P1; ++m) Mt[m * P1 + a] = M[a * P1 + m];
+    even_odd_table(M, P1, P1, -1, t);
+    for (int i = 0; i < SIZE; ++i) D[i] = static_cast<T>(t[i]);
+    even_odd_table(Mt, P1, P1, -1, t);
+    for (int i = 0; i < SIZE; ++i) Dt[i] = static_cast<T>(t[i]);
+  }
+};
+
 // Compile-time D^ on the p1 GLL nodes (collocated quadrature: the points
 // are the nodes), row-major D[a * p1 + m] = l_m'(xi_a), in the type T.
 template <int P1, typename T>

@@ -105,3 +105,24 @@ def test_orders_outside_the_compiled_range_are_rejected():
             c.op.grad_kappa(z, z)
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("p", range(7, 12))
+@pytest.mark.parametrize("ncomp", [2, 5])
+def test_several_components_around_the_one_launch_order(p, ncomp):
+    # one launch for all components up to p = 10 (p = 8 with the Helmholtz
+    # term), one per component beyond: stiffness and Helmholtz assembled, stiffness
+    # element-local
+    c = Case(6, p, 2, 2, 1, seed=110 + p, ncomp=ncomp)
+    try:
+        beta = np.random.default_rng(p).uniform(0.5, 3.0, size=(c.disc.E, c.q ** 3))
+        c.op.set_helmholtz(0.0, torch.tensor(beta, device="cuda"))
+        hd = Discretization(c.disc.rule, c.mesh.elem_dofs, c.mesh.node_xyz, c.disc.nglobal,
+                            c.dir, beta=beta)
+        u = c.vec(111 + p)
+        for which, d in ((STIFF, c.disc), (HELM, hd)):
+            assert rel(host(c.op.apply(which, dev(u))), d.apply(which, u)) <= TOL, which
+        uL = local_input(c, 112 + p, ncomp)
+        assert rel(run_local(c.op, STIFF, uL), oracle_local(c.disc, STIFF, uL)) <= TOL
+    finally:
+        c.close()
