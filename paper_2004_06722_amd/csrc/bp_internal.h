@@ -104,6 +104,9 @@ struct bp_op_s {
   double *basis_d = nullptr; // J | D | Dq on the device (FP64)
   double *Bb = nullptr;      // beta_q * B~ (allocated by bp_set_helmholtz; NULL: beta = 0)
   float *G32 = nullptr, *Gk32 = nullptr, *Bt32 = nullptr, *Bb32 = nullptr, *basis32 = nullptr;
+  // collocated operators: the assembled mass matrix, a diagonal, per caller's
+  // node; negative on Dirichlet nodes
+  double *md = nullptr;
   bool kappa_set = false;
   // inverse diagonals: [0] mass, [1] stiffness (masked), [2] Helmholtz (masked)
   double *dinv[3] = {nullptr, nullptr, nullptr};

@@ -71,6 +71,7 @@ void release(bp_op op) {
   dfree(op->basis32);
   dfree(op->Bb);
   dfree(op->Bb32);
+  dfree(op->md);
   dfree(op->dinv[0]);
   dfree(op->dinv[1]);
   dfree(op->dinv[2]);
@@ -787,6 +788,14 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   TRY(dmalloc(&op->part, op->part_len));
   TRY(dmalloc(&op->sc, 1));
   TRYHIP(hipHostMalloc((void **)&op->sc_host, sizeof(DevScalars), hipHostMallocDefault));
+  if (op->colloc) {  // the assembled mass matrix (its unmasked diagonal)
+    TRY(dmalloc(&op->md, nglobal));
+    fill_f64(op->md, nglobal, 0.0, s);
+    TRY(launch_diag(op, BP_MASS, caller_map(op), op->md, false, s));
+    mark_dirichlet(op->idx_c, nelem * n3, op->md, s);
+    TRYHIP(hipGetLastError());
+    TRYHIP(hipStreamSynchronize(s));
+  }
   // timing events: no system-scope fence on record (no cache writeback and
   // invalidation around the timed work; the solves synchronise the stream
   // themselves before reading them)
@@ -895,6 +904,14 @@ int bp_apply(bp_op op, int which, int prec, const void *u, void *w, unsigned fla
   hipStream_t s = (hipStream_t)stream;
   const int64_t nv = op->nglobal * op->ncomp;
   const bool f32 = prec == BP_FP32, masked = (flags & BP_MASKED) != 0;
+  if (which == BP_MASS && op->colloc) {
+    if (f32)
+      mass_diagonal(op->ncomp, op->nglobal, op->md, (const float *)u, (float *)w, masked, s);
+    else
+      mass_diagonal(op->ncomp, op->nglobal, op->md, (const double *)u, (double *)w, masked, s);
+    BP_HIP(hipGetLastError());
+    return BP_OK;
+  }
   if (which == BP_MASS && op->tr_off)
     ;  // overwrites w
   else if (f32)
@@ -1102,16 +1119,21 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
   hipStream_t s = (hipStream_t)stream;
   const int nc = op->ncomp;
   const int64_t n = op->nglobal, nv = n * nc;
-  // d = u - u_target in the operator's work vector r
-  difference(u, u_target, op->r, nv, s);
-  // M d (unmasked) with the element energies d_L^T B_L d_L per work-group
-  // and component, whose sum is d^T M d
+  // M d (unmasked) and d^T M d: with collocated points one pass with the
+  // diagonal M; else the operator on d, held in the work vector r, with the
+  // element energies d_L^T B_L d_L per work-group and component
   double *pa = op->part + (vec_blocks(n) + kStage2Rows) * 3 * nc;
-  double *Md = grad ? grad : op->w;
-  fill_f64(Md, nv, 0.0, s);
-  rc = launch_apply(op, BP_MASS, false, caller_map(op), op->r, Md, false, pa, nullptr, s);
-  if (rc) return rc;
-  operator_energies(nc, pa, apply_rows(op, BP_MASS), op->sc, s);
+  if (op->colloc) {
+    misfit_diagonal(nc, n, op->md, u, u_target, grad, op->part, s);
+    operator_energies(nc, op->part, vec_blocks(n), op->sc, s);
+  } else {
+    difference(u, u_target, op->r, nv, s);
+    double *Md = grad ? grad : op->w;
+    fill_f64(Md, nv, 0.0, s);
+    rc = launch_apply(op, BP_MASS, false, caller_map(op), op->r, Md, false, pa, nullptr, s);
+    if (rc) return rc;
+    operator_energies(nc, pa, apply_rows(op, BP_MASS), op->sc, s);
+  }
   BP_HIP(hipGetLastError());
   BP_HIP(hipMemcpyAsync(op->sc_host, op->sc, sizeof(DevScalars), hipMemcpyDeviceToHost, s));
   BP_HIP(hipStreamSynchronize(s));

@@ -1120,19 +1120,113 @@ __global__ __launch_bounds__(256) void k_geometry(int64_t nelem, int p1, int q, 
 }
 
 // ---------------------------------------------------------------------------
+// Diagonal of a collocated operator: with J^ = I
+//   diag(A^e)_ijk = sum_a D_ai^2 G_11(a,j,k) + sum_b D_bj^2 G_22(i,b,k)
+//                 + sum_c D_ck^2 G_33(i,j,c)
+//                 + 2 (D_ii D_jj G_12 + D_ii D_kk G_13 + D_jj D_kk G_23)(i,j,k),
+// whose last line vanishes off the element's edges (D_ii = 0 at interior
+// points), plus beta B~ (Helmholtz), or B~ alone (mass). Lanes and tiles as the
+// stiffness kernel's: G_33 along the column in registers, G_11 and G_22 through
+// one tile each; half of G is read, once. Scatter-added into d.
+// Bound by the additions: 134 us at p = 5, E = 32^3, where six passes over G
+// with runtime sizes (k_diag, now for the Gauss-Legendre operators alone) took
+// 404 us.
+// ---------------------------------------------------------------------------
+template <int P1, bool STIFF>
+__global__ __launch_bounds__((Plane<P1, P1>::THREADS)) void k_diag_colloc(
+    int64_t nelem, const int32_t *__restrict__ idx, const double *__restrict__ G,
+    const double *__restrict__ Bq, double *__restrict__ d, int masked) {
+  using PL = Plane<P1, P1>;
+  static constexpr GLLSquares<P1> kS{};
+  constexpr int N3 = P1 * P1 * P1, PP = P1 * P1, RS = P1 | 1, PS = P1 * RS, LAST = P1 - 1;
+  const int t = threadIdx.x;
+  const bool act = t < PL::USED;
+  const int slot = act ? t / PL::N : 0;
+  const int ij = t % PL::N;
+  const int i = ij % P1, j = ij / P1;
+  const int64_t e = (int64_t)blockIdx.x * PL::EPB + slot;
+  const bool live = act && e < nelem;
+  const int64_t ec = live ? e : nelem - 1;
+  __shared__ double sx[STIFF ? PL::EPB : 1][STIFF ? P1 * PS : 1];
+  __shared__ double sy[STIFF ? PL::EPB : 1][STIFF ? P1 * PS : 1];
+  int v[P1];
+#pragma unroll
+  for (int k = 0; k < P1; ++k) v[k] = idx[ec * N3 + ij + k * PP];
+  double acc[P1];
+#pragma unroll
+  for (int k = 0; k < P1; ++k) acc[k] = Bq ? Bq[ec * N3 + ij + k * PP] : 0.0;
+  if constexpr (STIFF) {
+    const double *Ge = G + ec * 6 * N3 + ij;
+    double *const X = sx[slot], *const Y = sy[slot];
+    const int oc = j * RS + i, orow = j * PS + i * RS, os = j * PS + i;
+    double x[P1], y[P1];
+#pragma unroll
+    for (int k = 0; k < P1; ++k) {
+      const double g0 = Ge[k * PP], g3 = Ge[3 * N3 + k * PP];
+      x[k] = Ge[5 * N3 + k * PP];
+      if (act) {
+        X[oc + k * PS] = g0;
+        Y[oc + k * PS] = g3;
+      }
+    }
+    eo_apply<P1, P1, 1>(kS.D2t, x, y);
+    // D_ii is +-D_pp at the ends of a direction and 0 between
+    const double di = i == 0 ? kS.diag[0] : i == LAST ? kS.diag[LAST] : 0.0;
+    const double dj = j == 0 ? kS.diag[0] : j == LAST ? kS.diag[LAST] : 0.0;
+    const bool ei = i == 0 || i == LAST, ej = j == 0 || j == LAST;
+#pragma unroll
+    for (int k = 0; k < P1; ++k) {
+      acc[k] += y[k];
+      if (ei && ej) acc[k] += 2.0 * di * dj * Ge[1 * N3 + k * PP];
+    }
+    if (ei) {
+      acc[0] += 2.0 * di * kS.diag[0] * Ge[2 * N3];
+      acc[LAST] += 2.0 * di * kS.diag[LAST] * Ge[2 * N3 + LAST * PP];
+    }
+    if (ej) {
+      acc[0] += 2.0 * dj * kS.diag[0] * Ge[4 * N3];
+      acc[LAST] += 2.0 * dj * kS.diag[LAST] * Ge[4 * N3 + LAST * PP];
+    }
+    __syncthreads();
+    // along r and s, in place
+#pragma unroll
+    for (int m = 0; m < P1; ++m) x[m] = X[orow + m];
+    eo_apply<P1, P1, 1>(kS.D2t, x, y);
+#pragma unroll
+    for (int m = 0; m < P1; ++m)
+      if (act) X[orow + m] = y[m];
+#pragma unroll
+    for (int m = 0; m < P1; ++m) x[m] = Y[os + m * RS];
+    eo_apply<P1, P1, 1>(kS.D2t, x, y);
+#pragma unroll
+    for (int m = 0; m < P1; ++m)
+      if (act) Y[os + m * RS] = y[m];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < P1; ++k) acc[k] += X[oc + k * PS] + Y[oc + k * PS];
+  }
+#pragma unroll
+  for (int k = 0; k < P1; ++k) {
+    const int g = decode_index(v[k], live, masked);
+    if (g >= 0) atomic_add(d + g, acc[k]);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Diagonal of the assembled operator (Jacobi preconditioner, section 3).
 // diag(A^e)_{ijk} = sum_{mm'} sum_{abc} G_mm'(a,b,c) phi_m phi_m' with
 // phi_1 = D[a][i] J[b][j] J[c][k], phi_2 = J[a][i] D[b][j] J[c][k],
 // phi_3 = J[a][i] J[b][j] D[c][k]; mass: sum B~ J[a][i]^2 J[b][j]^2 J[c][k]^2.
 // Sum-factorised per element (contract a, then b, then c), scatter-added.
 // Runtime sizes; dynamic LDS of q^3 + q^2 p1 + q p1^2 + p1^3 + 2 q p1 values.
-// rev: the quadrature data are stored with the point index reversed.
+// Gauss-Legendre operators (the quadrature data stored with the point index
+// reversed).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_diag(int64_t nelem, int p1, int q, int stiff,
                                               const int32_t *__restrict__ idx,
                                               const double *__restrict__ Gm,
                                               const double *__restrict__ basis,
-                                              double *__restrict__ d, int masked, int rev) {
+                                              double *__restrict__ d, int masked) {
   extern __shared__ double dsm[];
   const int q3 = q * q * q, n3 = p1 * p1 * p1;
   double *sg = dsm;                // [c][b][a]      q^3
@@ -1155,7 +1249,7 @@ __global__ __launch_bounds__(256) void k_diag(int64_t nelem, int p1, int q, int 
     for (int term = 0; term < nterms; ++term) {
       const double *src = stiff ? Gm + (e * 6 + term) * q3 : Gm + e * q3;
       for (int x = t; x < q3; x += nt)
-        sg[x] = src[rev ? (x % q * q + x / q % q) * q + x / (q * q) : x];
+        sg[x] = src[(x % q * q + x / q % q) * q + x / (q * q)];
       const int m0 = stiff ? pm[term] : -1, m1 = stiff ? pn[term] : -1;
       const double fac = (stiff && m0 != m1) ? 2.0 : 1.0;
       __syncthreads();
@@ -1205,23 +1299,25 @@ __global__ __launch_bounds__(256) void k_diag(int64_t nelem, int p1, int q, int 
 
 // ---------------------------------------------------------------------------
 // Gradient with respect to the coefficient at the quadrature points
-// (collocated GLL): g_q = - sum_c (D lam_c)_q^T G_q (D u_c)_q. The thread
-// layout is that of the stiffness kernel: each lane owns an (i, j) column of
-// an element and requests its G column and map once. Per component it takes
-// the gradient of u (t in registers, r and s through one LDS tile) and forms
-// v = G (D u) at its points, then the gradient of lam through the same tile
-// and accumulates (D lam) . v, so only v, not both gradients, stays live.
-// lam and u are masked on Dirichlet nodes (those read as 0).
+// (collocated GLL): g_q = - sum_c (D lam_c)_q^T G_q (D u_c)_q. Lanes, pencils
+// and tiles are those of the stiffness kernel: each lane owns an (i, j) column
+// and requests its G column and map once. Per component it takes the gradient
+// of u and forms v = G (D u) at its points, then the gradient of lam through
+// the same tiles and accumulates (D lam) . v, so only v, not both gradients,
+// stays live; the next field's column is requested while the current one is
+// differentiated. 300 us at p = 5, E = 32^3, eight components, in the caller's
+// node order (one thread per node: 405 us in the internal order, and two
+// permutations of 158 us before it). lam and u are masked on Dirichlet nodes (those read as 0).
 // ---------------------------------------------------------------------------
 template <int P1>
-__global__ __launch_bounds__((Plane<P1, P1>::THREADS)) void k_grad_kappa_colloc(
+__global__ __launch_bounds__((Plane<P1, P1>::THREADS)) __attribute__((amdgpu_waves_per_eu(2))) void k_grad_kappa_colloc(
     int64_t nelem, const int32_t *__restrict__ idx, const double *__restrict__ G,
     const double *__restrict__ lam, const double *__restrict__ u, double *__restrict__ gout,
     int64_t cstride, int ncomp) {
   using PL = Plane<P1, P1>;
-  constexpr int N3 = P1 * P1 * P1, PP = P1 * P1, PAD = P1 + 1;
-  static constexpr GLLDeriv<P1, double> kD{};  // D^[a][m] at a * p1 + m, compile-time
-  const double *const Dg = kD.D;
+  static constexpr GLLTables<P1, double> kD{};  // D^, compile-time constants
+  const double *const tD = kD.D;
+  constexpr int N3 = P1 * P1 * P1, PP = P1 * P1, RS = P1 | 1, PS = P1 * RS;
   const int t = threadIdx.x;
   const bool act = t < PL::USED;
   const int slot = act ? t / PL::N : 0;
@@ -1230,9 +1326,10 @@ __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) void k_grad_kappa_colloc(
   const int64_t e = (int64_t)blockIdx.x * PL::EPB + slot;
   const bool live = act && e < nelem;
   const int64_t ec = live ? e : nelem - 1;  // element whose data the lane reads
-  __shared__ double sD[P1][PAD];
-  __shared__ double sx[PL::EPB][P1][P1][PAD];
-  for (int x = t; x < PP; x += PL::THREADS) sD[x / P1][x % P1] = Dg[x];
+  __shared__ double sx[PL::EPB][P1 * PS];
+  __shared__ double sy[PL::EPB][P1 * PS];
+  double *const X = sx[slot], *const Y = sy[slot];
+  const int oc = j * RS + i, orow = j * PS + i * RS, os = j * PS + i;
   int gk[P1];
   double g[6][P1];
   unsigned mb = 0;  // bit k: node k is read (live and not a Dirichlet node)
@@ -1242,44 +1339,67 @@ __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) void k_grad_kappa_colloc(
     if (live && v >= 0) mb |= 1u << k;
     gk[k] = v >= 0 ? v : -1 - v;
   }
+  // G for all components, or (p1 = 9, where it does not fit beside v) again
+  // for each
+  constexpr bool HOLD = P1 <= 8;
+  const double *Ge = G + ec * 6 * N3 + ij;
+  if constexpr (HOLD)
 #pragma unroll
-  for (int k = 0; k < P1; ++k)
+    for (int n = 0; n < 6; ++n)
 #pragma unroll
-    for (int n = 0; n < 6; ++n) g[n][k] = G[ec * 6 * N3 + n * N3 + k * PP + ij];
-  double acc[P1];
+      for (int k = 0; k < P1; ++k) g[n][k] = __builtin_nontemporal_load(Ge + n * N3 + k * PP);
+  double acc[P1], xn[P1];
 #pragma unroll
-  for (int k = 0; k < P1; ++k) acc[k] = 0.0;
+  for (int k = 0; k < P1; ++k) {
+    acc[k] = 0.0;
+    xn[k] = u[gk[k]];
+  }
+  double vr[P1], vs[P1], vt[P1];
 #pragma unroll 1
   for (int c = 0; c < ncomp; ++c) {
-    double vr[P1], vs[P1], vt[P1];
-#pragma unroll 1
+#pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-      const double *x = (pass == 0 ? u : lam) + c * cstride;
-      double r[P1], rt[P1];
+      double rt[P1];
+      {
+        double r[P1];
 #pragma unroll
-      for (int k = 0; k < P1; ++k) {
-        const double val = x[gk[k]];
-        r[k] = (mb >> k & 1u) ? val : 0.0;
+        for (int k = 0; k < P1; ++k) {
+          r[k] = (mb >> k & 1u) ? xn[k] : 0.0;
+          if (act) X[oc + k * PS] = r[k];
+        }
+        // the next field: lam of this component, then u of the next (the
+        // last component re-reads its own)
+        const double *nx = pass == 0 ? lam + c * cstride
+                                     : u + (c + 1 < ncomp ? c + 1 : c) * cstride;
+#pragma unroll
+        for (int k = 0; k < P1; ++k) xn[k] = nx[gk[k]];
+        eo_apply<P1, P1, -1>(tD, r, rt);
       }
-      __syncthreads();  // the tile's previous contents have been read
+      __syncthreads();
+      {
+        double x[P1], y[P1];
 #pragma unroll
-      for (int k = 0; k < P1; ++k) {
-        if (act) sx[slot][k][j][i] = r[k];
-        double a = 0.0;
+        for (int m = 0; m < P1; ++m) x[m] = X[orow + m];
+        eo_apply<P1, P1, -1>(tD, x, y);
 #pragma unroll
-        for (int m = 0; m < P1; ++m) a += Dg[k * P1 + m] * r[m];
-        rt[k] = a;
+        for (int m = 0; m < P1; ++m)
+          if (act) Y[orow + m] = y[m];
+#pragma unroll
+        for (int m = 0; m < P1; ++m) x[m] = X[os + m * RS];
+        eo_apply<P1, P1, -1>(tD, x, y);
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < P1; ++m)
+          if (act) X[os + m * RS] = y[m];
       }
       __syncthreads();
 #pragma unroll
       for (int k = 0; k < P1; ++k) {
-        double dr = 0.0, ds = 0.0;
-#pragma unroll
-        for (int m = 0; m < P1; ++m) {
-          dr += sD[i][m] * sx[slot][k][j][m];
-          ds += sD[j][m] * sx[slot][k][m][i];
-        }
+        const double dr = Y[oc + k * PS], ds = X[oc + k * PS];
         if (pass == 0) {
+          if constexpr (!HOLD)
+#pragma unroll
+            for (int n = 0; n < 6; ++n) g[n][k] = Ge[n * N3 + k * PP];
           vr[k] = g[0][k] * dr + g[1][k] * ds + g[2][k] * rt[k];
           vs[k] = g[1][k] * dr + g[3][k] * ds + g[4][k] * rt[k];
           vt[k] = g[2][k] * dr + g[4][k] * ds + g[5][k] * rt[k];

@@ -54,8 +54,9 @@ int launch_grad_kappa(const bp_op_s *op, const double *lam, const double *u, dou
 // CG vector kernels give each work-group kVecThreads nodes (vec_blocks; FP32
 // iteration kernels two per thread, FP64 one); fills and
 // conversions use a capped grid-stride grid (grid_blocks). Up to
-// kDirectRows block partial sums go straight to the final fixed-order
-// single-work-group sum (one launch less per reduction on small meshes);
+// kDirectRows pairs of block partial sums go straight to the final fixed-order
+// single-work-group sum (one launch less per reduction on small meshes; eight
+// columns of 16,290 rows took it 28 us);
 // more are first folded to at most kStage2Rows rows, stored right after
 // the partials.
 constexpr int kVecThreads = 256;
@@ -193,6 +194,15 @@ void cg_restart(int nc, int64_t n, T *r, T *p, const T *dinv, double *part,
 // sc->pap[c] = sum over the rows of column c of the operator's energy table
 // part[rows][nc] (fixed order); part + rows nc holds the stage-1 rows
 void operator_energies(int nc, double *part, int64_t rows, DevScalars *sc, hipStream_t s);
+// collocated mass: w = M u with the assembled diagonal md (caller's order), and
+// the misfit's gradient and energy rows [vec_blocks(n)][nc]; mark_dirichlet
+// makes md negative on the Dirichlet nodes of the map
+template <typename T>
+void mass_diagonal(int nc, int64_t n, const double *md, const T *u, T *w, bool masked,
+                   hipStream_t s);
+void misfit_diagonal(int nc, int64_t n, const double *md, const double *u, const double *ut,
+                     double *grad, double *part, hipStream_t s);
+void mark_dirichlet(const int32_t *idx, int64_t count, double *md, hipStream_t s);
 // d = a - b over count entries (d may be a)
 void difference(const double *a, const double *b, double *d, int64_t count, hipStream_t s);
 

@@ -171,6 +171,14 @@ int stiff_colloc_pz(const bp_op_s *op, const double *G, const double *p, double 
   return BP_OK;
 }
 
+template <int P1, bool STIFF>
+void diag_colloc(const bp_op_s *op, const NodeMap &m, const double *G, const double *Bq,
+                 double *d, int masked, hipStream_t s) {
+  using PL = Plane<P1, P1>;
+  hipLaunchKernelGGL((k_diag_colloc<P1, STIFF>), dim3(apply_blocks(op)), dim3(PL::THREADS), 0, s,
+                     op->nelem, m.idx, G, Bq, d, masked);
+}
+
 template <int P1>
 void grad_colloc(const bp_op_s *op, const double *lam, const double *u, double *g,
                  hipStream_t s) {
@@ -279,20 +287,35 @@ int launch_apply_local(const bp_op_s *op, int which, bool f32, const void *uL, v
 int launch_diag(const bp_op_s *op, int which, const NodeMap &m, double *d, bool masked,
                 hipStream_t s) {
   const int p1 = op->p1, q = op->q;
+  const bool stiff = which != BP_MASS, helm = which == BP_HELM && op->Bb != nullptr;
+  const double *G = op->kappa_set ? op->Gk : op->G;
+  if (op->colloc) {  // one launch: diag(A), diag(A) + beta B~ or B~
+    const double *Bq = helm ? op->Bb : stiff ? nullptr : op->Bt;
+    switch (p1) {
+#define BP_CASE(P)                                                          \
+  case P:                                                                   \
+    if (stiff)                                                              \
+      diag_colloc<P, true>(op, m, G, Bq, d, masked ? 1 : 0, s);             \
+    else                                                                    \
+      diag_colloc<P, false>(op, m, G, Bq, d, masked ? 1 : 0, s);            \
+    break;
+      BP_CASE(2) BP_CASE(3) BP_CASE(4) BP_CASE(5) BP_CASE(6) BP_CASE(7) BP_CASE(8) BP_CASE(9)
+      BP_CASE(10) BP_CASE(11) BP_CASE(12) BP_CASE(13) BP_CASE(14) BP_CASE(15) BP_CASE(16)
+#undef BP_CASE
+    }
+    BP_HIP(hipGetLastError());
+    return BP_OK;
+  }
   const size_t lds = sizeof(double) *
                      ((size_t)q * q * q + (size_t)q * q * p1 + (size_t)q * p1 * p1 +
                       (size_t)p1 * p1 * p1 + 2 * (size_t)q * p1);
   const int64_t grid = op->nelem < 65536 ? op->nelem : 65536;
-  if (lds > 65536)  // high orders: more than the default dynamic LDS per work-group
-    BP_HIP(hipFuncSetAttribute((const void *)k_diag, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds));
   // BP_HELM: diag(A) + diag(B_beta), both added into d
-  const bool helm = which == BP_HELM && op->Bb != nullptr;
   for (int part = 0; part < (helm ? 2 : 1); ++part) {
-    const bool stiff = part == 0 && which != BP_MASS;
-    const double *Gm = stiff ? (op->kappa_set ? op->Gk : op->G) : (part == 1 ? op->Bb : op->Bt);
-    hipLaunchKernelGGL(k_diag, dim3(grid), dim3(256), lds, s, op->nelem, p1, q, stiff ? 1 : 0,
-                       m.idx, Gm, op->basis_d, d, masked ? 1 : 0, op->colloc ? 0 : 1);
+    const bool st = part == 0 && stiff;
+    const double *Gm = st ? G : (part == 1 ? op->Bb : op->Bt);
+    hipLaunchKernelGGL(k_diag, dim3(grid), dim3(256), lds, s, op->nelem, p1, q, st ? 1 : 0, m.idx,
+                       Gm, op->basis_d, d, masked ? 1 : 0);
     BP_HIP(hipGetLastError());
   }
   return BP_OK;

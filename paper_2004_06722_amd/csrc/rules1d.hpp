@@ -234,16 +234,21 @@ struct GLLTables {
   }
 };
 
-// Compile-time D^ on the p1 GLL nodes (collocated quadrature: the points
-// are the nodes), row-major D[a * p1 + m] = l_m'(xi_a), in the type T.
-template <int P1, typename T>
-struct GLLDeriv {
-  T D[P1 * P1];
-  constexpr GLLDeriv() : D() {
-    double xi[P1] = {}, M[P1 * P1] = {};
+// Compile-time even-odd table of the transpose of D^ squared entry by entry
+// (centro-symmetric) and the diagonal of D^, for diag(D^T G D).
+template <int P1>
+struct GLLSquares {
+  static constexpr int SIZE = ((P1 + 1) / 2) * P1;
+  double D2t[SIZE], diag[P1];
+  constexpr GLLSquares() : D2t(), diag() {
+    double xi[P1] = {}, M[P1 * P1] = {}, S[P1 * P1] = {};
     gll_rule(P1, xi, nullptr);
     lagrange_deriv(P1, xi, P1, xi, M);
-    for (int i = 0; i < P1 * P1; ++i) D[i] = static_cast<T>(M[i]);
+    for (int a = 0; a < P1; ++a) {
+      for (int m = 0; m < P1; ++m) S[m * P1 + a] = M[a * P1 + m] * M[a * P1 + m];
+      diag[a] = M[a * P1 + a];
+    }
+    even_odd_table(S, P1, P1, 1, D2t);
   }
 };
 

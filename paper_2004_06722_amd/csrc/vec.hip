@@ -962,6 +962,58 @@ __global__ __launch_bounds__(kFinThreads) void k_fin_energy(const double *__rest
     for (int c = 0; c < NC; ++c) sc->pap[c] = res[c];
 }
 
+// w = M u per component ([nc][n], the caller's order) with the diagonal mass
+// matrix of a collocated operator: Q^T B_L Q is diagonal where B_L is, so its
+// entries are assembled once, at set-up, and an application reads u and them
+// (as atomic additions per element 671 us at p = 5, E = 32^3, eight components).
+// md < 0: a Dirichlet node.
+template <typename T>
+__global__ __launch_bounds__(kVecThreads) void k_mass_diagonal(int64_t n, int nc,
+                                                               const double *__restrict__ md,
+                                                               const T *__restrict__ u,
+                                                               T *__restrict__ w, int masked) {
+  const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  if (v >= n) return;
+  const double m = md[v];
+  // skipped nodes (masked, or in no element) read as 0 whatever u holds there
+  const bool on = masked ? m > 0.0 : m != 0.0;
+  for (int c = 0; c < nc; ++c)
+    w[c * n + v] = on ? (T)(fabs(m) * (double)u[c * n + v]) : T(0);
+}
+
+// The misfit of bp_mass_misfit with that diagonal, one pass: d = u - ut, its
+// gradient M d (unless grad is NULL) and row blockIdx.x of the energies d^T M d
+// per component. HBM-bound: 146 us at p = 5, E = 32^3, eight components (5.7
+// TB/s), where d, the operator on it and the passes between took 900 us.
+__global__ __launch_bounds__(kVecThreads) void k_misfit_diagonal(
+    int64_t n, int nc, const double *__restrict__ md, const double *__restrict__ u,
+    const double *__restrict__ ut, double *__restrict__ grad, double *__restrict__ part) {
+  const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  const bool in = v < n;
+  const double m = in ? fabs(md[v]) : 0.0;
+  for (int c = 0; c < nc; ++c) {
+    double e = 0.0;
+    if (in) {
+      const double d = u[c * n + v] - ut[c * n + v];
+      const double g = m != 0.0 ? m * d : 0.0;
+      if (grad) grad[c * n + v] = g;
+      e = m != 0.0 ? d * g : 0.0;
+    }
+    block_partial1(e, part, nc, c);
+  }
+}
+
+// md = -|md| on the Dirichlet nodes that the map marks
+__global__ __launch_bounds__(kVecThreads) void k_mark_dirichlet(const int32_t *__restrict__ idx,
+                                                                int64_t count,
+                                                                double *__restrict__ md) {
+  for (int64_t k = (int64_t)blockIdx.x * kVecThreads + threadIdx.x; k < count;
+       k += (int64_t)gridDim.x * kVecThreads) {
+    const int32_t g = idx[k];
+    if (g < 0) md[-1 - g] = -fabs(md[-1 - g]);
+  }
+}
+
 // d = a - b entry by entry (d may be a)
 __global__ __launch_bounds__(kVecThreads) void k_difference(const double *a,
                                                             const double *__restrict__ b,
@@ -1002,23 +1054,29 @@ __global__ __launch_bounds__(kVecThreads) void k_invert(const double *__restrict
 // stored reversed, [a][b][c]; 0: same order).
 __device__ __forceinline__ int64_t natural_point(int64_t qp, int qrev) {
   if (!qrev) return qp;
-  const int64_t a = qp / ((int64_t)qrev * qrev), b = qp / qrev % qrev, c = qp % qrev;
+  const int q = (int)qp, a = q / (qrev * qrev), b = q / qrev % qrev, c = q % qrev;
   return (c * qrev + b) * qrev + a;
 }
 
+// One point per thread with its six factors, kappa read once: 127 us at p = 5,
+// E = 32^3 (5.8 TB/s; one factor per thread, kappa read six times: 155 us).
 __global__ __launch_bounds__(kVecThreads) void k_scale_geometry(const double *__restrict__ G,
                                                                 const double *__restrict__ kap,
                                                                 double *__restrict__ Gk,
                                                                 float *__restrict__ Gk32,
                                                                 int64_t nelem, int nq, int qrev) {
-  const int64_t total = nelem * 6 * nq;
-  for (int64_t i = (int64_t)blockIdx.x * kVecThreads + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * kVecThreads) {
-    const int64_t e = i / (6 * (int64_t)nq);
-    const int64_t qp = i % nq;
-    const double v = kap[e * nq + natural_point(qp, qrev)] * G[i];
-    Gk[i] = v;
-    if (Gk32) Gk32[i] = (float)v;
+  const int64_t i = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  if (i >= nelem * nq) return;
+  const int64_t e = i / nq, qp = i - e * nq, o = e * 6 * nq + qp;
+  const double k = kap[e * nq + natural_point(qp, qrev)];
+  double g[6];
+#pragma unroll
+  for (int m = 0; m < 6; ++m) g[m] = ld_v<true>(G + o + m * (int64_t)nq);
+#pragma unroll
+  for (int m = 0; m < 6; ++m) {
+    const double v = k * g[m];
+    st_v<true>(Gk + o + m * (int64_t)nq, v);
+    if (Gk32) Gk32[o + m * (int64_t)nq] = (float)v;
   }
 }
 
@@ -1271,11 +1329,11 @@ int64_t grid_blocks(int64_t n) {
 }
 
 // Reduce part[nb][width] to at most kStage2Rows rows in `stage` (nothing to
-// do up to kDirectRows rows), then return the pointer and row count the
+// do up to kDirectRows rows of two sums), then return the pointer and row count the
 // single-work-group finisher reads.
 static const double *reduce_stage1(const double *part, int64_t nb, int width, double *stage,
                                    int64_t *rows, hipStream_t s) {
-  if (nb <= kDirectRows) {
+  if (nb * width <= 2 * kDirectRows) {
     *rows = nb;
     return part;
   }
@@ -1301,7 +1359,7 @@ void invert_diag(const double *d, double *dinv, float *dinv32, int64_t n, hipStr
 }
 void scale_geometry(const double *G, const double *kappa, double *Gk, float *Gk32, int qrev,
                     int64_t nelem, int nq, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_geometry, dim3(grid_blocks(nelem * 6 * nq)), dim3(kVecThreads), 0, s,
+  hipLaunchKernelGGL(k_scale_geometry, dim3(vec_blocks(nelem * nq)), dim3(kVecThreads), 0, s,
                      G, kappa, Gk, Gk32, nelem, nq, qrev);
 }
 
@@ -1629,6 +1687,28 @@ void operator_energies(int nc, double *part, int64_t rows, DevScalars *sc, hipSt
   int64_t r = 0;
   const double *src = reduce_stage1(part, rows, nc, part + rows * nc, &r, s);
   launch_fin(FinKind::Energy, nc, src, r, sc, s);
+}
+
+template <typename T>
+void mass_diagonal(int nc, int64_t n, const double *md, const T *u, T *w, bool masked,
+                   hipStream_t s) {
+  hipLaunchKernelGGL((k_mass_diagonal<T>), dim3(vec_blocks(n)), dim3(kVecThreads), 0, s, n, nc,
+                     md, u, w, masked ? 1 : 0);
+}
+template void mass_diagonal<double>(int, int64_t, const double *, const double *, double *, bool,
+                                    hipStream_t);
+template void mass_diagonal<float>(int, int64_t, const double *, const float *, float *, bool,
+                                   hipStream_t);
+
+void misfit_diagonal(int nc, int64_t n, const double *md, const double *u, const double *ut,
+                     double *grad, double *part, hipStream_t s) {
+  hipLaunchKernelGGL(k_misfit_diagonal, dim3(vec_blocks(n)), dim3(kVecThreads), 0, s, n, nc, md,
+                     u, ut, grad, part);
+}
+
+void mark_dirichlet(const int32_t *idx, int64_t count, double *md, hipStream_t s) {
+  hipLaunchKernelGGL(k_mark_dirichlet, dim3(grid_blocks(count)), dim3(kVecThreads), 0, s, idx,
+                     count, md);
 }
 
 void difference(const double *a, const double *b, double *d, int64_t count, hipStream_t s) {
