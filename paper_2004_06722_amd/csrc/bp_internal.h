@@ -65,7 +65,8 @@ struct DevScalars {
   int nonfinite;  // NaN/Inf in a reduction
   int fixed;      // fixed-iteration mode: never set done
   int halted;     // set one iteration after done: the last x update has run
-  int pad_[2];
+  int x0_zero;    // the initial guess is zero everywhere (A x0 is skipped)
+  int pad_;
 };
 
 // Operands of the two-launch iteration of small meshes (k_stiff_colloc_pz
@@ -133,7 +134,7 @@ struct bp_op_s {
   // internal node order (interior_first_order): perm[v] = the caller's id of
   // internal node v (NULL: the caller's order); internal nodes [0, n_owned)
   // are element-interior, each written by its element with a plain store;
-  // bi, xi: b and x of a solve in the internal order
+  // xi: x of a solve in the internal order; bi: b of a mixed solve
   int32_t *perm = nullptr;
   int32_t *iperm = nullptr;  // iperm[g] = the internal id of the caller's node g
   int64_t n_owned = 0;

@@ -232,10 +232,12 @@ size_t scratch_layout(const bp_op_s *op, unsigned char *base, CgWork *ws, double
   return off;
 }
 
-int upload_scalars(bp_op op, DevScalars *sc, double rtol, bool fixed, hipStream_t s) {
+int upload_scalars(bp_op op, DevScalars *sc, double rtol, bool fixed, bool x0_zero,
+                   hipStream_t s) {
   std::memset(op->sc_host, 0, sizeof(DevScalars));
   op->sc_host->tol2 = rtol * rtol;
   op->sc_host->fixed = fixed ? 1 : 0;
+  op->sc_host->x0_zero = x0_zero ? 1 : 0;
   BP_HIP(hipMemcpyAsync(sc, op->sc_host, sizeof(DevScalars), hipMemcpyHostToDevice, s));
   return BP_OK;
 }
@@ -244,9 +246,6 @@ int download_scalars(bp_op op, const DevScalars *sc, hipStream_t s) {
   BP_HIP(hipMemcpyAsync(op->sc_host, sc, sizeof(DevScalars), hipMemcpyDeviceToHost, s));
   BP_HIP(hipStreamSynchronize(s));
   return BP_OK;
-}
-int upload_scalars(bp_op op, double rtol, bool fixed, hipStream_t s) {
-  return upload_scalars(op, op->sc, rtol, fixed, s);
 }
 int download_scalars(bp_op op, hipStream_t s) { return download_scalars(op, op->sc, s); }
 
@@ -258,6 +257,42 @@ int64_t stored_rows(const bp_op_s *op, int which) {
   return which == BP_MASS && op->tr_off ? 0 : op->n_owned;
 }
 
+// b, x0 and x of a solve. With perm, b and x0 are in the caller's order and x is
+// the solve's own copy, made by the initialisation; otherwise x0 is x.
+template <typename T>
+struct SolveVectors {
+  const T *b, *x0;
+  T *x;
+  const int32_t *perm;
+};
+
+void clear(double *x, int64_t n, hipStream_t s) { fill_f64(x, n, 0.0, s); }
+void clear(float *x, int64_t n, hipStream_t s) { fill_f32(x, n, 0.0f, s); }
+
+// w = A x0, which the CG initialisation subtracts from b; the device scalars are
+// uploaded first. A guess that is zero everywhere needs no operator: a pass
+// over x0 finds out (sc->x0_zero), and the launches then return at entry (at
+// p = 7, E = 64^3 0.18 ms against 1.5 ms). With a coefficient or a beta, which
+// the caller gives and nothing checks, the operator always runs: it passes a
+// non-finite entry on into the residual.
+template <typename T>
+int apply_guess(bp_op op, DevScalars *sc, int which, const SolveVectors<T> &v, T *w, double rtol,
+                bool fixed, bool x0_zero, hipStream_t s) {
+  const int64_t n = op->nglobal, nv = n * op->ncomp;
+  const bool own_data = which == BP_MASS || (!op->kappa_set && !(which == BP_HELM && op->Bb));
+  const bool scan = !x0_zero && sizeof(T) == 8 && own_data;
+  int rc = upload_scalars(op, sc, rtol, fixed, x0_zero || scan, s);
+  if (rc) return rc;
+  clear(w, nv, s);
+  if (x0_zero) return BP_OK;
+  if (scan) scan_nonzero((const double *)v.x0, nv, sc, s);
+  const int *skip = scan ? &sc->x0_zero : nullptr;
+  if constexpr (sizeof(T) == 8)
+    if (v.perm) permute_in<double>(op->ncomp, n, v.perm, v.x0, v.x, s, skip);
+  return launch_apply(op, which, sizeof(T) == 4, internal_map(op), v.x, w, op->has_dirichlet,
+                      nullptr, skip, s);
+}
+
 // Jacobi-PCG on precision T. x0_zero: x is zero on entry (skips A x0).
 // The buffer `r` holds the preconditioned residual z = dinv r during the
 // iteration (ten vector words per DOF and iteration; see k_cg_init).
@@ -266,29 +301,23 @@ int64_t stored_rows(const bp_op_s *op, int which) {
 // ws: partial sums and device scalars of the run (own_work(op) unless the
 // caller brings its own).
 template <typename T>
-int pcg_run(bp_op op, const CgWork &ws, int which, bool f32, const T *b, T *x, const T *dinv,
-            T *r, T *p, T *w, double rtol, int maxit, bool fixed, bool x0_zero, hipStream_t s,
+int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, const T *dinv, T *r,
+            T *p, T *w, double rtol, int maxit, bool fixed, bool x0_zero, hipStream_t s,
             int *iters_out, float *ms_out, double *apply_ms_out = nullptr,
             int *apply_count_out = nullptr, bool resume = false) {
+  constexpr bool f32 = sizeof(T) == 4;
   const int nc = op->ncomp;
-  const int64_t n = op->nglobal, nv = n * nc;
+  const int64_t n = op->nglobal;
+  T *const x = v.x;
   const bool masked = op->has_dirichlet;
   const int64_t nb_apply = apply_rows(op, which), nb_vec = vec_blocks(n);
   double *const part = ws.part;
   DevScalars *const sc = ws.sc;
   int rc = BP_OK;
   if (!resume) {
-    rc = upload_scalars(op, sc, rtol, fixed, s);
+    rc = apply_guess<T>(op, sc, which, v, w, rtol, fixed, x0_zero, s);
     if (rc) return rc;
-    if constexpr (sizeof(T) == 8)
-      fill_f64((double *)w, nv, 0.0, s);
-    else
-      fill_f32((float *)w, nv, 0.0f, s);
-    if (!x0_zero) {
-      rc = launch_apply(op, which, f32, internal_map(op), x, w, masked, nullptr, nullptr, s);
-      if (rc) return rc;
-    }
-    cg_init<T>(nc, n, b, r, w, p, dinv, part, sc, s);
+    cg_init<T>(nc, n, v.b, v.x0, x, v.perm, r, w, p, dinv, part, sc, s);
     BP_HIP(hipGetLastError());
   }
   BP_HIP(hipEventRecord(op->ev0, s));
@@ -410,25 +439,20 @@ int pcg_run(bp_op op, const CgWork &ws, int which, bool f32, const T *b, T *x, c
 // Single-reduction Jacobi-PCG (FP64): per iteration the fused vector update,
 // the operator on u = dinv r (its energy partials give (u, A u)) and one
 // finisher. u lives in op->tmp, s = A p in op->sv. Same timing and stopping
-// conventions as pcg_run; x0_zero skips the operator on x0.
-int pcg_run_sr(bp_op op, int which, const double *b, double *x, const double *dinv,
-               double rtol, int maxit, bool fixed, bool x0_zero, hipStream_t s,
-               int *iters_out, float *ms_out, double *apply_ms_out, int *apply_count_out) {
+// conventions as pcg_run.
+int pcg_run_sr(bp_op op, int which, const SolveVectors<double> &v, const double *dinv,
+               double rtol, int maxit, bool fixed, hipStream_t s, int *iters_out, float *ms_out,
+               double *apply_ms_out, int *apply_count_out) {
   const int nc = op->ncomp;
-  const int64_t n = op->nglobal, nv = n * nc;
+  const int64_t n = op->nglobal;
   const bool masked = op->has_dirichlet;
   const int64_t nba = apply_rows(op, which), nbv = vec_blocks(n);
   double *pv = op->part;                                     // vector partials + stage 1
   double *pa = op->part + (nbv + kStage2Rows) * 3 * nc;      // operator partials + stage 1
-  double *r = op->r, *u = op->tmp, *w = op->w, *p = op->pv, *sv = op->sv;
-  int rc = upload_scalars(op, rtol, fixed, s);
+  double *u = op->tmp, *w = op->w, *p = op->pv, *sv = op->sv, *x = v.x;
+  int rc = apply_guess<double>(op, op->sc, which, v, w, rtol, fixed, false, s);
   if (rc) return rc;
-  fill_f64(w, nv, 0.0, s);
-  if (!x0_zero) {
-    rc = launch_apply(op, which, false, internal_map(op), x, w, masked, nullptr, nullptr, s);
-    if (rc) return rc;
-  }
-  sr_init<double>(nc, n, b, r, w, u, p, sv, dinv, pv, s);
+  sr_init(nc, n, v.b, v.x0, x, v.perm, w, u, p, sv, dinv, pv, op->sc, s);
   rc = launch_apply(op, which, false, internal_map(op), u, w, masked, pa, nullptr, s);
   if (rc) return rc;
   sr_fin(true, nc, pv, nbv, pa, nba, op->sc, s);
@@ -509,6 +533,11 @@ int true_residual(bp_op op, const double *b, const double *x, double *worst, hip
   return BP_OK;
 }
 
+// b and x of the FP32 inner solves (the solve's own order throughout)
+SolveVectors<float> inner_vectors(bp_op op) {
+  return {op->b32, op->x32, op->x32, nullptr};
+}
+
 // FP32 Jacobi-PCG with reliable updates: one FP32 iteration whose search
 // direction is kept for the whole solve; whenever the recursive FP32
 // residual has dropped by `delta` since the last replacement, x += x32 in
@@ -530,9 +559,9 @@ int mixed_reliable(bp_op op, const double *b, double *x, double rtol, double del
     fill_f32(op->x32, nv, 0.0f, s);
     bool resume = false;
     for (;;) {
-      rc = pcg_run<float>(op, own_work(op), BP_STIFF, true, op->b32, op->x32, op->dinv32,
-                          op->r32, op->p32, op->w32, delta, max_iters - iters, false, true, s,
-                          &iters, nullptr, nullptr, nullptr, resume);
+      rc = pcg_run<float>(op, own_work(op), BP_STIFF, inner_vectors(op), op->dinv32, op->r32,
+                          op->p32, op->w32, delta, max_iters - iters, false, true, s, &iters,
+                          nullptr, nullptr, nullptr, resume);
       if (rc) break;
       const bool reached = op->sc_host->done != 0;
       dc_accumulate(nv, x, op->x32, s);
@@ -551,18 +580,8 @@ int mixed_reliable(bp_op op, const double *b, double *x, double rtol, double del
   return rc;
 }
 
-// The b and x a solve iterates on: the caller's (caller order), or the
-// internal copies bi, xi with b and x0 permuted into them.
-struct SolveVectors {
-  const double *b;
-  double *x;
-};
-
-SolveVectors solve_in(bp_op op, const double *b, double *x, hipStream_t s) {
-  if (!op->perm) return SolveVectors{b, x};
-  permute_in<double>(op->ncomp, op->nglobal, op->perm, b, op->bi, s);
-  permute_in<double>(op->ncomp, op->nglobal, op->perm, x, op->xi, s);
-  return SolveVectors{op->bi, op->xi};
+SolveVectors<double> solve_vectors(bp_op op, const double *b, double *x) {
+  return {b, x, op->perm ? op->xi : x, op->perm};
 }
 
 // the solution back into the caller's x (nothing to do in the caller's
@@ -717,7 +736,7 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
     map_internal(op->idx_c, op->iperm, op->idx, nelem * n3, s);
     TRYHIP(hipGetLastError());
     TRYHIP(hipStreamSynchronize(s));
-    TRY(dmalloc(&op->bi, nv));
+    if (op->fp32) TRY(dmalloc(&op->bi, nv));
     TRY(dmalloc(&op->xi, nv));
   }
   // Gauss-Legendre operators: the transposed gather map (counting sort of the
@@ -958,14 +977,14 @@ int bp_pcg_solve(bp_op op, int which, const double *b, double *x, double rtol, i
   float ms = 0.0f;
   double apply_ms = 0.0;
   int apply_count = 0;
-  const SolveVectors v = solve_in(op, b, x, s);
+  const SolveVectors<double> v = solve_vectors(op, b, x);
   if (op->cg_variant == BP_CG_SINGLE_REDUCTION) {
-    rc = pcg_run_sr(op, which, v.b, v.x, op->dinv[dinv_slot(op, which)], rtol, maxit,
-                    fixed_iters != 0, false, s, &iters, &ms, &apply_ms, &apply_count);
+    rc = pcg_run_sr(op, which, v, op->dinv[dinv_slot(op, which)], rtol, maxit, fixed_iters != 0, s,
+                    &iters, &ms, &apply_ms, &apply_count);
   } else {
-    rc = pcg_run<double>(op, own_work(op), which, false, v.b, v.x,
-                         op->dinv[dinv_slot(op, which)], op->r, op->pv, op->w, rtol, maxit,
-                         fixed_iters != 0, false, s, &iters, &ms, &apply_ms, &apply_count);
+    rc = pcg_run<double>(op, own_work(op), which, v, op->dinv[dinv_slot(op, which)], op->r, op->pv,
+                         op->w, rtol, maxit, fixed_iters != 0, false, s, &iters, &ms, &apply_ms,
+                         &apply_count);
   }
   const int rc_out = solve_out(op, x, s);
   if (rc == BP_OK) rc = rc_out;
@@ -1011,9 +1030,8 @@ int bp_pcg_solve_static(bp_op op, int which, const double *b, double *x, double 
   int apply_count = 0;
   // standard recurrences whatever BP_OPT_CG_VARIANT says; every workspace
   // word is written (w cleared, scalars uploaded) before it is read
-  const SolveVectors v = solve_in(op, b, x, s);
-  rc = pcg_run<double>(op, ws, which, false, v.b, v.x, op->dinv[dinv_slot(op, which)], z, p, w,
-                       rtol, maxit, fixed_iters != 0, false, s, &iters, &ms, &apply_ms,
+  rc = pcg_run<double>(op, ws, which, solve_vectors(op, b, x), op->dinv[dinv_slot(op, which)], z,
+                       p, w, rtol, maxit, fixed_iters != 0, false, s, &iters, &ms, &apply_ms,
                        &apply_count);
   const int rc_out = solve_out(op, x, s);
   if (rc == BP_OK) rc = rc_out;
@@ -1046,9 +1064,12 @@ int bp_pcg_solve_mixed(bp_op op, const double *b, double *x_out, double outer_rt
   const bool masked = op->has_dirichlet;
   // the events were created by bp_setup: the solve allocates nothing
   hipEvent_t t0 = op->evm0, t1 = op->evm1;
-  const SolveVectors v = solve_in(op, b, x, s);
-  b = v.b;
-  x = v.x;
+  if (op->perm) {
+    permute_in<double>(nc, n, op->perm, b, op->bi, s);
+    permute_in<double>(nc, n, op->perm, x, op->xi, s);
+    b = op->bi;
+    x = op->xi;
+  }
   BP_HIP(hipEventRecord(t0, s));
   int outer = 0, inner_total = 0;
   if (op->mixed_mode == BP_MIXED_RELIABLE) {
@@ -1077,9 +1098,8 @@ int bp_pcg_solve_mixed(bp_op op, const double *b, double *x_out, double outer_rt
     to_f32(op->r, op->b32, nv, s);
     fill_f32(op->x32, nv, 0.0f, s);
     int it = 0;
-    rc = pcg_run<float>(op, own_work(op), BP_STIFF, true, op->b32, op->x32, op->dinv32,
-                        op->r32, op->p32, op->w32, inner_rtol, max_inner, false, true, s, &it,
-                        nullptr);
+    rc = pcg_run<float>(op, own_work(op), BP_STIFF, inner_vectors(op), op->dinv32, op->r32,
+                        op->p32, op->w32, inner_rtol, max_inner, false, true, s, &it, nullptr);
     if (rc) break;
     inner_total += it;
     dc_accumulate(nv, x, op->x32, s);

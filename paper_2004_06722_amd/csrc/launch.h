@@ -79,9 +79,13 @@ void to_f32(const double *src, float *dst, int64_t n, hipStream_t s);
 void invert_diag(const double *d, double *dinv, float *dinv32, int64_t n, hipStream_t s);
 
 // CG steps; part holds per-block partial sums, sc the device scalars.
+// Where perm is given, b and x0 are in the caller's order, and x0 is copied
+// into x.
 template <typename T>
-void cg_init(int nc, int64_t n, const T *b, T *r, T *w, T *p, const T *dinv, double *part,
-             DevScalars *sc, hipStream_t s);
+void cg_init(int nc, int64_t n, const T *b, const T *x0, T *x, const int32_t *perm, T *r, T *w,
+             T *p, const T *dinv, double *part, DevScalars *sc, hipStream_t s);
+// clears sc->x0_zero if any entry of x is not zero
+void scan_nonzero(const double *x, int64_t count, DevScalars *sc, hipStream_t s);
 // check = false (a fixed number of iterations): the kernels do not stop on
 // the done flag, so their loads need not wait for it
 void cg_fin_alpha(int nc, const double *part, int64_t nb, DevScalars *sc, hipStream_t s,
@@ -161,9 +165,9 @@ void cg_update_r_gather(int nc, int64_t n, int64_t nl, T *r, const T *wl, const 
 // single-reduction PCG: init (r, u = dinv r, p = s = w = 0; partials r.u, r.r,
 // b.b), the fused vector update (partials r.u, r.r), and the finisher that
 // combines them with the operator's (u, A u) partials (alpha, beta, flags)
-template <typename T>
-void sr_init(int nc, int64_t n, const T *b, T *r, T *w, T *u, T *p, T *sv, const T *dinv,
-             double *part, hipStream_t s);
+void sr_init(int nc, int64_t n, const double *b, const double *x0, double *x,
+             const int32_t *perm, double *w, double *u, double *p, double *sv,
+             const double *dinv, double *part, DevScalars *sc, hipStream_t s);
 template <typename T>
 void sr_update(int nc, int64_t n, T *x, T *u, T *w, T *p, T *sv, const T *dinv, double *part,
                DevScalars *sc, hipStream_t s, bool check = true, int64_t n_own = 0);
@@ -171,9 +175,10 @@ void sr_update(int nc, int64_t n, T *x, T *u, T *w, T *p, T *sv, const T *dinv, 
 // vectors [nc][n] between the caller's node order and the internal one,
 // both as gathers: in, dst[c][v] = src[c][perm[v]] (perm[v] = the caller's
 // id of internal node v); out, dst[c][g] = src[c][iperm[g]] (iperm[g] = the
-// internal id of the caller's node g)
+// internal id of the caller's node g); nothing is done if *skip
 template <typename T>
-void permute_in(int nc, int64_t n, const int32_t *perm, const T *src, T *dst, hipStream_t s);
+void permute_in(int nc, int64_t n, const int32_t *perm, const T *src, T *dst, hipStream_t s,
+                const int *skip = nullptr);
 template <typename T>
 void permute_out(int nc, int64_t n, const int32_t *iperm, const T *src, T *dst, hipStream_t s);
 // the gather map in internal ids: idx = idx_c through iperm, Dirichlet signs kept

@@ -188,31 +188,40 @@ __device__ __forceinline__ void block_partial1(double v, double *part, int width
   __syncthreads();
 }
 
-// r = b - w (w holds A x0), w = 0, p = z = dinv r; partials r.z, r.r, b.b.
-// Entries of b on Dirichlet nodes are treated as zero. The iteration keeps
-// the preconditioned residual z = dinv r (stored in `r`) rather than r: the
-// residual update then advances z and the direction update reads z alone,
-// ten vector words per DOF and iteration instead of eleven.
+// r = b - w (w holds A x0; nothing to subtract where the initial guess is zero
+// everywhere, sc->x0_zero), w = 0, p = z = dinv r; partials r.z, r.r, b.b.
+// With perm, b and x0 are in the caller's order: they are gathered here, and
+// x0 is copied into x, the solve's own (one pass; as a permutation of each
+// before it 2 x 0.5 ms at n = 9e7). Entries of b on Dirichlet nodes are treated
+// as zero. The iteration keeps the preconditioned residual z = dinv r (stored
+// in `r`) rather than r: the residual update then advances z and the direction
+// update reads z alone, ten vector words per DOF and iteration instead of
+// eleven.
 template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_cg_init(int64_t n, const T *__restrict__ b,
-                                                         T *__restrict__ r, T *__restrict__ w,
-                                                         T *__restrict__ p,
-                                                         const T *__restrict__ dinv,
-                                                         double *__restrict__ part) {
+__global__ __launch_bounds__(kVecThreads) void k_cg_init(
+    int64_t n, const T *__restrict__ b, const T *__restrict__ x0, T *__restrict__ x,
+    const int32_t *__restrict__ perm, T *__restrict__ r, T *__restrict__ w, T *__restrict__ p,
+    const T *__restrict__ dinv, double *__restrict__ part, const DevScalars *__restrict__ sc) {
   const int comp = blockIdx.y, nc = gridDim.y;
   const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  const bool zero = sc->x0_zero != 0;
   double rz = 0.0, rr = 0.0, bb = 0.0;
   if (v < n) {
-    const int64_t f = comp * n + v;
+    const int64_t f = comp * n + v, g = perm ? comp * n + perm[v] : f;
+    if (perm) x[f] = x0[g];
+    T wv = T(0);
+    if (!zero) {
+      wv = w[f];
+      w[f] = T(0);
+    }
     const T di = dinv[v];
     // dinv = 0 exactly on Dirichlet nodes: b is read as 0 there
     const bool free = di != T(0);
-    const T bv = free ? b[f] : T(0);
-    const T rv = free ? bv - w[f] : T(0);
+    const T bv = free ? b[g] : T(0);
+    const T rv = free ? bv - wv : T(0);
     const T z = di * rv;
     r[f] = z;
     p[f] = z;
-    w[f] = T(0);
     rz = (double)rv * (double)z;
     rr = (double)rv * (double)rv;
     bb = (double)bv * (double)bv;
@@ -220,6 +229,23 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_init(int64_t n, const T *__r
   block_partial1(rz, part, 3 * nc, comp);
   block_partial1(rr, part, 3 * nc, nc + comp);
   block_partial1(bb, part, 3 * nc, 2 * nc + comp);
+}
+
+// Clears sc->x0_zero (set by the host) if any entry of x is not zero.
+__global__ __launch_bounds__(kVecThreads) void k_scan_nonzero(const double *__restrict__ x,
+                                                              int64_t count, DevScalars *sc) {
+  bool any = false;
+  const int64_t step = (int64_t)gridDim.x * kVecThreads;
+  int64_t i = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  for (; i + 3 * step < count; i += 4 * step) {
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = x[i + q * step];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) any = any || !(v[q] == 0.0);
+  }
+  for (; i < count; i += step) any = any || !(x[i] == 0.0);
+  if (__any(any) && (threadIdx.x & 63) == 0) sc->x0_zero = 0;
 }
 
 template <int NC>
@@ -1085,33 +1111,37 @@ __global__ __launch_bounds__(kVecThreads) void k_scale_geometry(const double *__
 // from the vector pass and (u, w) from the operator's fused energy, so one
 // finisher per iteration computes alpha and beta.
 
-// r = b - w (w = A x0), u = dinv r, p = s = 0, w = 0; partials r.u, r.r, b.b
-// (entries of b on Dirichlet nodes read as 0)
-template <typename T>
-__global__ __launch_bounds__(kVecThreads) void k_sr_init(int64_t n, const T *__restrict__ b,
-                                                         T *__restrict__ r, T *__restrict__ w,
-                                                         T *__restrict__ u, T *__restrict__ p,
-                                                         T *__restrict__ sv,
-                                                         const T *__restrict__ dinv,
-                                                         double *__restrict__ part) {
+// u = dinv (b - w) (w = A x0), p = s = 0, w = 0; partials r.u, r.r, b.b; b, x0
+// and x as in k_cg_init
+__global__ __launch_bounds__(kVecThreads) void k_sr_init(
+    int64_t n, const double *__restrict__ b, const double *__restrict__ x0,
+    double *__restrict__ x, const int32_t *__restrict__ perm, double *__restrict__ w,
+    double *__restrict__ u, double *__restrict__ p, double *__restrict__ sv,
+    const double *__restrict__ dinv, double *__restrict__ part,
+    const DevScalars *__restrict__ sc) {
   const int comp = blockIdx.y, nc = gridDim.y;
   const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  const bool zero = sc->x0_zero != 0;
   double ru = 0.0, rr = 0.0, bb = 0.0;
   if (v < n) {
-    const int64_t f = comp * n + v;
-    const T di = dinv[v];
-    const bool free = di != T(0);
-    const T bv = free ? b[f] : T(0);
-    const T rv = free ? bv - w[f] : T(0);
-    const T uv = di * rv;
-    r[f] = rv;
+    const int64_t f = comp * n + v, g = perm ? comp * n + perm[v] : f;
+    if (perm) x[f] = x0[g];
+    double wv = 0.0;
+    if (!zero) {
+      wv = w[f];
+      w[f] = 0.0;
+    }
+    const double di = dinv[v];
+    const bool free = di != 0.0;
+    const double bv = free ? b[g] : 0.0;
+    const double rv = free ? bv - wv : 0.0;
+    const double uv = di * rv;
     u[f] = uv;
-    p[f] = T(0);
-    sv[f] = T(0);
-    w[f] = T(0);
-    ru = (double)rv * (double)uv;
-    rr = (double)rv * (double)rv;
-    bb = (double)bv * (double)bv;
+    p[f] = 0.0;
+    sv[f] = 0.0;
+    ru = rv * uv;
+    rr = rv * rv;
+    bb = bv * bv;
   }
   block_partial1(ru, part, 3 * nc, comp);
   block_partial1(rr, part, 3 * nc, nc + comp);
@@ -1287,7 +1317,9 @@ __global__ __launch_bounds__(kVecThreads) void k_map_internal(const int32_t *__r
 template <typename T>
 __global__ __launch_bounds__(kVecThreads) void k_permute(int64_t n, const int32_t *__restrict__ map,
                                                          const T *__restrict__ src,
-                                                         T *__restrict__ dst) {
+                                                         T *__restrict__ dst,
+                                                         const int *__restrict__ skip) {
+  if (skip && *skip) return;
   const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
   if (v >= n) return;
   const int64_t c = (int64_t)blockIdx.y * n;
@@ -1297,17 +1329,18 @@ __global__ __launch_bounds__(kVecThreads) void k_permute(int64_t n, const int32_
 }  // namespace
 
 template <typename T>
-void permute_in(int nc, int64_t n, const int32_t *perm, const T *src, T *dst, hipStream_t s) {
+void permute_in(int nc, int64_t n, const int32_t *perm, const T *src, T *dst, hipStream_t s,
+                const int *skip) {
   hipLaunchKernelGGL((k_permute<T>), dim3(vec_blocks(n), nc), dim3(kVecThreads), 0, s, n, perm,
-                     src, dst);
+                     src, dst, skip);
 }
 template <typename T>
 void permute_out(int nc, int64_t n, const int32_t *iperm, const T *src, T *dst, hipStream_t s) {
   hipLaunchKernelGGL((k_permute<T>), dim3(vec_blocks(n), nc), dim3(kVecThreads), 0, s, n, iperm,
-                     src, dst);
+                     src, dst, (const int *)nullptr);
 }
 template void permute_in<double>(int, int64_t, const int32_t *, const double *, double *,
-                                 hipStream_t);
+                                 hipStream_t, const int *);
 template void permute_out<double>(int, int64_t, const int32_t *, const double *, double *,
                                   hipStream_t);
 
@@ -1437,14 +1470,20 @@ void scale_mass(const double *Bt, const double *beta_q, double beta, double *Bb,
 }
 
 template <typename T>
-void cg_init(int nc, int64_t n, const T *b, T *r, T *w, T *p, const T *dinv, double *part,
-             DevScalars *sc, hipStream_t s) {
+void cg_init(int nc, int64_t n, const T *b, const T *x0, T *x, const int32_t *perm, T *r, T *w,
+             T *p, const T *dinv, double *part, DevScalars *sc, hipStream_t s) {
   const int64_t nb = vec_blocks(n);
-  hipLaunchKernelGGL((k_cg_init<T>), dim3(nb, nc), dim3(kVecThreads), 0, s, n, b, r, w, p, dinv,
-                     part);
+  hipLaunchKernelGGL((k_cg_init<T>), dim3(nb, nc), dim3(kVecThreads), 0, s, n, b, x0, x, perm, r,
+                     w, p, dinv, part, sc);
   int64_t rows = 0;
   const double *src = reduce_stage1(part, nb, 3 * nc, part + nb * 3 * nc, &rows, s);
   launch_fin(FinKind::Init, nc, src, rows, sc, s);
+}
+
+void scan_nonzero(const double *x, int64_t count, DevScalars *sc, hipStream_t s) {
+  const int64_t b = (count + 4 * kVecThreads - 1) / (4 * kVecThreads);
+  hipLaunchKernelGGL(k_scan_nonzero, dim3(b < kVecMaxBlocks ? b : kVecMaxBlocks),
+                     dim3(kVecThreads), 0, s, x, count, sc);
 }
 
 void cg_fin_alpha(int nc, const double *part, int64_t nb, DevScalars *sc, hipStream_t s,
@@ -1726,11 +1765,11 @@ void dc_residual(int nc, int64_t n, const double *b, double *r, double *w, const
   launch_fin(FinKind::Norms, nc, src, rows, sc, s);
 }
 
-template <typename T>
-void sr_init(int nc, int64_t n, const T *b, T *r, T *w, T *u, T *p, T *sv, const T *dinv,
-             double *part, hipStream_t s) {
-  hipLaunchKernelGGL((k_sr_init<T>), dim3(vec_blocks(n), nc), dim3(kVecThreads), 0, s, n, b, r,
-                     w, u, p, sv, dinv, part);
+void sr_init(int nc, int64_t n, const double *b, const double *x0, double *x,
+             const int32_t *perm, double *w, double *u, double *p, double *sv,
+             const double *dinv, double *part, DevScalars *sc, hipStream_t s) {
+  hipLaunchKernelGGL(k_sr_init, dim3(vec_blocks(n), nc), dim3(kVecThreads), 0, s, n, b, x0, x,
+                     perm, w, u, p, sv, dinv, part, sc);
 }
 
 template <typename T>
@@ -1775,8 +1814,6 @@ void sr_fin(bool first, int nc, double *pv, int64_t nbv, double *pa, int64_t nba
   }
 }
 
-template void sr_init<double>(int, int64_t, const double *, double *, double *, double *,
-                              double *, double *, const double *, double *, hipStream_t);
 template void sr_update<double>(int, int64_t, double *, double *, double *, double *, double *,
                                 const double *, double *, DevScalars *, hipStream_t, bool,
                                 int64_t);
@@ -1801,10 +1838,12 @@ void dc_accumulate(int64_t n, double *x, const float *d, hipStream_t s) {
   hipLaunchKernelGGL(k_accumulate, dim3(grid_blocks(n)), dim3(kVecThreads), 0, s, x, d, n);
 }
 
-template void cg_init<double>(int, int64_t, const double *, double *, double *, double *,
-                              const double *, double *, DevScalars *, hipStream_t);
-template void cg_init<float>(int, int64_t, const float *, float *, float *, float *,
-                             const float *, double *, DevScalars *, hipStream_t);
+template void cg_init<double>(int, int64_t, const double *, const double *, double *,
+                              const int32_t *, double *, double *, double *, const double *,
+                              double *, DevScalars *, hipStream_t);
+template void cg_init<float>(int, int64_t, const float *, const float *, float *,
+                             const int32_t *, float *, float *, float *, const float *, double *,
+                             DevScalars *, hipStream_t);
 template void cg_update_r<double>(int, int64_t, double *, double *, const double *, double *,
                                   DevScalars *, hipStream_t, bool, int64_t);
 template void cg_update_r<float>(int, int64_t, float *, float *, const float *, double *,
