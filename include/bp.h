@@ -327,10 +327,11 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
 #define BP_CG_STANDARD 0
 #define BP_CG_SINGLE_REDUCTION 1
 /*   BP_OPT_CG_FUSE (2, default, 1 or 0): fewer launches per iteration with
- *     the standard recurrences in FP64, where the partial-sum tables are short
- *     enough for every work-group to reduce them itself, each in one fixed
- *     order (bit-identical in all work-groups):
- *     1: at most 1024 partial rows (about 2.6e5 nodes): every work-group of
+ *     the standard recurrences (FP64 solves and FP32 inner solves), where the
+ *     partial-sum tables are short enough for every work-group to reduce them
+ *     itself, each in one fixed order (bit-identical in all work-groups):
+ *     1: rows of 256 nodes up to 1024 rows, of 1024 nodes beyond (up to 1024
+ *     rows, about 1e6 nodes, and four components): every work-group of
  *     the residual update computes alpha from the operator's partial sums and
  *     every work-group of the direction update computes beta and the
  *     convergence test from the residual update's: three launches per
@@ -338,12 +339,11 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
  *     assembles by a gather in the residual update, keeps five).
  *     2: in addition, for the collocated stiffness operator of one component
  *     up to p = 8, while (vector rows) x (operator work-groups) stays at
- *     most 4M (about 8e5 nodes at p = 7; rows of 256 nodes up to 1024
- *     rows, of 1024 nodes beyond): the
+ *     most 9M (about 1.2e6 nodes at p = 7): the
  *     operator launch forms the direction p_k = z_k + beta p_{k-1} at the
  *     nodes it gathers (beta and the stopping test from the vector kernel's
  *     partial sums) and one vector kernel stores p_k and updates x and the
- *     residual: two launches per iteration. Above those bounds, while a
+ *     residual: two launches per iteration. Above those bounds, in FP64 while a
  *     vector stays below 64 MiB, the same operator takes beta from the
  *     finisher of the previous iteration and the vector kernel sits between
  *     the two finishers: four launches.

@@ -76,8 +76,9 @@ struct DevScalars {
 // (r_{k-1}.z_{k-1}) from the vector kernel's partial rows; the vector kernel
 // then stores p_k (same expression, same beta). r.z by iteration parity:
 // iteration k's operator launch writes rzs[k & 1].
+template <typename T>
 struct PZIter {
-  const double *z;   // z_k = dinv r_k, [n]
+  const T *z;        // z_k = dinv r_k, [n]
   const double *pr;  // partial rows [nbv][2]: r_k.z_k, r_k.r_k
   int64_t nbv;
   DevScalars *sc;

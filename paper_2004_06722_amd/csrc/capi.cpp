@@ -333,66 +333,61 @@ int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, con
   const int64_t nl = op->nelem * op->p1 * op->p1 * op->p1;
   const T *wl = reinterpret_cast<const T *>(sizeof(T) == 4 ? (const void *)op->wl32
                                                            : (const void *)op->wl);
-  // small meshes (FP64): alpha and beta computed inside the two vector
+  // small and mid-size meshes: alpha and beta computed inside the two vector
   // updates, three launches per iteration; the operator's partials stay at
   // the start of `part`, the residual update's follow them
-  const bool fused =
-      op->cg_fuse > 0 && sizeof(T) == 8 && !mass_wl && !resume && cg_fused_fits(n, nb_apply);
+  const bool fused = op->cg_fuse > 0 && !mass_wl && cg_fused_fits(nc, n, nb_apply);
   // two launches per iteration where the operator forms p itself (PZIter);
   // its shorter vector table lets it run on larger meshes than the three
-  const bool fused2 = op->cg_fuse == 2 && sizeof(T) == 8 && !mass_wl && !resume &&
-                      apply_pz_supported(op, which) && cg_fused2_fits(n, nb_apply);
+  const bool fused2 = op->cg_fuse == 2 && !mass_wl && apply_pz_supported(op, which) &&
+                      cg_fused2_fits(n, nb_apply);
   // above those bounds the same operator with beta from the finisher and one
-  // vector pass for p, x and z: four launches instead of five, while the
-  // vectors stay below the streaming size (measured at p = 7: 0.3-2% faster
-  // at E = 2^12..2^14, 1.2% slower at E = 2^18, where the z gathered by the
-  // operator costs more than the z the vector pass no longer reads)
-  const bool fused4 = sizeof(T) == 8 && !mass_wl && !resume && apply_pz_supported(op, which) &&
-                      !fused2 &&
-                      (op->cg_fuse == 3 || (op->cg_fuse == 2 && !cg_streams(n)));
+  // vector pass for p, x and z: four launches instead of five, in FP64 while
+  // the vectors stay below the streaming size (measured at p = 7: 0.3-2%
+  // faster at E = 2^12..2^14, 1.2% slower at E = 2^18, where the z gathered by
+  // the operator costs more than the z the vector pass no longer reads; in
+  // FP32 1-5% slower at E = 16^3, p = 7, 8 and E = 31^3, p = 4)
+  const bool fused4 = !mass_wl && apply_pz_supported(op, which) && !fused2 &&
+                      (op->cg_fuse == 3 || (op->cg_fuse == 2 && !f32 && !cg_streams(n)));
   double *const part_r = part + nb_apply * nc;
   while (it < maxit) {
     const int chunk = fixed ? maxit - it : std::min(poll, maxit - it);
     for (int c = 0; c < chunk; ++c) {
       const bool tm = op->time_apply && timed < kMaxTimedApplies;
-      if constexpr (sizeof(T) == 8) {
-        if (fused2) {
-          const int k = it + c;
-          const PZIter pz{r, part_r, rxp_rows(n), sc, k & 1, check ? 1 : 0, k == 0 ? 1 : 0, 1};
-          if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed], s));
-          rc = launch_apply_pz(op, p, w, masked, part, done, pz, s);
-          if (rc) return rc;
-          if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed++ + 1], s));
-          cg_update_rxp_fused(nc, n, x, p, r, w, dinv, part, nb_apply, part_r, sc, k & 1, s,
-                              check, k == 0, stored_rows(op, which));
-          continue;
-        }
-        if (fused4) {
-          const int k = it + c;
-          const PZIter pz{r, nullptr, 0, sc, k & 1, check ? 1 : 0, k == 0 ? 1 : 0, 0};
-          if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed], s));
-          rc = launch_apply_pz(op, p, w, masked, part, done, pz, s);
-          if (rc) return rc;
-          if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed++ + 1], s));
-          cg_fin_alpha(nc, part, nb_apply, sc, s, check);
-          cg_update_rxp(n, x, p, r, w, dinv, part, sc, s, check, k == 0, stored_rows(op, which));
-          cg_fin_beta(nc, nb_vec, part, sc, s, check);
-          continue;
-        }
+      if (fused2) {
+        const int k = it + c;
+        const PZIter<T> pz{r, part_r, rxp_rows(n), sc, k & 1, check ? 1 : 0, k == 0 ? 1 : 0, 1};
+        if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed], s));
+        rc = launch_apply_pz<T>(op, p, w, masked, part, done, pz, s);
+        if (rc) return rc;
+        if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed++ + 1], s));
+        cg_update_rxp_fused<T>(n, x, p, r, w, dinv, part, nb_apply, part_r, sc, k & 1, s, check,
+                               k == 0, stored_rows(op, which));
+        continue;
+      }
+      if (fused4) {
+        const int k = it + c;
+        const PZIter<T> pz{r, nullptr, 0, sc, k & 1, check ? 1 : 0, k == 0 ? 1 : 0, 0};
+        if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed], s));
+        rc = launch_apply_pz<T>(op, p, w, masked, part, done, pz, s);
+        if (rc) return rc;
+        if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed++ + 1], s));
+        cg_fin_alpha(nc, part, nb_apply, sc, s, check);
+        cg_update_rxp<T>(n, x, p, r, w, dinv, part, sc, s, check, k == 0, stored_rows(op, which));
+        cg_fin_beta(nc, nb_vec, part, sc, s, check);
+        continue;
       }
       if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed], s));
       rc = mass_wl ? launch_mass_wl(op, f32, internal_map(op), p, masked, part, done, s)
                    : launch_apply(op, which, f32, internal_map(op), p, w, masked, part, done, s);
       if (rc) return rc;
       if (tm) BP_HIP(hipEventRecord(op->apply_ev[2 * timed++ + 1], s));
-      if constexpr (sizeof(T) == 8) {
-        if (fused) {
-          const int parity = (it + c) & 1;
-          cg_update_r_fused(nc, n, r, w, dinv, part, nb_apply, part_r, sc, parity, s, check,
-                            stored_rows(op, which));
-          cg_update_xp_fused(nc, n, x, p, r, part_r, sc, parity, s, check);
-          continue;
-        }
+      if (fused) {
+        const int parity = (it + c) & 1;
+        cg_update_r_fused<T>(nc, n, r, w, dinv, part, nb_apply, part_r, sc, parity, s, check,
+                             stored_rows(op, which));
+        cg_update_xp_fused<T>(nc, n, x, p, r, part_r, sc, parity, s, check);
+        continue;
       }
       cg_fin_alpha(nc, part, nb_apply, sc, s, check);
       if (mass_wl)
@@ -412,9 +407,7 @@ int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, con
     }
   }
   BP_HIP(hipEventRecord(op->ev1, s));
-  if constexpr (sizeof(T) == 8) {
-    if (fused2 && it > 0) cg_fin_rxp_fused(nc, n, part_r, sc, s);  // r.z, r.r of the last x
-  }
+  if (fused2 && it > 0) cg_fin_rxp_fused(n, part_r, sc, s);  // r.z, r.r of the last x
   rc = download_scalars(op, sc, s);
   if (rc) return rc;
   float ms = 0.0f;

@@ -276,7 +276,7 @@ __device__ __forceinline__ void stiff_colloc_body(
     int64_t nelem, const int32_t *__restrict__ idx, const T *__restrict__ G,
     const T *__restrict__ Bb, const T *__restrict__ u, T *__restrict__ w, int64_t cs, int ncomp,
     int c0, int masked, double *__restrict__ part, const int *__restrict__ done, int own,
-    PZIter pz = {}) {
+    PZIter<T> pz = {}) {
   static constexpr GLLTables<P1, T> kD{};  // D^ and its transpose, compile-time constants
   const T *const tD = kD.D, *const tDt = kD.Dt;
   using PL = Plane<P1, P1>;
@@ -388,7 +388,7 @@ __device__ __forceinline__ void stiff_colloc_body(
     }
     if (!pz.first)
 #pragma unroll
-      for (int k = 0; k < P1; ++k) un[k] = __builtin_fma(pz_beta, un[k], pzz[k]);
+      for (int k = 0; k < P1; ++k) un[k] = fma((T)pz_beta, un[k], pzz[k]);
   }
 #pragma unroll 1
   for (int cc = 0; cc < nrun; ++cc) {
@@ -542,15 +542,15 @@ __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) __attribute__((amdgpu_wav
 }
 
 // The operator of the two-launch iteration (PZIter): p_k formed at the
-// gathered nodes from z_k and p_{k-1}, FP64, assembled output.
+// gathered nodes from z_k and p_{k-1}, assembled output.
 // One component (ncomp = 1): u = p_{k-1} (p_0 at k = 0), pz.z = z_k.
-template <int P1>
+template <int P1, typename T>
 __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) void k_stiff_colloc_pz(
-    int64_t nelem, const int32_t *__restrict__ idx, const double *__restrict__ G,
-    const double *__restrict__ u, double *__restrict__ w, int ncomp, int c0, int masked,
-    double *__restrict__ part, const int *__restrict__ done, int own, PZIter pz) {
-  stiff_colloc_body<P1, double, false, false, false, true>(
-      nelem, idx, G, nullptr, u, w, 0, ncomp, c0, masked, part, done, own, pz);
+    int64_t nelem, const int32_t *__restrict__ idx, const T *__restrict__ G,
+    const T *__restrict__ u, T *__restrict__ w, int ncomp, int c0, int masked,
+    double *__restrict__ part, const int *__restrict__ done, int own, PZIter<T> pz) {
+  stiff_colloc_body<P1, T, false, false, false, true>(nelem, idx, G, nullptr, u, w, 0, ncomp, c0,
+                                                      masked, part, done, own, pz);
 }
 
 template <int P1, typename T, bool LOCAL = false, bool HELM = false>

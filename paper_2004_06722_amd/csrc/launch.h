@@ -101,22 +101,31 @@ template <typename T>
 void cg_update_xp(int nc, int64_t n, T *x, T *p, const T *z, DevScalars *sc, hipStream_t s,
                   bool check = true);
 
-// The fused iteration of small meshes (FP64): at most kFusedRows partial
-// rows in both tables. The residual update computes alpha itself from the
-// operator's partials pa[nba][nc] and writes its own partials into pr
-// ([vec_blocks(n)][2 nc]); the direction update computes beta and the
-// convergence test from pr. Three launches per iteration instead of five;
-// parity = iteration index & 1 (selects the r.z slot, DevScalars::rzs).
+// The fused iteration of small and mid-size meshes. The residual update
+// computes alpha itself from the operator's partials pa[nba][nc] and writes its
+// own partials into pr ([rxp_rows(n)][2 nc]); the direction update computes beta
+// and the convergence test from pr. Three launches per iteration instead of
+// five; parity = iteration index & 1 (selects the r.z slot, DevScalars::rzs).
+// One node per thread up to kFusedRows groups of 256, kRxpNodes beyond, so that
+// the tables that every work-group reduces stay short.
 constexpr int64_t kFusedRows = 1024;
-bool cg_fused_fits(int64_t n, int64_t nb_apply);
-void cg_update_r_fused(int nc, int64_t n, double *z, double *w, const double *dinv,
-                       const double *pa, int64_t nba, double *pr, DevScalars *sc, int parity,
-                       hipStream_t s, bool check, int64_t n_own);
-void cg_update_xp_fused(int nc, int64_t n, double *x, double *p, const double *z,
-                        const double *pr, DevScalars *sc, int parity, hipStream_t s,
-                        bool check);
+constexpr int kRxpNodes = 4;
+// the wider form: components, and the bounds of its tables (20 iterations,
+// five launches -> three: BP3 p = 7, E = 11^3 772 -> 687 us, three components
+// there 1470 -> 1263 us, p = 11, E = 7^3 three components 1656 -> 1427 us)
+constexpr int kFusedWide = 4;
+constexpr int64_t kFused3ApplyRows = 4096, kFused3Product = int64_t(1) << 20;
+int64_t rxp_rows(int64_t n);  // partial rows of the fused vector kernels
+bool cg_fused_fits(int nc, int64_t n, int64_t nb_apply);
+template <typename T>
+void cg_update_r_fused(int nc, int64_t n, T *z, T *w, const T *dinv, const double *pa,
+                       int64_t nba, double *pr, DevScalars *sc, int parity, hipStream_t s,
+                       bool check, int64_t n_own);
+template <typename T>
+void cg_update_xp_fused(int nc, int64_t n, T *x, T *p, const T *z, const double *pr,
+                        DevScalars *sc, int parity, hipStream_t s, bool check);
 
-// The two-launch iteration of small and mid-size meshes (FP64, collocated
+// The two-launch iteration of small and mid-size meshes (collocated
 // stiffness, one component, p1 <= 9; PZIter; cg_fused2_fits): the operator
 // launch forms p_k = z_k + beta p_{k-1} while gathering and takes the
 // stopping test on r_k; cg_update_rxp_fused then
@@ -124,30 +133,29 @@ void cg_update_xp_fused(int nc, int64_t n, double *x, double *p, const double *z
 // r.z and r.r into pr. cg_fin_rxp_fused, once after the last iteration,
 // reduces pr into the scalars the host reads (r.z, r.r, and the stopping
 // test of the last iterate).
-// k_cg_update_rxp_fused: one node per thread up to kFusedRows groups,
-// kRxpNodes beyond; the bounds of the two partial tables (measured at p = 7:
-// the two-launch form gains 13-14% at E = 2^10, 2^11 and breaks even at 2^12)
-constexpr int kRxpNodes = 4;
-constexpr int64_t kFused2VecRows = 2048, kFused2ApplyRows = 8192;
-constexpr int64_t kFused2Product = int64_t(4) << 20;
-int64_t rxp_rows(int64_t n);  // partial rows of the vector kernel
+// The bounds of the two partial tables: every work-group of each launch reads
+// the other's (measured at p = 7: 13-14% gained at E = 2^10, 2^11; up to
+// products of 9M FP32 solves gain 1-10%, FP64 ones 0-4%, against the forms below)
+constexpr int64_t kFused2VecRows = 2400, kFused2ApplyRows = 8192;
+constexpr int64_t kFused2Product = int64_t(9) << 20;
 bool cg_fused2_fits(int64_t n, int64_t nb_apply);
 bool apply_pz_supported(const bp_op_s *op, int which);
-int launch_apply_pz(const bp_op_s *op, const double *p, double *w, bool masked, double *part,
-                    const int *done, const PZIter &pz, hipStream_t s);
-void cg_update_rxp_fused(int nc, int64_t n, double *x, double *p, double *z, double *w,
-                         const double *dinv, const double *pa, int64_t nba, double *pr,
-                         DevScalars *sc, int parity, hipStream_t s, bool check, bool first,
-                         int64_t n_own);
-void cg_fin_rxp_fused(int nc, int64_t n, const double *pr, DevScalars *sc, hipStream_t s);
+template <typename T>
+int launch_apply_pz(const bp_op_s *op, const T *p, T *w, bool masked, double *part,
+                    const int *done, const PZIter<T> &pz, hipStream_t s);
+template <typename T>
+void cg_update_rxp_fused(int64_t n, T *x, T *p, T *z, T *w, const T *dinv, const double *pa,
+                         int64_t nba, double *pr, DevScalars *sc, int parity, hipStream_t s,
+                         bool check, bool first, int64_t n_own);
+void cg_fin_rxp_fused(int64_t n, const double *pr, DevScalars *sc, hipStream_t s);
 // The four-launch form (one component, above those bounds): the operator
 // launch (PZIter with fused = 0: beta from k_fin_beta), cg_fin_alpha,
 // cg_update_rxp (p, x and z in one pass; partials for cg_fin_beta),
 // cg_fin_beta.
 bool cg_streams(int64_t n);  // FP64 vectors of n entries take the streaming kernels
-void cg_update_rxp(int64_t n, double *x, double *p, double *z, double *w, const double *dinv,
-                   double *part, DevScalars *sc, hipStream_t s, bool check, bool first,
-                   int64_t n_own);
+template <typename T>
+void cg_update_rxp(int64_t n, T *x, T *p, T *z, T *w, const T *dinv, double *part,
+                   DevScalars *sc, hipStream_t s, bool check, bool first, int64_t n_own);
 
 // transposed gather Q^T w_L: w[c][g] = sum of wl[c][pos[k]] for k in
 // [off[v], off[v+1]) in ascending order (wl is [nc][nl]), v = iperm[g] or g;

@@ -162,11 +162,11 @@ int dispatch(const bp_op_s *op, int which, const NodeMap &m, const T *G, const T
 
 // The operator of the two-launch iteration (PZIter): collocated stiffness,
 // one component.
-template <int P1>
-int stiff_colloc_pz(const bp_op_s *op, const double *G, const double *p, double *w, int masked,
-                    double *part, const int *done, const PZIter &pz, hipStream_t s) {
+template <int P1, typename T>
+int stiff_colloc_pz(const bp_op_s *op, const T *G, const T *p, T *w, int masked, double *part,
+                    const int *done, const PZIter<T> &pz, hipStream_t s) {
   using PL = Plane<P1, P1>;
-  hipLaunchKernelGGL((k_stiff_colloc_pz<P1>), dim3(apply_blocks(op)), dim3(PL::THREADS), 0, s,
+  hipLaunchKernelGGL((k_stiff_colloc_pz<P1, T>), dim3(apply_blocks(op)), dim3(PL::THREADS), 0, s,
                      op->nelem, op->idx, G, p, w, op->ncomp, 0, masked, part, done, op->n_owned > 0, pz);
   return BP_OK;
 }
@@ -256,12 +256,17 @@ bool apply_pz_supported(const bp_op_s *op, int which) {
   return op->colloc && which == BP_STIFF && op->ncomp == 1 && op->p1 >= 2 && op->p1 <= 9;
 }
 
-int launch_apply_pz(const bp_op_s *op, const double *p, double *w, bool masked, double *part,
-                    const int *done, const PZIter &pz, hipStream_t s) {
+template <typename T>
+int launch_apply_pz(const bp_op_s *op, const T *p, T *w, bool masked, double *part,
+                    const int *done, const PZIter<T> &pz, hipStream_t s) {
   if (!apply_pz_supported(op, BP_STIFF))
     return set_error(BP_ERR_ARG,
                      "two-launch iteration: collocated stiffness, one component, p <= 8");
-  const double *G = op->kappa_set ? op->Gk : op->G;
+  const T *G;
+  if constexpr (sizeof(T) == 4)
+    G = op->kappa_set ? op->Gk32 : op->G32;
+  else
+    G = op->kappa_set ? op->Gk : op->G;
   const int m = masked ? 1 : 0;
   int rc = BP_OK;
   switch (op->p1) {
@@ -276,6 +281,10 @@ int launch_apply_pz(const bp_op_s *op, const double *p, double *w, bool masked, 
   BP_HIP(hipGetLastError());
   return BP_OK;
 }
+template int launch_apply_pz<double>(const bp_op_s *, const double *, double *, bool, double *,
+                                     const int *, const PZIter<double> &, hipStream_t);
+template int launch_apply_pz<float>(const bp_op_s *, const float *, float *, bool, double *,
+                                    const int *, const PZIter<float> &, hipStream_t);
 
 int launch_apply_local(const bp_op_s *op, int which, bool f32, const void *uL, void *wL,
                        hipStream_t s) {

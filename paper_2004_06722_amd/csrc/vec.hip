@@ -602,31 +602,37 @@ __device__ __forceinline__ void block_reduce_rows(const double *__restrict__ par
   __syncthreads();
 }
 
-// z -= alpha dinv w for every component (one thread per node), alpha from
-// the operator's partials pa[nba][NC] and r.z of this iteration (rz_old);
-// partials of the new r.z and r.r into pr. A breakdown (see k_fin_alpha) or
-// a non-finite p.Ap leaves z as it is in every work-group and, with a
-// stopping test, ends the solve.
-template <int NC>
+// z -= alpha dinv w for every component (K nodes per thread, 256 apart), alpha
+// from the operator's partials pa[nba][NC] and r.z of this iteration (rz_old);
+// partials of the new r.z and r.r into pr, one row per K * 256 nodes. A
+// breakdown (see k_fin_alpha) or a non-finite p.Ap leaves z as it is in every
+// work-group and, with a stopping test, ends the solve.
+template <typename T, int NC, int K>
 __global__ __launch_bounds__(kVecThreads) void k_cg_update_r_fused(
-    int64_t n, double *__restrict__ z, double *__restrict__ w, const double *__restrict__ dinv,
+    int64_t n, T *__restrict__ z, T *__restrict__ w, const T *__restrict__ dinv,
     const double *__restrict__ pa, int64_t nba, double *__restrict__ pr, DevScalars *sc,
     int parity, int check, int64_t n_own) {
   if (check && sc->done) {
     if (blockIdx.x == 0 && threadIdx.x == 0) sc->halted = 1;
     return;
   }
-  // the node's vectors are requested first, so that they arrive while the
+  // the nodes' vectors are requested first, so that they arrive while the
   // partial rows are reduced
-  const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
-  const bool in = v < n;
-  double di = 0.0, zo[NC], wo[NC];
-  if (in) {
-    di = dinv[v];
+  const int64_t v0 = (int64_t)blockIdx.x * (K * kVecThreads) + threadIdx.x;
+  T di[K], zo[K][NC], wo[K][NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      zo[c] = z[c * n + v];
-      wo[c] = w[c * n + v];
+  for (int j = 0; j < K; ++j) {
+    const int64_t v = v0 + j * kVecThreads;
+    di[j] = T(0);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) zo[j][c] = wo[j][c] = T(0);
+    if (v < n) {
+      di[j] = dinv[v];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        zo[j][c] = z[c * n + v];
+        wo[j][c] = w[c * n + v];
+      }
     }
   }
   __shared__ double pap[NC];
@@ -653,39 +659,44 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_update_r_fused(
   double acc[2 * NC];
 #pragma unroll
   for (int c = 0; c < 2 * NC; ++c) acc[c] = 0.0;
-  if (in) {
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const int64_t v = v0 + j * kVecThreads;
+    if (v >= n) continue;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const double zv = zo[c] - (al[c] * di) * wo[c];
+      const T zv = zo[j][c] - ((T)al[c] * di[j]) * wo[j][c];
       z[c * n + v] = zv;
-      if (v >= n_own) w[c * n + v] = 0.0;
-      const double rv = di != 0.0 ? zv / di : 0.0;
-      acc[c] = rv * zv;
-      acc[NC + c] = rv * rv;
+      if (v >= n_own) w[c * n + v] = T(0);
+      const T rv = di[j] != T(0) ? zv / di[j] : T(0);
+      acc[c] += (double)rv * (double)zv;
+      acc[NC + c] += (double)rv * (double)rv;
     }
   }
   block_partials<2 * NC>(acc, pr);
 }
 
-// x += alpha p, then p = z + beta p unless the iteration converged; beta and
-// the convergence test from the residual update's partials pr[nbv][2 NC] and
-// r.z of this iteration; work-group 0 stores the new r.z into the other
-// parity slot and updates the scalars the host polls.
-template <int NC>
+// x += alpha p, then p = z + beta p unless the iteration converged (K nodes per
+// thread); beta and the convergence test from the residual update's partials
+// pr[nbv][2 NC] and r.z of this iteration; work-group 0 stores the new r.z into
+// the other parity slot and updates the scalars the host polls.
+template <typename T, int NC, int K>
 __global__ __launch_bounds__(kVecThreads) void k_cg_update_xp_fused(
-    int64_t n, double *__restrict__ x, double *__restrict__ p, const double *__restrict__ z,
+    int64_t n, T *__restrict__ x, T *__restrict__ p, const T *__restrict__ z,
     const double *__restrict__ pr, int64_t nbv, DevScalars *sc, int parity, int check) {
   if (check && sc->halted) return;
-  const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
-  const bool in = v < n;
-  double pv[NC], xv[NC], zv[NC];
-  if (in) {  // requested before the reduction, as in the residual update
+  const int64_t v0 = (int64_t)blockIdx.x * (K * kVecThreads) + threadIdx.x;
+  T pv[K][NC], xv[K][NC], zv[K][NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      pv[c] = p[c * n + v];
-      xv[c] = x[c * n + v];
-      zv[c] = z[c * n + v];
-    }
+  for (int j = 0; j < K; ++j) {  // requested before the reduction, as above
+    const int64_t v = v0 + j * kVecThreads;
+    if (v < n)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        pv[j][c] = p[c * n + v];
+        xv[j][c] = x[c * n + v];
+        zv[j][c] = z[c * n + v];
+      }
   }
   __shared__ double res[2 * NC];
   block_reduce_rows<2 * NC>(pr, nbv, res);
@@ -714,11 +725,15 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_update_xp_fused(
     if (bad) sc->nonfinite = 1;
     if (!dir) sc->done = 1;
   }
-  if (!in) return;
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    x[c * n + v] = xv[c] + al[c] * pv[c];
-    if (dir) p[c * n + v] = zv[c] + be[c] * pv[c];
+  for (int j = 0; j < K; ++j) {
+    const int64_t v = v0 + j * kVecThreads;
+    if (v >= n) continue;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      x[c * n + v] = xv[j][c] + (T)al[c] * pv[j][c];
+      if (dir) p[c * n + v] = zv[j][c] + (T)be[c] * pv[j][c];
+    }
   }
 }
 
@@ -734,50 +749,36 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_update_xp_fused(
 // 1024 rows, so that the table that every work-group of the operator reduces
 // stays short. A breakdown or a non-finite p.Ap ends the
 // solve as in k_cg_update_r_fused.
-template <int NC, int K>
+template <typename T, int K>
 __global__ __launch_bounds__(kVecThreads) void k_cg_update_rxp_fused(
-    int64_t n, double *__restrict__ x, double *__restrict__ p, double *__restrict__ z,
-    double *__restrict__ w, const double *__restrict__ dinv, const double *__restrict__ pa,
-    int64_t nba, double *__restrict__ pr, DevScalars *sc, int parity, int check, int first,
-    int64_t n_own) {
+    int64_t n, T *__restrict__ x, T *__restrict__ p, T *__restrict__ z, T *__restrict__ w,
+    const T *__restrict__ dinv, const double *__restrict__ pa, int64_t nba,
+    double *__restrict__ pr, DevScalars *sc, int parity, int check, int first, int64_t n_own) {
   if (check && sc->done) return;  // x_k met the stopping test in the operator launch
   const int64_t v0 = (int64_t)blockIdx.x * (K * kVecThreads) + threadIdx.x;
-  double di[K], zo[K][NC], wo[K][NC], po[K][NC], xo[K][NC];
+  T di[K], zo[K], wo[K], po[K], xo[K];
 #pragma unroll
   for (int j = 0; j < K; ++j) {  // requested before the reduction
     const int64_t v = v0 + j * kVecThreads;
-    di[j] = 0.0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) zo[j][c] = wo[j][c] = po[j][c] = xo[j][c] = 0.0;
+    di[j] = zo[j] = wo[j] = po[j] = xo[j] = T(0);
     if (v < n) {
       di[j] = dinv[v];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        zo[j][c] = z[c * n + v];
-        wo[j][c] = w[c * n + v];
-        po[j][c] = p[c * n + v];
-        xo[j][c] = x[c * n + v];
-      }
+      zo[j] = z[v];
+      wo[j] = w[v];
+      po[j] = p[v];
+      xo[j] = x[v];
     }
   }
-  __shared__ double pap[NC];
-  block_reduce_rows<NC>(pa, nba, pap);
-  double al[NC], be[NC];
-  int bad = 0, brk = 0;
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const double rz = sc->rzs[parity][c];
-    al[c] = pap[c] != 0.0 ? rz / pap[c] : 0.0;
-    be[c] = first ? 0.0 : sc->beta[c];
-    brk |= indefinite(rz, pap[c]);
-    bad |= !isfinite(pap[c]);
-  }
+  __shared__ double pap[1];
+  block_reduce_rows<1>(pa, nba, pap);
+  const double rz0 = sc->rzs[parity][0];
+  const double ald = pap[0] != 0.0 ? rz0 / pap[0] : 0.0;
+  const T al = (T)ald, be = first ? T(0) : (T)sc->beta[0];
+  const int brk = indefinite(rz0, pap[0]), bad = !isfinite(pap[0]);
   const bool stop = check && (brk || bad);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    for (int c = 0; c < NC; ++c) {
-      sc->pap[c] = pap[c];
-      sc->alpha[c] = al[c];
-    }
+    sc->pap[0] = pap[0];
+    sc->alpha[0] = ald;
     if (brk) sc->breakdown = 1;
     if (bad) sc->nonfinite = 1;
     if (stop)
@@ -786,27 +787,22 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_update_rxp_fused(
       sc->iters += 1;
   }
   if (stop) return;
-  double acc[2 * NC];
-#pragma unroll
-  for (int c = 0; c < 2 * NC; ++c) acc[c] = 0.0;
+  double acc[2] = {0.0, 0.0};
 #pragma unroll
   for (int j = 0; j < K; ++j) {
     const int64_t v = v0 + j * kVecThreads;
     if (v >= n) continue;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const double pk = first ? po[j][c] : __builtin_fma(be[c], po[j][c], zo[j][c]);
-      if (!first) p[c * n + v] = pk;
-      x[c * n + v] = xo[j][c] + al[c] * pk;
-      const double zv = zo[j][c] - (al[c] * di[j]) * wo[j][c];
-      z[c * n + v] = zv;
-      if (v >= n_own) w[c * n + v] = 0.0;
-      const double rv = di[j] != 0.0 ? zv / di[j] : 0.0;
-      acc[c] += rv * zv;
-      acc[NC + c] += rv * rv;
-    }
+    const T pk = first ? po[j] : fma(be, po[j], zo[j]);
+    if (!first) p[v] = pk;
+    x[v] = xo[j] + al * pk;
+    const T zv = zo[j] - (al * di[j]) * wo[j];
+    z[v] = zv;
+    if (v >= n_own) w[v] = T(0);
+    const T rv = di[j] != T(0) ? zv / di[j] : T(0);
+    acc[0] += (double)rv * (double)zv;
+    acc[1] += (double)rv * (double)rv;
   }
-  block_partials<2 * NC>(acc, pr);
+  block_partials<2>(acc, pr);
 }
 
 // The vector kernel of the four-launch form (one component, meshes above the
@@ -817,30 +813,45 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_update_rxp_fused(
 // partials of r.z and r.r as k_cg_update_r writes them (for k_fin_beta).
 // Five words read and three written per node, against the six and four of
 // the residual and direction updates.
-template <bool NT>
-__global__ __launch_bounds__(kVecThreads) void k_cg_update_rxp(
-    int64_t n, double *__restrict__ x, double *__restrict__ p, double *__restrict__ z,
-    double *__restrict__ w, const double *__restrict__ dinv, double *__restrict__ part,
-    const DevScalars *__restrict__ sc, int check, int first, int64_t n_own) {
+template <typename T, bool NT>
+__global__ __launch_bounds__(kGroupThreads<T>) void k_cg_update_rxp(
+    int64_t n, T *__restrict__ x, T *__restrict__ p, T *__restrict__ z, T *__restrict__ w,
+    const T *__restrict__ dinv, double *__restrict__ part, const DevScalars *__restrict__ sc,
+    int check, int first, int64_t n_own) {
+  constexpr int K = kNodesPerThread<T>, TH = kGroupThreads<T>;
   if (check && sc->done) return;
-  const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
-  const double al = sc->alpha[0], be = first ? 0.0 : sc->beta[0];
-  double rz = 0.0, rr = 0.0;
-  if (v < n) {
-    const double di = ld_v<NT>(dinv + v), zo = ld_v<NT>(z + v), wo = ld_v<NT>(w + v);
-    const double po = ld_v<NT>(p + v), xo = ld_v<NT>(x + v);
-    const double pk = first ? po : __builtin_fma(be, po, zo);
-    if (!first) st_v<NT>(p + v, pk);
-    st_v<NT>(x + v, xo + al * pk);
-    const double zv = zo - (al * di) * wo;
-    st_v<NT>(z + v, zv);
-    if (v >= n_own) st_v<NT>(w + v, 0.0);
-    const double rv = di != 0.0 ? zv / di : 0.0;
-    rz = rv * zv;
-    rr = rv * rv;
+  const int64_t v0 = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  const T al = (T)sc->alpha[0], be = first ? T(0) : (T)sc->beta[0];
+  T di[K], zo[K], wo[K], po[K], xo[K];
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const int64_t v = v0 + j * TH;
+    di[j] = zo[j] = wo[j] = po[j] = xo[j] = T(0);
+    if (v < n) {
+      di[j] = ld_v<NT>(dinv + v);
+      zo[j] = ld_v<NT>(z + v);
+      wo[j] = ld_v<NT>(w + v);
+      po[j] = ld_v<NT>(p + v);
+      xo[j] = ld_v<NT>(x + v);
+    }
   }
-  block_partial1(rz, part, 2, 0);
-  block_partial1(rr, part, 2, 1);
+  double rz = 0.0, rr = 0.0;
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const int64_t v = v0 + j * TH;
+    if (v >= n) continue;
+    const T pk = first ? po[j] : fma(be, po[j], zo[j]);
+    if (!first) st_v<NT>(p + v, pk);
+    st_v<NT>(x + v, xo[j] + al * pk);
+    const T zv = zo[j] - (al * di[j]) * wo[j];
+    st_v<NT>(z + v, zv);
+    if (v >= n_own) st_v<NT>(w + v, T(0));
+    const T rv = di[j] != T(0) ? zv / di[j] : T(0);
+    rz += (double)rv * (double)zv;
+    rr += (double)rv * (double)rv;
+  }
+  block_partial1<TH>(rz, part, 2, 0);
+  block_partial1<TH>(rr, part, 2, 1);
 }
 
 // After the last iteration of the two-launch form: r.z and r.r of the last
@@ -856,6 +867,7 @@ __global__ __launch_bounds__(kFinThreads) void k_fin_rxp_fused(const double *__r
   reduce_columns<2 * NC>(pr, nb, res);
   if (threadIdx.x == 0) {
     for (int c = 0; c < nc; ++c) {
+      sc->rzp[c] = sc->rz[c];
       sc->rz[c] = res[c];
       sc->rr[c] = res[nc + c];
       if (!isfinite(res[c]) || !isfinite(res[nc + c])) sc->nonfinite = 1;
@@ -1409,7 +1421,7 @@ __global__ __launch_bounds__(kFinThreads) void k_fin_restart(const double *__res
     int bad = 0;
     for (int c = 0; c < NC; ++c) {
       sc->beta[c] = sc->rzp[c] != 0.0 ? res[c] / sc->rzp[c] : 0.0;
-      sc->rz[c] = res[c];
+      sc->rz[c] = sc->rzs[0][c] = res[c];  // the next run's iteration 0
       sc->rr[c] = sc->bb[c] = res[NC + c];
       bad |= !isfinite(res[c]) || !isfinite(res[NC + c]);
     }
@@ -1545,68 +1557,96 @@ void cg_fin_beta(int nc, int64_t nb, const double *part, DevScalars *sc, hipStre
   launch_fin(FinKind::Beta, nc, src, rows, sc, s, check ? 1 : 0);
 }
 
-template <int NC>
-static void launch_fused_nc(bool residual, int64_t n, double *x, double *p, double *z,
-                            double *w, const double *dinv, const double *pa, int64_t nba,
-                            double *pr, DevScalars *sc, int parity, int check, int64_t n_own,
-                            hipStream_t s) {
-  if (residual)
-    hipLaunchKernelGGL((k_cg_update_r_fused<NC>), dim3(vec_blocks(n)), dim3(kVecThreads), 0, s,
-                       n, z, w, dinv, pa, nba, pr, sc, parity, check, n_own);
-  else
-    hipLaunchKernelGGL((k_cg_update_xp_fused<NC>), dim3(vec_blocks(n)), dim3(kVecThreads), 0,
-                       s, n, x, p, z, pr, vec_blocks(n), sc, parity, check);
+// the kernels of the three-launch form: four nodes per thread above kFusedRows
+// groups of 256 (cg_fused_fits: up to four components there)
+template <typename T, int NC>
+static void launch_r_fused(int64_t n, T *z, T *w, const T *dinv, const double *pa, int64_t nba,
+                           double *pr, DevScalars *sc, int parity, int check, int64_t n_own,
+                           hipStream_t s) {
+  const dim3 g(rxp_rows(n)), t(kVecThreads);
+  if constexpr (NC <= kFusedWide)
+    if (vec_blocks(n) > kFusedRows) {
+      hipLaunchKernelGGL((k_cg_update_r_fused<T, NC, kRxpNodes>), g, t, 0, s, n, z, w, dinv, pa,
+                         nba, pr, sc, parity, check, n_own);
+      return;
+    }
+  hipLaunchKernelGGL((k_cg_update_r_fused<T, NC, 1>), g, t, 0, s, n, z, w, dinv, pa, nba, pr, sc,
+                     parity, check, n_own);
 }
-
-static void launch_fused(bool residual, int nc, int64_t n, double *x, double *p, double *z,
-                         double *w, const double *dinv, const double *pa, int64_t nba,
-                         double *pr, DevScalars *sc, int parity, int check, int64_t n_own,
-                         hipStream_t s) {
-#define BP_FUSED(NC) \
-  launch_fused_nc<NC>(residual, n, x, p, z, w, dinv, pa, nba, pr, sc, parity, check, n_own, s)
-  switch (nc) {
-    case 1: BP_FUSED(1); break;
-    case 2: BP_FUSED(2); break;
-    case 3: BP_FUSED(3); break;
-    case 4: BP_FUSED(4); break;
-    case 5: BP_FUSED(5); break;
-    case 6: BP_FUSED(6); break;
-    case 7: BP_FUSED(7); break;
-    default: BP_FUSED(kMaxComp); break;
+template <typename T, int NC>
+static void launch_xp_fused(int64_t n, T *x, T *p, const T *z, const double *pr, DevScalars *sc,
+                            int parity, int check, hipStream_t s) {
+  const dim3 g(rxp_rows(n)), t(kVecThreads);
+  if constexpr (NC <= kFusedWide)
+    if (vec_blocks(n) > kFusedRows) {
+      hipLaunchKernelGGL((k_cg_update_xp_fused<T, NC, kRxpNodes>), g, t, 0, s, n, x, p, z, pr,
+                         rxp_rows(n), sc, parity, check);
+      return;
+    }
+  hipLaunchKernelGGL((k_cg_update_xp_fused<T, NC, 1>), g, t, 0, s, n, x, p, z, pr, rxp_rows(n),
+                     sc, parity, check);
+}
+#define BP_COMPONENTS(nc, CALL) \
+  switch (nc) {                 \
+    case 1: CALL(1); break;     \
+    case 2: CALL(2); break;     \
+    case 3: CALL(3); break;     \
+    case 4: CALL(4); break;     \
+    case 5: CALL(5); break;     \
+    case 6: CALL(6); break;     \
+    case 7: CALL(7); break;     \
+    default: CALL(kMaxComp);    \
   }
-#undef BP_FUSED
+
+template <typename T>
+void cg_update_r_fused(int nc, int64_t n, T *z, T *w, const T *dinv, const double *pa,
+                       int64_t nba, double *pr, DevScalars *sc, int parity, hipStream_t s,
+                       bool check, int64_t n_own) {
+  const int ch = check ? 1 : 0;
+#define BP_CALL(NC) launch_r_fused<T, NC>(n, z, w, dinv, pa, nba, pr, sc, parity, ch, n_own, s)
+  BP_COMPONENTS(nc, BP_CALL)
+#undef BP_CALL
 }
 
-void cg_update_rxp_fused(int nc, int64_t n, double *x, double *p, double *z, double *w,
-                         const double *dinv, const double *pa, int64_t nba, double *pr,
-                         DevScalars *sc, int parity, hipStream_t s, bool check, bool first,
-                         int64_t n_own) {
-  (void)nc;  // one component (apply_pz_supported)
+template <typename T>
+void cg_update_xp_fused(int nc, int64_t n, T *x, T *p, const T *z, const double *pr,
+                        DevScalars *sc, int parity, hipStream_t s, bool check) {
+  const int ch = check ? 1 : 0;
+#define BP_CALL(NC) launch_xp_fused<T, NC>(n, x, p, z, pr, sc, parity, ch, s)
+  BP_COMPONENTS(nc, BP_CALL)
+#undef BP_CALL
+}
+
+template <typename T>
+void cg_update_rxp_fused(int64_t n, T *x, T *p, T *z, T *w, const T *dinv, const double *pa,
+                         int64_t nba, double *pr, DevScalars *sc, int parity, hipStream_t s,
+                         bool check, bool first, int64_t n_own) {
+  const dim3 g(rxp_rows(n)), t(kVecThreads);
+  const int ch = check ? 1 : 0, f = first ? 1 : 0;
   if (vec_blocks(n) <= kFusedRows)
-    hipLaunchKernelGGL((k_cg_update_rxp_fused<1, 1>), dim3(rxp_rows(n)), dim3(kVecThreads), 0,
-                       s, n, x, p, z, w, dinv, pa, nba, pr, sc, parity, check ? 1 : 0,
-                       first ? 1 : 0, n_own);
+    hipLaunchKernelGGL((k_cg_update_rxp_fused<T, 1>), g, t, 0, s, n, x, p, z, w, dinv, pa, nba, pr,
+                       sc, parity, ch, f, n_own);
   else
-    hipLaunchKernelGGL((k_cg_update_rxp_fused<1, kRxpNodes>), dim3(rxp_rows(n)),
-                       dim3(kVecThreads), 0, s, n, x, p, z, w, dinv, pa, nba, pr, sc, parity,
-                       check ? 1 : 0, first ? 1 : 0, n_own);
+    hipLaunchKernelGGL((k_cg_update_rxp_fused<T, kRxpNodes>), g, t, 0, s, n, x, p, z, w, dinv, pa,
+                       nba, pr, sc, parity, ch, f, n_own);
 }
 
-void cg_fin_rxp_fused(int nc, int64_t n, const double *pr, DevScalars *sc, hipStream_t s) {
-  (void)nc;
+void cg_fin_rxp_fused(int64_t n, const double *pr, DevScalars *sc, hipStream_t s) {
   hipLaunchKernelGGL((k_fin_rxp_fused<1>), dim3(1), dim3(kFinThreads), 0, s, pr, rxp_rows(n),
                      sc);
 }
 
-void cg_update_rxp(int64_t n, double *x, double *p, double *z, double *w, const double *dinv,
-                   double *part, DevScalars *sc, hipStream_t s, bool check, bool first,
-                   int64_t n_own) {
-  if (n * (int64_t)sizeof(double) >= kStreamBytes)
-    hipLaunchKernelGGL((k_cg_update_rxp<true>), dim3(vec_blocks(n)), dim3(kVecThreads), 0, s, n,
-                       x, p, z, w, dinv, part, sc, check ? 1 : 0, first ? 1 : 0, n_own);
+template <typename T>
+void cg_update_rxp(int64_t n, T *x, T *p, T *z, T *w, const T *dinv, double *part,
+                   DevScalars *sc, hipStream_t s, bool check, bool first, int64_t n_own) {
+  const dim3 g(vec_blocks(n)), t(kGroupThreads<T>);
+  const int ch = check ? 1 : 0, f = first ? 1 : 0;
+  if (n * (int64_t)sizeof(T) >= kStreamBytes)
+    hipLaunchKernelGGL((k_cg_update_rxp<T, true>), g, t, 0, s, n, x, p, z, w, dinv, part, sc, ch,
+                       f, n_own);
   else
-    hipLaunchKernelGGL((k_cg_update_rxp<false>), dim3(vec_blocks(n)), dim3(kVecThreads), 0, s,
-                       n, x, p, z, w, dinv, part, sc, check ? 1 : 0, first ? 1 : 0, n_own);
+    hipLaunchKernelGGL((k_cg_update_rxp<T, false>), g, t, 0, s, n, x, p, z, w, dinv, part, sc, ch,
+                       f, n_own);
 }
 
 bool cg_streams(int64_t n) { return n * (int64_t)sizeof(double) >= kStreamBytes; }
@@ -1626,22 +1666,11 @@ bool cg_fused2_fits(int64_t n, int64_t nb_apply) {
          nv * nb_apply <= kFused2Product;
 }
 
-bool cg_fused_fits(int64_t n, int64_t nb_apply) {
-  return vec_blocks(n) <= kFusedRows && nb_apply <= kFusedRows;
-}
-
-void cg_update_r_fused(int nc, int64_t n, double *z, double *w, const double *dinv,
-                       const double *pa, int64_t nba, double *pr, DevScalars *sc, int parity,
-                       hipStream_t s, bool check, int64_t n_own) {
-  launch_fused(true, nc, n, nullptr, nullptr, z, w, dinv, pa, nba, pr, sc, parity,
-               check ? 1 : 0, n_own, s);
-}
-
-void cg_update_xp_fused(int nc, int64_t n, double *x, double *p, const double *z,
-                        const double *pr, DevScalars *sc, int parity, hipStream_t s,
-                        bool check) {
-  launch_fused(false, nc, n, x, p, const_cast<double *>(z), nullptr, nullptr, nullptr, 0,
-               const_cast<double *>(pr), sc, parity, check ? 1 : 0, 0, s);
+bool cg_fused_fits(int nc, int64_t n, int64_t nb_apply) {
+  if (vec_blocks(n) <= kFusedRows && nb_apply <= kFusedRows) return true;
+  const int64_t nv = rxp_rows(n);
+  return nc <= kFusedWide && nv <= kFusedRows && nb_apply <= kFused3ApplyRows &&
+         nv * nb_apply * nc <= kFused3Product;
 }
 
 template <typename T>
@@ -1837,6 +1866,20 @@ template void cg_restart<double>(int, int64_t, double *, double *, const double 
 void dc_accumulate(int64_t n, double *x, const float *d, hipStream_t s) {
   hipLaunchKernelGGL(k_accumulate, dim3(grid_blocks(n)), dim3(kVecThreads), 0, s, x, d, n);
 }
+
+#define BP_INSTANCES(T)                                                                         \
+  template void cg_update_r_fused<T>(int, int64_t, T *, T *, const T *, const double *, int64_t, \
+                                     double *, DevScalars *, int, hipStream_t, bool, int64_t);   \
+  template void cg_update_xp_fused<T>(int, int64_t, T *, T *, const T *, const double *,         \
+                                      DevScalars *, int, hipStream_t, bool);                     \
+  template void cg_update_rxp_fused<T>(int64_t, T *, T *, T *, T *, const T *, const double *,   \
+                                       int64_t, double *, DevScalars *, int, hipStream_t, bool,  \
+                                       bool, int64_t);                                           \
+  template void cg_update_rxp<T>(int64_t, T *, T *, T *, T *, const T *, double *, DevScalars *, \
+                                 hipStream_t, bool, bool, int64_t);
+BP_INSTANCES(double)
+BP_INSTANCES(float)
+#undef BP_INSTANCES
 
 template void cg_init<double>(int, int64_t, const double *, const double *, double *,
                               const int32_t *, double *, double *, double *, const double *,
