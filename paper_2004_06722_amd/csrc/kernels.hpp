@@ -726,13 +726,15 @@ __device__ __forceinline__ void gl_body(
   for (int k = 0; k < P1; ++k)
     gk[k] = LOCAL ? (int)(ec * N3) + ci + P1 * (cj + P1 * k)
                   : idx[ec * N3 + ci + P1 * (cj + P1 * k)];
+  // (component by component: the planes of one are contiguous; points first it
+  // was 2% slower, BP3 p = 7, E = 48^3 29.76 against 29.10 ms a solve)
   T g[NG][Q];
   {
     const T *Ge = Gm + ec * NG * NQ + rl;
 #pragma unroll
-    for (int a = 0; a < Q; ++a)
+    for (int n = 0; n < NG; ++n)
 #pragma unroll
-      for (int n = 0; n < NG; ++n) g[n][a] = __builtin_nontemporal_load(Ge + n * NQ + a * QQ);
+      for (int a = 0; a < Q; ++a) g[n][a] = __builtin_nontemporal_load(Ge + n * NQ + a * QQ);
   }
   unsigned mb = 0;  // bit k: node k of the column is gathered and scattered
 #pragma unroll
