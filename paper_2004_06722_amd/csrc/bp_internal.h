@@ -127,11 +127,13 @@ struct bp_op_s {
   int cg_variant = 0;  // BP_CG_STANDARD or BP_CG_SINGLE_REDUCTION (bp_pcg_solve)
   int cg_fuse = 2;  // BP_OPT_CG_FUSE: fewer launches per iteration (0 off, 1, 2, 3)
   double *sv = nullptr;  // s = A p of the single-reduction PCG (allocated when selected)
-  // Gauss-Legendre operators: the gather map transposed (CSR over global
-  // nodes: the element-local slots e p1^3 + l of node g are
-  // tr_pos[tr_off[g] .. tr_off[g + 1]), ascending) and the element-local
+  // Gauss-Legendre operators: the gather map transposed (the element-local
+  // slots e p1^3 + l of each node, ascending: tr_pair[v] = (first, second), -1
+  // for none; with more than two, (first, -2 - k) and the others in the record
+  // tr_list[k], ... = (their number, slots...) in the int4s) and the element-local
   // output wl [ncomp][nelem][p1^3] of the mass kernel (wl32 in FP32)
-  int32_t *tr_off = nullptr, *tr_pos = nullptr;
+  int2 *tr_pair = nullptr;
+  int4 *tr_list = nullptr;
   // internal node order (interior_first_order): perm[v] = the caller's id of
   // internal node v (NULL: the caller's order); internal nodes [0, n_owned)
   // are element-interior, each written by its element with a plain store;

@@ -81,8 +81,8 @@ void release(bp_op op) {
   dfree(op->part);
   dfree(op->tmp);
   dfree(op->sv);
-  dfree(op->tr_off);
-  dfree(op->tr_pos);
+  dfree(op->tr_pair);
+  dfree(op->tr_list);
   dfree(op->perm);
   dfree(op->iperm);
   dfree(op->bi);
@@ -254,7 +254,7 @@ int download_scalars(bp_op op, hipStream_t s) { return download_scalars(op, op->
 // so the vector updates need not clear them. The Gauss-Legendre mass
 // assembles w by adding Q^T w_L (gather_local) and needs w cleared.
 int64_t stored_rows(const bp_op_s *op, int which) {
-  return which == BP_MASS && op->tr_off ? 0 : op->n_owned;
+  return which == BP_MASS && op->tr_pair ? 0 : op->n_owned;
 }
 
 // b, x0 and x of a solve. With perm, b and x0 are in the caller's order and x is
@@ -329,7 +329,7 @@ int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, con
   const int *done = check ? &sc->done : nullptr;
   // mass on Gauss-Legendre points: the kernel stores w_L and the residual
   // update gathers w = Q^T w_L itself (w stays zero)
-  const bool mass_wl = which == BP_MASS && op->tr_off != nullptr;
+  const bool mass_wl = which == BP_MASS && op->tr_pair != nullptr;
   const int64_t nl = op->nelem * op->p1 * op->p1 * op->p1;
   const T *wl = reinterpret_cast<const T *>(sizeof(T) == 4 ? (const void *)op->wl32
                                                            : (const void *)op->wl);
@@ -391,7 +391,7 @@ int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, con
       }
       cg_fin_alpha(nc, part, nb_apply, sc, s, check);
       if (mass_wl)
-        cg_update_r_gather<T>(nc, n, nl, r, wl, op->tr_off, op->tr_pos, dinv, part, sc, s,
+        cg_update_r_gather<T>(nc, n, nl, r, wl, op->tr_pair, op->tr_list, dinv, part, sc, s,
                               check);
       else
         cg_update_r<T>(nc, n, r, w, dinv, part, sc, s, check, stored_rows(op, which));
@@ -732,28 +732,46 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
     if (op->fp32) TRY(dmalloc(&op->bi, nv));
     TRY(dmalloc(&op->xi, nv));
   }
-  // Gauss-Legendre operators: the transposed gather map (counting sort of the
-  // element-local slots by global node, ascending within a node) for the
-  // mass operator's fixed-order assembly, and its element-local output
+  // Gauss-Legendre operators: the transposed gather map (each node's
+  // element-local slots, ascending) for the mass operator's fixed-order
+  // assembly, and its element-local output
   const int64_t nl = nelem * n3;
   if (!op->colloc && nl < (int64_t(1) << 31)) {
     auto node = [&](int64_t k) -> size_t {
       const size_t g = (size_t)elem_dofs[k];
       return renum ? (size_t)new_of_old[g] : g;
     };
-    std::vector<int32_t> off((size_t)nglobal + 1, 0), pos((size_t)nl);
-    for (int64_t k = 0; k < nl; ++k) ++off[node(k) + 1];
-    for (int64_t g = 0; g < nglobal; ++g) off[(size_t)g + 1] += off[(size_t)g];
+    std::vector<int2> pair((size_t)nglobal, make_int2(-1, -1));
+    std::vector<int4> list(1);  // never empty: absent records read list[0]
     {
-      std::vector<int32_t> cur(off.begin(), off.end() - 1);
-      for (int64_t k = 0; k < nl; ++k) pos[(size_t)cur[node(k)]++] = (int32_t)k;
+      std::vector<int32_t> count((size_t)nglobal, 0);
+      for (int64_t k = 0; k < nl; ++k) ++count[node(k)];
+      int64_t rec = 0;
+      for (size_t v = 0; v < (size_t)nglobal; ++v)
+        if (count[v] > 2) {
+          pair[v].y = (int32_t)(-2 - rec);
+          rec += count[v] / 4 + (count[v] % 4 != 0);
+        }
+      list.assign((size_t)std::max<int64_t>(rec, 1), make_int4(0, 0, 0, 0));
     }
-    TRY(dmalloc(&op->tr_off, off.size()));
-    TRY(dmalloc(&op->tr_pos, pos.size()));
+    int32_t *flat = &list[0].x;
+    for (int64_t k = 0; k < nl; ++k) {
+      int2 &t = pair[node(k)];
+      if (t.x < 0) {
+        t.x = (int32_t)k;
+      } else if (t.y < -1) {
+        int32_t *rec = flat + 4 * (int64_t)(-2 - t.y);
+        rec[++rec[0]] = (int32_t)k;
+      } else {
+        t.y = (int32_t)k;
+      }
+    }
+    TRY(dmalloc(&op->tr_pair, pair.size()));
+    TRY(dmalloc(&op->tr_list, list.size()));
     TRY(dmalloc(&op->wl, nl * ncomp));
-    TRYHIP(hipMemcpyAsync(op->tr_off, off.data(), off.size() * sizeof(int32_t),
+    TRYHIP(hipMemcpyAsync(op->tr_pair, pair.data(), pair.size() * sizeof(int2),
                           hipMemcpyHostToDevice, s));
-    TRYHIP(hipMemcpyAsync(op->tr_pos, pos.data(), pos.size() * sizeof(int32_t),
+    TRYHIP(hipMemcpyAsync(op->tr_list, list.data(), list.size() * sizeof(int4),
                           hipMemcpyHostToDevice, s));
     TRYHIP(hipStreamSynchronize(s));
   }
@@ -826,7 +844,7 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
     TRY(dmalloc(&op->x32, nv));
     TRY(dmalloc(&op->b32, nv));
     TRY(dmalloc(&op->dinv32, nglobal));
-    if (op->tr_off) TRY(dmalloc(&op->wl32, nl * ncomp));
+    if (op->tr_pair) TRY(dmalloc(&op->wl32, nl * ncomp));
     TRYHIP(hipEventCreateWithFlags(&op->evm0, kTimingEvent));
     TRYHIP(hipEventCreateWithFlags(&op->evm1, kTimingEvent));
   }
@@ -924,7 +942,7 @@ int bp_apply(bp_op op, int which, int prec, const void *u, void *w, unsigned fla
     BP_HIP(hipGetLastError());
     return BP_OK;
   }
-  if (which == BP_MASS && op->tr_off)
+  if (which == BP_MASS && op->tr_pair)
     ;  // overwrites w
   else if (f32)
     fill_f32((float *)w, nv, 0.0f, s);

@@ -157,17 +157,17 @@ template <typename T>
 void cg_update_rxp(int64_t n, T *x, T *p, T *z, T *w, const T *dinv, double *part,
                    DevScalars *sc, hipStream_t s, bool check, bool first, int64_t n_own);
 
-// transposed gather Q^T w_L: w[c][g] = sum of wl[c][pos[k]] for k in
-// [off[v], off[v+1]) in ascending order (wl is [nc][nl]), v = iperm[g] or g;
+// transposed gather Q^T w_L: w[c][g] = sum of wl[c][.] over the slots of node
+// v = iperm[g] or g (pair and list as in bp_op_s), ascending (wl is [nc][nl]);
 // skipped while *done (done may be NULL)
 template <typename T>
-void gather_local(int nc, int64_t n, int64_t nl, const int32_t *off, const int32_t *pos,
+void gather_local(int nc, int64_t n, int64_t nl, const int2 *pair, const int4 *list,
                   const int32_t *iperm, const T *wl, T *w, const int *done, hipStream_t s);
 // cg_update_r with w = Q^T w_L gathered per node (no w vector is read,
 // written or cleared)
 template <typename T>
-void cg_update_r_gather(int nc, int64_t n, int64_t nl, T *r, const T *wl, const int32_t *off,
-                        const int32_t *pos, const T *dinv, double *part, DevScalars *sc,
+void cg_update_r_gather(int nc, int64_t n, int64_t nl, T *r, const T *wl, const int2 *pair,
+                        const int4 *list, const T *dinv, double *part, DevScalars *sc,
                         hipStream_t s, bool check = true);
 
 // single-reduction PCG: init (r, u = dinv r, p = s = w = 0; partials r.u, r.r,

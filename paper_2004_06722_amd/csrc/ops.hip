@@ -219,7 +219,7 @@ static int launch_apply_impl(const bp_op_s *op, int which, bool f32, const NodeM
 
 int launch_mass_wl(const bp_op_s *op, bool f32, const NodeMap &m, const void *u, bool masked,
                    double *part, const int *done, hipStream_t s) {
-  if (!op->tr_off) return set_error(BP_ERR_ARG, "no transposed gather map");
+  if (!op->tr_pair) return set_error(BP_ERR_ARG, "no transposed gather map");
   int rc;
   if (f32)
     rc = dispatch_mass_wl<float>(op, m, op->Bt32, op->basis32, (const float *)u, op->wl32, masked,
@@ -234,17 +234,17 @@ int launch_mass_wl(const bp_op_s *op, bool f32, const NodeMap &m, const void *u,
 
 int launch_apply(const bp_op_s *op, int which, bool f32, const NodeMap &m, const void *u, void *w,
                  bool masked, double *part, const int *done, hipStream_t s) {
-  if (which == BP_MASS && op->tr_off) {
+  if (which == BP_MASS && op->tr_pair) {
     // element kernel into w_L, then w = Q^T w_L by the transposed gather
     const int rc = launch_mass_wl(op, f32, m, u, masked, part, done, s);
     if (rc != BP_OK) return rc;
     const int64_t nl = op->nelem * op->p1 * op->p1 * op->p1;
     const int32_t *iperm = m.idx == op->idx ? nullptr : op->iperm;
     if (f32)
-      gather_local<float>(op->ncomp, op->nglobal, nl, op->tr_off, op->tr_pos, iperm, op->wl32,
+      gather_local<float>(op->ncomp, op->nglobal, nl, op->tr_pair, op->tr_list, iperm, op->wl32,
                           (float *)w, done, s);
     else
-      gather_local<double>(op->ncomp, op->nglobal, nl, op->tr_off, op->tr_pos, iperm, op->wl,
+      gather_local<double>(op->ncomp, op->nglobal, nl, op->tr_pair, op->tr_list, iperm, op->wl,
                            (double *)w, done, s);
     BP_HIP(hipGetLastError());
     return BP_OK;

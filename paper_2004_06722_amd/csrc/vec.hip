@@ -28,6 +28,11 @@ __device__ __forceinline__ T ld_v(const T *p) {
   else
     return *p;
 }
+template <bool NT>
+__device__ __forceinline__ int2 ld_pair(const int2 *p) {
+  const uint64_t v = ld_v<NT>(reinterpret_cast<const uint64_t *>(p));
+  return make_int2((int32_t)(uint32_t)v, (int32_t)(uint32_t)(v >> 32));
+}
 template <bool NT, typename T>
 __device__ __forceinline__ void st_v(T *p, T v) {
   if constexpr (NT)
@@ -353,41 +358,67 @@ __global__ __launch_bounds__(kVecThreads / K) void k_cg_update_r(
   block_partial1<TH>(rr, part, 2 * nc, nc + comp);
 }
 
-// Q^T w_L at one node: the sum of wc[pos[k]] over k in [k0, k1) in
-// ascending order. The first four contributions are requested together and
-// branch-free (two round trips: pos, then w_L; an index past the node's range
-// is clamped to the last slot nl - 1 and its value dropped); a conforming
-// hexahedral mesh gives every node 1, 2, 4 or 8, so only nodes shared by more
-// than four elements go round the loop. Dropped values add an exact zero, so
-// the order of the additions is that of the plain loop.
-template <typename T>
-__device__ __forceinline__ T gather_node(const T *__restrict__ wc,
-                                         const int32_t *__restrict__ pos, int32_t k0,
-                                         int32_t k1, int32_t last) {
-  int32_t ps[4];
+// Q^T w_L at one node, for NC components: the sum of wl[slot] over the node's
+// element-local slots in ascending order. t = (first slot, second slot) with
+// -1 for none; a node of more than two slots has -2 - k in place of the
+// second: its others are in list[k], list[k + 1], ... = (their number, slot,
+// slot, slot), (slot, slot, slot, slot), .... On a conforming mesh of degree p
+// all but about 3 / p^2 of the nodes lie inside an element or a face: for
+// those the values are two dependent trips away (the pair, then both values,
+// branch-free: an absent one reads slot 0 and is dropped), and the pair is
+// 8 bytes a node. An offset and a list of all slots were three trips and
+// 4 + 4 E (p + 1)^3 / n bytes (the residual update at p = 6, 9.6e6 nodes in a
+// lexicographic order: 103 -> 96 us). Dropped values add an exact zero, so the
+// additions are those of the plain loop.
+template <typename T, int NC>
+__device__ __forceinline__ void gather_node(T (&w)[NC], const T *__restrict__ wl, int64_t nl,
+                                            int2 t, const int4 *__restrict__ list) {
+  T a[NC], b[NC];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) ps[m] = pos[min(k0 + m, last)];
-  T c[4];
+  for (int c = 0; c < NC; ++c) {
+    a[c] = wl[c * nl + max(t.x, 0)];
+    b[c] = wl[c * nl + max(t.y, 0)];
+  }
+  const bool more = t.y < -1;
+  const int32_t rec = more ? -2 - t.y : 0;
+  int4 m = list[rec];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) c[m] = wc[ps[m]];
-  T acc = T(0);
+  for (int c = 0; c < NC; ++c) {
+    w[c] = T(0) + (t.x >= 0 ? a[c] : T(0));
+    w[c] += t.y >= 0 ? b[c] : T(0);
+  }
+  if (!more) return;
+  const int32_t count = m.x;
+  m.x = m.y, m.y = m.z, m.z = m.w;  // the first int4 holds three slots
+  for (int32_t k = 0, nk = 3;;) {
+    T e[4][NC];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) acc += k0 + m < k1 ? c[m] : T(0);
-  for (int32_t k = k0 + 4; k < k1; ++k) acc += wc[pos[k]];
-  return acc;
+    for (int c = 0; c < NC; ++c) {
+      e[0][c] = wl[c * nl + m.x];
+      e[1][c] = wl[c * nl + m.y];
+      e[2][c] = wl[c * nl + m.z];
+      e[3][c] = nk == 4 ? wl[c * nl + m.w] : T(0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) w[c] += i < nk && k + i < count ? e[i][c] : T(0);
+    k += nk;
+    if (k >= count) break;
+    nk = 4;
+    m = list[rec + (k + 1) / 4];
+  }
 }
 
 // The same update with w = Q^T w_L formed per node from the element-local
-// output of the mass kernel: w_v is the sum of wl[pos[k]] over
-// k in [off[v], off[v+1]) in ascending order, a fixed order, so the result
-// does not depend on scheduling as an atomic scatter does. No w vector is
-// read, written or cleared; the pass reads z, dinv, the two offsets, and
-// pos and w_L once per element-local slot.
+// output of the mass kernel: w_v is the sum of the node's slots in ascending
+// order, a fixed order, so the result does not depend on scheduling as an
+// atomic scatter does. No w vector is read, written or cleared; the pass
+// reads z, dinv, the slot pair and w_L once per element-local slot.
 template <typename T, bool NT>
 __global__ __launch_bounds__(kGroupThreads<T>) void k_cg_update_r_gather(
     int64_t n, int64_t nl, T *__restrict__ z, const T *__restrict__ wl,
-    const int32_t *__restrict__ off, const int32_t *__restrict__ pos,
-    const T *__restrict__ dinv, double *__restrict__ part, const DevScalars *__restrict__ sc,
+    const int2 *__restrict__ pair, const int4 *__restrict__ list, const T *__restrict__ dinv, double *__restrict__ part, const DevScalars *__restrict__ sc,
     int check) {
   constexpr int K = kNodesPerThread<T>, TH = kGroupThreads<T>;
   if (check && sc->done) return;
@@ -395,28 +426,27 @@ __global__ __launch_bounds__(kGroupThreads<T>) void k_cg_update_r_gather(
   const int64_t v0 = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
   const T al = (T)sc->alpha[comp];
   const T *wc = wl + comp * nl;
-  T di[K], zo[K], wv[K];
-  int32_t o0[K], o1[K];
+  T di[K], zo[K], wv[K][1];
+  int2 t[K];
 #pragma unroll
   for (int j = 0; j < K; ++j) {
     const int64_t v = v0 + j * TH;
-    di[j] = zo[j] = wv[j] = T(0);
-    o0[j] = o1[j] = 0;
-    if (v < n) {  // the offsets first: the gather waits only for them
-      o0[j] = off[v];
-      o1[j] = off[v + 1];
+    di[j] = zo[j] = T(0);
+    t[j] = make_int2(-1, -1);
+    if (v < n) {  // the pair first: the gather waits only for it
+      t[j] = ld_pair<NT>(pair + v);
       di[j] = ld_v<NT>(dinv + v);
       zo[j] = ld_v<NT>(z + comp * n + v);
     }
   }
 #pragma unroll
-  for (int j = 0; j < K; ++j) wv[j] = gather_node(wc, pos, o0[j], o1[j], (int32_t)(nl - 1));
+  for (int j = 0; j < K; ++j) gather_node<T, 1>(wv[j], wc, 0, t[j], list);
   double rz = 0.0, rr = 0.0;
 #pragma unroll
   for (int j = 0; j < K; ++j) {
     const int64_t v = v0 + j * TH;
     if (v < n) {
-      const T zv = zo[j] - (al * di[j]) * wv[j];
+      const T zv = zo[j] - (al * di[j]) * wv[j][0];
       st_v<NT>(z + comp * n + v, zv);
       const T rv = di[j] != T(0) ? zv / di[j] : T(0);
       rz += (double)rv * (double)zv;
@@ -500,14 +530,12 @@ __global__ __launch_bounds__(kVecThreads / K) void k_cg_update_r_nc(
   block_partials<2 * NC, TH>(acc, part);
 }
 
-// k_cg_update_r_gather for NC > 1 components: the node's offsets and slot
-// positions are read once and each component gathers its w_L through them
+// k_cg_update_r_gather for NC > 1 components: the node's slots are read once and each component gathers its w_L through them
 // (the same fixed order per component).
 template <typename T, bool NT, int NC>
 __global__ __launch_bounds__(kVecThreads) void k_cg_update_r_gather_nc(
     int64_t n, int64_t nl, T *__restrict__ z, const T *__restrict__ wl,
-    const int32_t *__restrict__ off, const int32_t *__restrict__ pos,
-    const T *__restrict__ dinv, double *__restrict__ part, const DevScalars *__restrict__ sc,
+    const int2 *__restrict__ pair, const int4 *__restrict__ list, const T *__restrict__ dinv, double *__restrict__ part, const DevScalars *__restrict__ sc,
     int check) {
   if (check && sc->done) return;
   const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
@@ -515,30 +543,12 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_update_r_gather_nc(
 #pragma unroll
   for (int c = 0; c < 2 * NC; ++c) acc[c] = 0.0;
   if (v < n) {
-    const int32_t k0 = off[v], k1 = off[v + 1], last = (int32_t)(nl - 1);
+    const int2 t = ld_pair<NT>(pair + v);
     const T di = ld_v<NT>(dinv + v);
     T zo[NC], wv[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) zo[c] = ld_v<NT>(z + c * n + v);
-    int32_t ps[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) ps[m] = pos[min(k0 + m, last)];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const T *wc = wl + c * nl;
-      T cm[4];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) cm[m] = wc[ps[m]];
-      T a = T(0);
-#pragma unroll
-      for (int m = 0; m < 4; ++m) a += k0 + m < k1 ? cm[m] : T(0);
-      wv[c] = a;
-    }
-    for (int32_t k = k0 + 4; k < k1; ++k) {
-      const int32_t q = pos[k];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) wv[c] += wl[c * nl + q];
-    }
+    gather_node<T, NC>(wv, wl, nl, t, list);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const T zv = zo[c] - ((T)sc->alpha[c] * di) * wv[c];
@@ -880,15 +890,16 @@ __global__ __launch_bounds__(kFinThreads) void k_fin_rxp_fused(const double *__r
 // as above), one node per thread
 template <typename T>
 __global__ __launch_bounds__(kVecThreads) void k_gather_local(
-    int64_t n, int64_t nl, const int32_t *__restrict__ off, const int32_t *__restrict__ pos,
+    int64_t n, int64_t nl, const int2 *__restrict__ pair, const int4 *__restrict__ list,
     const int32_t *__restrict__ iperm, const T *__restrict__ wl, T *__restrict__ w,
     const int *__restrict__ done) {
   if (done && *done) return;
   const int64_t g = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
   if (g >= n) return;
   const int64_t v = iperm ? iperm[g] : g;
-  const T *wc = wl + blockIdx.y * nl;
-  w[blockIdx.y * n + g] = gather_node(wc, pos, off[v], off[v + 1], (int32_t)(nl - 1));
+  T wv[1];
+  gather_node<T, 1>(wv, wl + blockIdx.y * nl, 0, pair[v], list);
+  w[blockIdx.y * n + g] = wv[0];
 }
 
 template <int NC>
@@ -1700,54 +1711,54 @@ void cg_update_xp(int nc, int64_t n, T *x, T *p, const T *z, DevScalars *sc, hip
 }
 
 template <typename T>
-void gather_local(int nc, int64_t n, int64_t nl, const int32_t *off, const int32_t *pos,
+void gather_local(int nc, int64_t n, int64_t nl, const int2 *pair, const int4 *list,
                   const int32_t *iperm, const T *wl, T *w, const int *done, hipStream_t s) {
   hipLaunchKernelGGL((k_gather_local<T>), dim3(vec_blocks(n), nc), dim3(kVecThreads), 0, s, n, nl,
-                     off, pos, iperm, wl, w, done);
+                     pair, list, iperm, wl, w, done);
 }
 
 template <typename T, bool NT, int NC>
-static void launch_gather_nc(int64_t n, int64_t nl, T *r, const T *wl, const int32_t *off,
-                             const int32_t *pos, const T *dinv, double *part, DevScalars *sc,
+static void launch_gather_nc(int64_t n, int64_t nl, T *r, const T *wl, const int2 *pair,
+                             const int4 *list, const T *dinv, double *part, DevScalars *sc,
                              hipStream_t s, int check) {
   hipLaunchKernelGGL((k_cg_update_r_gather_nc<T, NT, NC>), dim3(vec_blocks(n)),
-                     dim3(kVecThreads), 0, s, n, nl, r, wl, off, pos, dinv, part, sc, check);
+                     dim3(kVecThreads), 0, s, n, nl, r, wl, pair, list, dinv, part, sc, check);
 }
 
 template <typename T, bool NT>
 static void update_r_gather_nc(int nc, int64_t n, int64_t nl, T *r, const T *wl,
-                               const int32_t *off, const int32_t *pos, const T *dinv,
+                               const int2 *pair, const int4 *list, const T *dinv,
                                double *part, DevScalars *sc, hipStream_t s, int check) {
   switch (nc) {
-    case 2: launch_gather_nc<T, NT, 2>(n, nl, r, wl, off, pos, dinv, part, sc, s, check); break;
-    case 3: launch_gather_nc<T, NT, 3>(n, nl, r, wl, off, pos, dinv, part, sc, s, check); break;
-    case 4: launch_gather_nc<T, NT, 4>(n, nl, r, wl, off, pos, dinv, part, sc, s, check); break;
-    case 5: launch_gather_nc<T, NT, 5>(n, nl, r, wl, off, pos, dinv, part, sc, s, check); break;
-    case 6: launch_gather_nc<T, NT, 6>(n, nl, r, wl, off, pos, dinv, part, sc, s, check); break;
-    case 7: launch_gather_nc<T, NT, 7>(n, nl, r, wl, off, pos, dinv, part, sc, s, check); break;
+    case 2: launch_gather_nc<T, NT, 2>(n, nl, r, wl, pair, list, dinv, part, sc, s, check); break;
+    case 3: launch_gather_nc<T, NT, 3>(n, nl, r, wl, pair, list, dinv, part, sc, s, check); break;
+    case 4: launch_gather_nc<T, NT, 4>(n, nl, r, wl, pair, list, dinv, part, sc, s, check); break;
+    case 5: launch_gather_nc<T, NT, 5>(n, nl, r, wl, pair, list, dinv, part, sc, s, check); break;
+    case 6: launch_gather_nc<T, NT, 6>(n, nl, r, wl, pair, list, dinv, part, sc, s, check); break;
+    case 7: launch_gather_nc<T, NT, 7>(n, nl, r, wl, pair, list, dinv, part, sc, s, check); break;
     default:
-      launch_gather_nc<T, NT, kMaxComp>(n, nl, r, wl, off, pos, dinv, part, sc, s, check);
+      launch_gather_nc<T, NT, kMaxComp>(n, nl, r, wl, pair, list, dinv, part, sc, s, check);
   }
 }
 
 template <typename T>
-void cg_update_r_gather(int nc, int64_t n, int64_t nl, T *r, const T *wl, const int32_t *off,
-                        const int32_t *pos, const T *dinv, double *part, DevScalars *sc,
+void cg_update_r_gather(int nc, int64_t n, int64_t nl, T *r, const T *wl, const int2 *pair,
+                        const int4 *list, const T *dinv, double *part, DevScalars *sc,
                         hipStream_t s, bool check) {
   if (nc > 1) {  // one thread per node for every component: map and dinv read once
     if (n * (int64_t)sizeof(T) >= kStreamBytes)
-      update_r_gather_nc<T, true>(nc, n, nl, r, wl, off, pos, dinv, part, sc, s, check ? 1 : 0);
+      update_r_gather_nc<T, true>(nc, n, nl, r, wl, pair, list, dinv, part, sc, s, check ? 1 : 0);
     else
-      update_r_gather_nc<T, false>(nc, n, nl, r, wl, off, pos, dinv, part, sc, s, check ? 1 : 0);
+      update_r_gather_nc<T, false>(nc, n, nl, r, wl, pair, list, dinv, part, sc, s, check ? 1 : 0);
     return;
   }
   if (n * (int64_t)sizeof(T) >= kStreamBytes)
     hipLaunchKernelGGL((k_cg_update_r_gather<T, true>), dim3(vec_blocks(n), nc),
-                       dim3(kGroupThreads<T>), 0, s, n, nl, r, wl, off, pos, dinv, part, sc,
+                       dim3(kGroupThreads<T>), 0, s, n, nl, r, wl, pair, list, dinv, part, sc,
                        check ? 1 : 0);
   else
     hipLaunchKernelGGL((k_cg_update_r_gather<T, false>), dim3(vec_blocks(n), nc),
-                       dim3(kGroupThreads<T>), 0, s, n, nl, r, wl, off, pos, dinv, part, sc,
+                       dim3(kGroupThreads<T>), 0, s, n, nl, r, wl, pair, list, dinv, part, sc,
                        check ? 1 : 0);
 }
 
@@ -1895,15 +1906,15 @@ template void cg_update_xp<double>(int, int64_t, double *, double *, const doubl
                                    DevScalars *, hipStream_t, bool);
 template void cg_update_xp<float>(int, int64_t, float *, float *, const float *, DevScalars *,
                                   hipStream_t, bool);
-template void gather_local<double>(int, int64_t, int64_t, const int32_t *, const int32_t *,
+template void gather_local<double>(int, int64_t, int64_t, const int2 *, const int4 *,
                                    const int32_t *, const double *, double *, const int *, hipStream_t);
-template void gather_local<float>(int, int64_t, int64_t, const int32_t *, const int32_t *,
+template void gather_local<float>(int, int64_t, int64_t, const int2 *, const int4 *,
                                   const int32_t *, const float *, float *, const int *, hipStream_t);
 template void cg_update_r_gather<double>(int, int64_t, int64_t, double *, const double *,
-                                         const int32_t *, const int32_t *, const double *,
+                                         const int2 *, const int4 *, const double *,
                                          double *, DevScalars *, hipStream_t, bool);
 template void cg_update_r_gather<float>(int, int64_t, int64_t, float *, const float *,
-                                        const int32_t *, const int32_t *, const float *, double *,
+                                        const int2 *, const int4 *, const float *, double *,
                                         DevScalars *, hipStream_t, bool);
 
 }  // namespace bp

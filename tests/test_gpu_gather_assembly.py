@@ -121,3 +121,37 @@ def test_mass_gather_with_unreferenced_nodes():
             assert rel(xh[:n], rec[-1]) <= TOL
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("ncomp", [1, 3])
+@pytest.mark.parametrize("caller_order", [False, True])
+@pytest.mark.parametrize("spread", [1, 3, 40])
+def test_mass_gather_of_nodes_with_any_number_of_slots(spread, caller_order, ncomp):
+    # random gather maps over nl / spread node ids: nodes of 0, 1, 2 (the slot
+    # pair), 3, 4 (one list entry), 5, ... and many slots, repeats inside an
+    # element included; the apply and the residual update of the solve
+    import paper_2004_06722_amd.bp as B
+    from oracle.operators import Discretization
+    from oracle.quadrature import bp_rule
+    p = 3
+    rng = np.random.default_rng(700 + spread)
+    xi, _ = B.rule(p + 1, B.GLL)
+    lm = synth.brick_mesh(3, 2, 2, p, xi, 97)
+    n = lm.elem_dofs.size // spread
+    dofs = rng.integers(0, n, size=lm.elem_dofs.shape)
+    counts = np.bincount(dofs.ravel(), minlength=n)
+    assert counts.max() >= (5 if spread < 40 else 40)
+    rule = bp_rule(1, p)
+    om = synth.brick_mesh(3, 2, 2, p, rule.xi, 97)
+    disc = Discretization(rule, dofs, om.node_xyz, n)
+    u = synth.rhs_uniform(n, 98, ncomp=ncomp)
+    with B.Operator(p, p + 2, B.GL, dofs, lm.node_xyz, n, ncomp=ncomp,
+                    caller_order=caller_order) as op:
+        w = host(op.apply(MASS, dev(u), masked=False))
+        assert rel(w, disc.apply(MASS, u, masked=False)) <= TOL
+        b = u * (counts > 0).reshape((n,) + (1,) * (u.ndim - 1))
+        rec = []
+        pcg(lambda v: disc.apply(MASS, v, masked=False), b,
+            disc.jacobi_inverse(MASS, masked=False), maxit=3, fixed_iters=True, record=rec)
+        x, _ = op.pcg_solve(dev(b), which=MASS, maxit=3, fixed_iters=True)
+        assert rel(host(x), rec[-1]) <= TOL
