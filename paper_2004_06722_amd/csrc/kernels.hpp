@@ -12,6 +12,7 @@
 #pragma once
 #include "bp_internal.h"
 #include "rules1d.hpp"
+#include "xcd.hpp"
 
 #include <hip/hip_runtime.h>
 
@@ -697,7 +698,8 @@ __device__ __forceinline__ void gl_body(
   const bool act = t < PL::USED;
   const int slot = act ? t / QQ : 0;
   const int l = act ? t % QQ : QQ;  // lane in the element's plane (QQ: no role)
-  const int64_t e = (int64_t)blockIdx.x * PL::EPB + slot;
+  const int64_t bx = WL ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int64_t e = bx * PL::EPB + slot;
   const bool live = act && e < nelem;
   const int64_t ec = live ? e : nelem - 1;  // element whose data the lane reads
   // roles: column (i, j) along t; pencil (i, c) along s; pencil (b, c) along r
@@ -995,8 +997,7 @@ __device__ __forceinline__ void gl_body(
     }
     double enb[1] = {en};
     if (part)
-      block_sum_store<1, PL::THREADS>(enb, part + (int64_t)blockIdx.x * ncomp + (MULTI ? cc : c0),
-                                      1);
+      block_sum_store<1, PL::THREADS>(enb, part + bx * ncomp + (MULTI ? cc : c0), 1);
   }
 }
 
@@ -1325,7 +1326,7 @@ __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) __attribute__((amdgpu_wav
   const int slot = act ? t / PL::N : 0;
   const int ij = t % PL::N;
   const int i = ij % P1, j = ij / P1;
-  const int64_t e = (int64_t)blockIdx.x * PL::EPB + slot;
+  const int64_t e = (int64_t)xcd_block(blockIdx.x, gridDim.x) * PL::EPB + slot;
   const bool live = act && e < nelem;
   const int64_t ec = live ? e : nelem - 1;  // element whose data the lane reads
   __shared__ double sx[PL::EPB][P1 * PS];

@@ -9,6 +9,7 @@
 
 #include "bp_internal.h"
 #include "launch.h"
+#include "xcd.hpp"
 
 namespace bp {
 
@@ -177,7 +178,8 @@ __device__ __forceinline__ int64_t comp_node(int64_t slot, int64_t head) {
 }
 
 template <int TH = kVecThreads>
-__device__ __forceinline__ void block_partial1(double v, double *part, int width, int col) {
+__device__ __forceinline__ void block_partial1(double v, double *part, int width, int col,
+                                               int64_t row = blockIdx.x) {
   constexpr int NW = TH / 64;
   __shared__ double red[NW];
 #pragma unroll
@@ -188,7 +190,7 @@ __device__ __forceinline__ void block_partial1(double v, double *part, int width
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < NW; ++k) s += red[k];
-    part[(int64_t)blockIdx.x * width + col] = s;
+    part[row * width + col] = s;
   }
   __syncthreads();
 }
@@ -418,12 +420,14 @@ __device__ __forceinline__ void gather_node(T (&w)[NC], const T *__restrict__ wl
 template <typename T, bool NT>
 __global__ __launch_bounds__(kGroupThreads<T>) void k_cg_update_r_gather(
     int64_t n, int64_t nl, T *__restrict__ z, const T *__restrict__ wl,
-    const int2 *__restrict__ pair, const int4 *__restrict__ list, const T *__restrict__ dinv, double *__restrict__ part, const DevScalars *__restrict__ sc,
+    const int2 *__restrict__ pair, const int4 *__restrict__ list, const T *__restrict__ dinv,
+    double *__restrict__ part, const DevScalars *__restrict__ sc,
     int check) {
   constexpr int K = kNodesPerThread<T>, TH = kGroupThreads<T>;
   if (check && sc->done) return;
   const int comp = blockIdx.y, nc = gridDim.y;
-  const int64_t v0 = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  const int64_t bx = xcd_block(blockIdx.x, gridDim.x);
+  const int64_t v0 = bx * kVecThreads + threadIdx.x;
   const T al = (T)sc->alpha[comp];
   const T *wc = wl + comp * nl;
   T di[K], zo[K], wv[K][1];
@@ -453,15 +457,16 @@ __global__ __launch_bounds__(kGroupThreads<T>) void k_cg_update_r_gather(
       rr += (double)rv * (double)rv;
     }
   }
-  block_partial1<TH>(rz, part, 2 * nc, comp);
-  block_partial1<TH>(rr, part, 2 * nc, nc + comp);
+  block_partial1<TH>(rz, part, 2 * nc, comp, bx);
+  block_partial1<TH>(rr, part, 2 * nc, nc + comp, bx);
 }
 
 // Partial sums of W values over the work-group in a fixed order: row
 // blockIdx.x of part[.][W] (one shuffle tree per wave, then the wave sums in
 // order; one barrier for all W).
 template <int W, int TH = kVecThreads>
-__device__ __forceinline__ void block_partials(double (&v)[W], double *part) {
+__device__ __forceinline__ void block_partials(double (&v)[W], double *part,
+                                               int64_t row = blockIdx.x) {
   constexpr int NW = TH / 64;
   __shared__ double red[NW][W];
 #pragma unroll
@@ -476,7 +481,7 @@ __device__ __forceinline__ void block_partials(double (&v)[W], double *part) {
     double x = 0.0;
 #pragma unroll
     for (int k = 0; k < NW; ++k) x += red[k][threadIdx.x];
-    part[(int64_t)blockIdx.x * W + threadIdx.x] = x;
+    part[row * W + threadIdx.x] = x;
   }
 }
 
@@ -530,15 +535,17 @@ __global__ __launch_bounds__(kVecThreads / K) void k_cg_update_r_nc(
   block_partials<2 * NC, TH>(acc, part);
 }
 
-// k_cg_update_r_gather for NC > 1 components: the node's slots are read once and each component gathers its w_L through them
-// (the same fixed order per component).
+// k_cg_update_r_gather for NC > 1 components: the node's slots are read once
+// and each component gathers its w_L through them (the same fixed order per component).
 template <typename T, bool NT, int NC>
 __global__ __launch_bounds__(kVecThreads) void k_cg_update_r_gather_nc(
     int64_t n, int64_t nl, T *__restrict__ z, const T *__restrict__ wl,
-    const int2 *__restrict__ pair, const int4 *__restrict__ list, const T *__restrict__ dinv, double *__restrict__ part, const DevScalars *__restrict__ sc,
+    const int2 *__restrict__ pair, const int4 *__restrict__ list, const T *__restrict__ dinv,
+    double *__restrict__ part, const DevScalars *__restrict__ sc,
     int check) {
   if (check && sc->done) return;
-  const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  const int64_t bx = xcd_block(blockIdx.x, gridDim.x);
+  const int64_t v = bx * kVecThreads + threadIdx.x;
   double acc[2 * NC];
 #pragma unroll
   for (int c = 0; c < 2 * NC; ++c) acc[c] = 0.0;
@@ -558,7 +565,7 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_update_r_gather_nc(
       acc[NC + c] = (double)rv * (double)rv;
     }
   }
-  block_partials<2 * NC>(acc, part);
+  block_partials<2 * NC>(acc, part, bx);
 }
 
 // ---- the fused iteration of small meshes ----------------------------------
@@ -894,7 +901,7 @@ __global__ __launch_bounds__(kVecThreads) void k_gather_local(
     const int32_t *__restrict__ iperm, const T *__restrict__ wl, T *__restrict__ w,
     const int *__restrict__ done) {
   if (done && *done) return;
-  const int64_t g = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  const int64_t g = (int64_t)xcd_block(blockIdx.x, gridDim.x) * kVecThreads + threadIdx.x;
   if (g >= n) return;
   const int64_t v = iperm ? iperm[g] : g;
   T wv[1];
