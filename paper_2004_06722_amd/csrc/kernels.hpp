@@ -289,7 +289,8 @@ __device__ __forceinline__ void stiff_colloc_body(
   const int slot = act ? t / PL::N : 0;
   const int ij = t % PL::N;
   const int i = ij % P1, j = ij / P1;
-  const int64_t e = (int64_t)blockIdx.x * PL::EPB + slot;
+  const int64_t bx = LOCAL ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
+  const int64_t e = bx * PL::EPB + slot;
   if (PL::EPB == 1 && e >= nelem) return;  // uniform over the work-group
   const bool live = act && e < nelem;
   const int64_t ec = live ? e : nelem - 1;  // element whose data a lane reads
@@ -487,8 +488,7 @@ __device__ __forceinline__ void stiff_colloc_body(
     }
     if (part) {
       double ev[1] = {en};
-      block_sum_store<1, PL::THREADS>(ev, part + (int64_t)blockIdx.x * ncomp + (MULTI ? cc : c0),
-                                      1);
+      block_sum_store<1, PL::THREADS>(ev, part + bx * ncomp + (MULTI ? cc : c0), 1);
     }
   }
 }
@@ -698,7 +698,8 @@ __device__ __forceinline__ void gl_body(
   const bool act = t < PL::USED;
   const int slot = act ? t / QQ : 0;
   const int l = act ? t % QQ : QQ;  // lane in the element's plane (QQ: no role)
-  const int64_t bx = WL ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int64_t bx =
+      LOCAL ? blockIdx.x : xcd_block<WL ? kXcdRun : kXcdRunGL>(blockIdx.x, gridDim.x);
   const int64_t e = bx * PL::EPB + slot;
   const bool live = act && e < nelem;
   const int64_t ec = live ? e : nelem - 1;  // element whose data the lane reads
