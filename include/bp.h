@@ -105,7 +105,8 @@ int bp_rule(int n, int quad, double *x, double *w);
  * second gather map in the caller's ids (int32, nelem p1^3). The results are
  * the same up to the rounding order of the assembly sums.
  * With GL quadrature (and nelem p1^3 < 2^31) the operator also holds the
- * transposed gather map (int32, nglobal + 1 offsets and nelem p1^3 slots) and
+ * transposed gather map (two int32 a node, and a list of at most 2 nelem p1^3
+ * int32 for the nodes of more than two slots) and
  * an element-local output buffer of ncomp nelem p1^3 words (per precision):
  * the mass operator stores B_L u_L per element and assembles Q^T of it by a
  * fixed-order gather, so its results do not depend on scheduling.
