@@ -711,11 +711,13 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   } while (0)
 
   const int64_t nv = nglobal * ncomp;
+  // the uploads below are waited for once, with the geometric factors (their
+  // host arrays live until the return; an early one frees device memory first,
+  // which waits)
   TRY(dmalloc(&op->idx_c, idx.size()));
   op->idx = op->idx_c;
   TRYHIP(hipMemcpyAsync(op->idx_c, idx.data(), idx.size() * sizeof(int32_t),
                         hipMemcpyHostToDevice, s));
-  TRYHIP(hipStreamSynchronize(s));
   if (renum) {
     op->n_owned = n_owned;
     TRY(dmalloc(&op->perm, old_of_new.size()));
@@ -728,7 +730,6 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
     TRY(dmalloc(&op->idx, idx.size()));
     map_internal(op->idx_c, op->iperm, op->idx, nelem * n3, s);
     TRYHIP(hipGetLastError());
-    TRYHIP(hipStreamSynchronize(s));
     if (op->fp32) TRY(dmalloc(&op->bi, nv));
     TRY(dmalloc(&op->xi, nv));
   }
@@ -737,31 +738,43 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   // assembly, and its element-local output
   const int64_t nl = nelem * n3;
   if (!op->colloc && nl < (int64_t(1) << 31)) {
-    auto node = [&](int64_t k) -> size_t {
-      const size_t g = (size_t)elem_dofs[k];
-      return renum ? (size_t)new_of_old[g] : g;
-    };
-    std::vector<int2> pair((size_t)nglobal, make_int2(-1, -1));
-    std::vector<int4> list(1);  // never empty: absent records read list[0]
-    {
-      std::vector<int32_t> count((size_t)nglobal, 0);
-      for (int64_t k = 0; k < nl; ++k) ++count[node(k)];
-      int64_t rec = 0;
-      for (size_t v = 0; v < (size_t)nglobal; ++v)
-        if (count[v] > 2) {
-          pair[v].y = (int32_t)(-2 - rec);
-          rec += count[v] / 4 + (count[v] % 4 != 0);
-        }
-      list.assign((size_t)std::max<int64_t>(rec, 1), make_int4(0, 0, 0, 0));
+    // the internal node of each slot once, and prefetches ahead of the writes
+    // into the pairs and the records: with a random map each is a cache miss
+    constexpr int64_t kAhead = 32, kAheadList = 12;
+    std::vector<int32_t> node((size_t)nl);
+    if (renum)
+      for (int64_t k = 0; k < nl; ++k) {
+        if (k + kAhead < nl) __builtin_prefetch(&new_of_old[(size_t)elem_dofs[k + kAhead]]);
+        node[k] = new_of_old[(size_t)elem_dofs[k]];
+      }
+    else
+      for (int64_t k = 0; k < nl; ++k) node[k] = (int32_t)elem_dofs[k];
+    std::vector<int2> pair((size_t)nglobal, make_int2(0, 0));  // first .x counts
+    for (int64_t k = 0; k < nl; ++k) {
+      if (k + kAhead < nl) __builtin_prefetch(&pair[node[k + kAhead]], 1);
+      ++pair[node[k]].x;
     }
+    int64_t rec = 0;
+    for (int2 &t : pair) {
+      const int32_t count = t.x;
+      t = make_int2(-1, count > 2 ? (int32_t)(-2 - rec) : -1);
+      if (count > 2) rec += count / 4 + (count % 4 != 0);
+    }
+    // never empty: absent records read list[0]
+    std::vector<int4> list((size_t)std::max<int64_t>(rec, 1), make_int4(0, 0, 0, 0));
     int32_t *flat = &list[0].x;
     for (int64_t k = 0; k < nl; ++k) {
-      int2 &t = pair[node(k)];
+      if (k + kAhead < nl) __builtin_prefetch(&pair[node[k + kAhead]], 1);
+      if (k + kAheadList < nl) {
+        const int32_t y = pair[node[k + kAheadList]].y;
+        if (y < -1) __builtin_prefetch(&list[-2 - y], 1);
+      }
+      int2 &t = pair[node[k]];
       if (t.x < 0) {
         t.x = (int32_t)k;
       } else if (t.y < -1) {
-        int32_t *rec = flat + 4 * (int64_t)(-2 - t.y);
-        rec[++rec[0]] = (int32_t)k;
+        int32_t *r = flat + 4 * (int64_t)(-2 - t.y);
+        r[++r[0]] = (int32_t)k;
       } else {
         t.y = (int32_t)k;
       }
@@ -782,6 +795,7 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   const int64_t ng = nelem * 6 * nq, nb = nelem * nq;
   TRY(dmalloc(&op->G, ng));
   TRY(dmalloc(&op->Bt, nb));
+  if (op->colloc) TRY(dmalloc(&op->md, nglobal));
   {
     double *X = nullptr;
     int *bad = nullptr;
@@ -795,6 +809,11 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
     if (!rc && hipMemcpyAsync(bad, &big, sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess)
       rc = set_error(BP_ERR_HIP, "bp_setup: flag upload failed");
     if (!rc) rc = launch_geometry(op, X, op->G, op->Bt, bad, s);
+    if (!rc && op->colloc) {  // the assembled mass matrix (its unmasked diagonal)
+      fill_f64(op->md, nglobal, 0.0, s);
+      rc = launch_diag(op, BP_MASS, caller_map(op), op->md, false, s);
+      mark_dirichlet(op->idx_c, nelem * n3, op->md, s);
+    }
     if (!rc && (hipMemcpyAsync(&bad_host, bad, sizeof(int), hipMemcpyDeviceToHost, s) !=
                     hipSuccess ||
                 hipStreamSynchronize(s) != hipSuccess))
@@ -818,14 +837,6 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   TRY(dmalloc(&op->part, op->part_len));
   TRY(dmalloc(&op->sc, 1));
   TRYHIP(hipHostMalloc((void **)&op->sc_host, sizeof(DevScalars), hipHostMallocDefault));
-  if (op->colloc) {  // the assembled mass matrix (its unmasked diagonal)
-    TRY(dmalloc(&op->md, nglobal));
-    fill_f64(op->md, nglobal, 0.0, s);
-    TRY(launch_diag(op, BP_MASS, caller_map(op), op->md, false, s));
-    mark_dirichlet(op->idx_c, nelem * n3, op->md, s);
-    TRYHIP(hipGetLastError());
-    TRYHIP(hipStreamSynchronize(s));
-  }
   // timing events: no system-scope fence on record (no cache writeback and
   // invalidation around the timed work; the solves synchronise the stream
   // themselves before reading them)
