@@ -300,11 +300,13 @@ int apply_guess(bp_op op, DevScalars *sc, int which, const SolveVectors<T> &v, T
 // previous call or cg_restart left, without the set-up (b, rtol unused).
 // ws: partial sums and device scalars of the run (own_work(op) unless the
 // caller brings its own).
+// started: set once the initialisation is queued; until then v.x may hold the
+// solution of an earlier solve.
 template <typename T>
 int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, const T *dinv, T *r,
             T *p, T *w, double rtol, int maxit, bool fixed, bool x0_zero, hipStream_t s,
             int *iters_out, float *ms_out, double *apply_ms_out = nullptr,
-            int *apply_count_out = nullptr, bool resume = false) {
+            int *apply_count_out = nullptr, bool resume = false, bool *started = nullptr) {
   constexpr bool f32 = sizeof(T) == 4;
   const int nc = op->ncomp;
   const int64_t n = op->nglobal;
@@ -319,6 +321,7 @@ int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, con
     if (rc) return rc;
     cg_init<T>(nc, n, v.b, v.x0, x, v.perm, r, w, p, dinv, part, sc, s);
     BP_HIP(hipGetLastError());
+    if (started) *started = true;
   }
   BP_HIP(hipEventRecord(op->ev0, s));
   const int poll = 8;
@@ -432,10 +435,10 @@ int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, con
 // Single-reduction Jacobi-PCG (FP64): per iteration the fused vector update,
 // the operator on u = dinv r (its energy partials give (u, A u)) and one
 // finisher. u lives in op->tmp, s = A p in op->sv. Same timing and stopping
-// conventions as pcg_run.
+// conventions as pcg_run, `started` among them.
 int pcg_run_sr(bp_op op, int which, const SolveVectors<double> &v, const double *dinv,
                double rtol, int maxit, bool fixed, hipStream_t s, int *iters_out, float *ms_out,
-               double *apply_ms_out, int *apply_count_out) {
+               double *apply_ms_out, int *apply_count_out, bool *started) {
   const int nc = op->ncomp;
   const int64_t n = op->nglobal;
   const bool masked = op->has_dirichlet;
@@ -446,6 +449,8 @@ int pcg_run_sr(bp_op op, int which, const SolveVectors<double> &v, const double 
   int rc = apply_guess<double>(op, op->sc, which, v, w, rtol, fixed, false, s);
   if (rc) return rc;
   sr_init(nc, n, v.b, v.x0, x, v.perm, w, u, p, sv, dinv, pv, op->sc, s);
+  BP_HIP(hipGetLastError());
+  *started = true;
   rc = launch_apply(op, which, false, internal_map(op), u, w, masked, pa, nullptr, s);
   if (rc) return rc;
   sr_fin(true, nc, pv, nbv, pa, nba, op->sc, s);
@@ -577,12 +582,15 @@ SolveVectors<double> solve_vectors(bp_op op, const double *b, double *x) {
   return {b, x, op->perm ? op->xi : x, op->perm};
 }
 
-// the solution back into the caller's x (nothing to do in the caller's
-// order); the stream is synchronised, as the solves promise
-int solve_out(bp_op op, double *x, hipStream_t s) {
+// the solution back into the caller's x (nothing to do in the caller's order,
+// or where the solve failed before it had taken x0 into xi: x stays as given);
+// the stream is synchronised, as the solves promise
+int solve_out(bp_op op, double *x, bool started, hipStream_t s) {
   if (!op->perm) return BP_OK;
-  permute_out<double>(op->ncomp, op->nglobal, op->iperm, op->xi, x, s);
-  BP_HIP(hipGetLastError());
+  if (started) {
+    permute_out<double>(op->ncomp, op->nglobal, op->iperm, op->xi, x, s);
+    BP_HIP(hipGetLastError());
+  }
   BP_HIP(hipStreamSynchronize(s));
   return BP_OK;
 }
@@ -999,16 +1007,17 @@ int bp_pcg_solve(bp_op op, int which, const double *b, double *x, double rtol, i
   float ms = 0.0f;
   double apply_ms = 0.0;
   int apply_count = 0;
+  bool started = false;
   const SolveVectors<double> v = solve_vectors(op, b, x);
   if (op->cg_variant == BP_CG_SINGLE_REDUCTION) {
     rc = pcg_run_sr(op, which, v, op->dinv[dinv_slot(op, which)], rtol, maxit, fixed_iters != 0, s,
-                    &iters, &ms, &apply_ms, &apply_count);
+                    &iters, &ms, &apply_ms, &apply_count, &started);
   } else {
     rc = pcg_run<double>(op, own_work(op), which, v, op->dinv[dinv_slot(op, which)], op->r, op->pv,
                          op->w, rtol, maxit, fixed_iters != 0, false, s, &iters, &ms, &apply_ms,
-                         &apply_count);
+                         &apply_count, false, &started);
   }
-  const int rc_out = solve_out(op, x, s);
+  const int rc_out = solve_out(op, x, started, s);
   if (rc == BP_OK) rc = rc_out;
   if (st) {
     std::memset(st, 0, sizeof(*st));
@@ -1050,12 +1059,13 @@ int bp_pcg_solve_static(bp_op op, int which, const double *b, double *x, double 
   float ms = 0.0f;
   double apply_ms = 0.0;
   int apply_count = 0;
+  bool started = false;
   // standard recurrences whatever BP_OPT_CG_VARIANT says; every workspace
   // word is written (w cleared, scalars uploaded) before it is read
   rc = pcg_run<double>(op, ws, which, solve_vectors(op, b, x), op->dinv[dinv_slot(op, which)], z,
                        p, w, rtol, maxit, fixed_iters != 0, false, s, &iters, &ms, &apply_ms,
-                       &apply_count);
-  const int rc_out = solve_out(op, x, s);
+                       &apply_count, false, &started);
+  const int rc_out = solve_out(op, x, started, s);
   if (rc == BP_OK) rc = rc_out;
   if (st) {
     std::memset(st, 0, sizeof(*st));
@@ -1128,7 +1138,7 @@ int bp_pcg_solve_mixed(bp_op op, const double *b, double *x_out, double outer_rt
     ++outer;
   }
   BP_HIP(hipEventRecord(t1, s));
-  const int rc_out = solve_out(op, x_out, s);
+  const int rc_out = solve_out(op, x_out, true, s);
   if (rc == BP_OK) rc = rc_out;
   BP_HIP(hipEventSynchronize(t1));
   float ms = 0.0f;
