@@ -286,8 +286,10 @@ int bp_grad_kappa(bp_op op, const double *lam, const double *u, double *g,
  * quadrature (section 5 eq. (mass); M is symmetric). With bp_pcg_solve and
  * bp_grad_kappa it gives the adjoint gradient of L with respect to the
  * coefficient of bp_set_coeff (A lam = mask * M d, then bp_grad_kappa).
- * d^T M d is summed from the element energies d_L^T B_L d_L in a fixed
- * order, so repeated calls give the same bits.
+ * d^T M d is summed in a fixed order -- from the element energies d_L^T B_L d_L,
+ * or with collocated points, where M is a diagonal that bp_setup assembles
+ * exactly (each entry rounded once), node by node -- so repeated calls give the
+ * same bits, also on another operator of the same mesh.
  *   u, u_target: device double [ncomp][nglobal], read only.
  *   grad: device double [ncomp][nglobal], overwritten with M d; NULL skips it.
  *   loss: host double, written on return (the call synchronises the stream).

@@ -1059,6 +1059,50 @@ __global__ __launch_bounds__(kVecThreads) void k_misfit_diagonal(
   }
 }
 
+// The assembled mass matrix of a collocated operator, md[g] = the sum of Bt over
+// the slots k with idx[k] = g, in three passes whose atomics commute exactly, so
+// that every operator on a mesh has the same bits (floating-point additions in
+// order of arrival differ in the last ones): the largest term of each node (as
+// bits: positive doubles order as integers), then each term as two integers
+// against that one's exponent E, 2^(E - 30) hi + 2^(E - 61) lo with hi, lo <=
+// 2^31 (a term is off by at most 2^-62 of the largest, and 2^32 of them fit),
+// then the node's sum, rounded once.
+using u64 = unsigned long long;
+static_assert(sizeof(u64) == sizeof(double), "sums in place of doubles");
+__device__ __forceinline__ int64_t slot_node(int32_t v) { return v >= 0 ? v : -1 - v; }
+
+__global__ __launch_bounds__(kVecThreads) void k_mass_largest(const int32_t *__restrict__ idx,
+                                                              const double *__restrict__ Bt,
+                                                              int64_t count, u64 *largest) {
+  for (int64_t k = (int64_t)blockIdx.x * kVecThreads + threadIdx.x; k < count;
+       k += (int64_t)gridDim.x * kVecThreads)
+    atomicMax(largest + slot_node(idx[k]), (u64)__double_as_longlong(Bt[k]));
+}
+
+__global__ __launch_bounds__(kVecThreads) void k_mass_add(const int32_t *__restrict__ idx,
+                                                          const double *__restrict__ Bt,
+                                                          int64_t count,
+                                                          const double *__restrict__ largest,
+                                                          u64 *hi, u64 *lo) {
+  for (int64_t k = (int64_t)blockIdx.x * kVecThreads + threadIdx.x; k < count;
+       k += (int64_t)gridDim.x * kVecThreads) {
+    const int64_t g = slot_node(idx[k]);
+    const double v = ldexp(Bt[k], 30 - ilogb(largest[g])), h = floor(v);
+    atomicAdd(hi + g, (u64)h);
+    atomicAdd(lo + g, (u64)rint(ldexp(v - h, 31)));
+  }
+}
+
+// md holds the largest terms on entry
+__global__ __launch_bounds__(kVecThreads) void k_mass_sum(int64_t n, double *__restrict__ md,
+                                                          const u64 *__restrict__ hi,
+                                                          const u64 *__restrict__ lo) {
+  const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  if (v >= n || md[v] == 0.0 || isinf(md[v])) return;
+  const int e = ilogb(md[v]);
+  md[v] = ldexp((double)hi[v], e - 30) + ldexp((double)lo[v], e - 61);
+}
+
 // md = -|md| on the Dirichlet nodes that the map marks
 __global__ __launch_bounds__(kVecThreads) void k_mark_dirichlet(const int32_t *__restrict__ idx,
                                                                 int64_t count,
@@ -1792,9 +1836,15 @@ void misfit_diagonal(int nc, int64_t n, const double *md, const double *u, const
                      u, ut, grad, part);
 }
 
-void mark_dirichlet(const int32_t *idx, int64_t count, double *md, hipStream_t s) {
-  hipLaunchKernelGGL(k_mark_dirichlet, dim3(grid_blocks(count)), dim3(kVecThreads), 0, s, idx,
-                     count, md);
+void assemble_mass(const int32_t *idx, const double *Bt, int64_t count, int64_t n, double *md,
+                   double *hi, double *lo, hipStream_t s) {
+  u64 *const h = reinterpret_cast<u64 *>(hi), *const l = reinterpret_cast<u64 *>(lo);
+  const dim3 g(grid_blocks(count)), t(kVecThreads);
+  for (double *x : {md, hi, lo}) fill_f64(x, n, 0.0, s);
+  hipLaunchKernelGGL(k_mass_largest, g, t, 0, s, idx, Bt, count, reinterpret_cast<u64 *>(md));
+  hipLaunchKernelGGL(k_mass_add, g, t, 0, s, idx, Bt, count, md, h, l);
+  hipLaunchKernelGGL(k_mass_sum, dim3(vec_blocks(n)), t, 0, s, n, md, h, l);
+  hipLaunchKernelGGL(k_mark_dirichlet, g, t, 0, s, idx, count, md);
 }
 
 void difference(const double *a, const double *b, double *d, int64_t count, hipStream_t s) {
