@@ -156,7 +156,12 @@ int bp_set_helmholtz(bp_op op, double beta, const double *beta_q, void *stream);
  * Appendix A1 (Nek5000 ax).
  *   prec = BP_FP64: u, w are double [ncomp][nglobal].
  *   prec = BP_FP32: u, w are float; requires BP_SETUP_FP32.
- *   w is overwritten (it must not alias u).
+ *   w is overwritten (it must not alias u). u and w may be any memory the device
+ *   can reach; where w is not ordinary memory of the operator's device (pinned
+ *   host or managed memory, a fine-grained allocation, another device's), in
+ *   which atomic additions could be lost, the result is assembled in a buffer of
+ *   the operator's and copied (likewise the results of bp_diag and
+ *   bp_mass_misfit).
  */
 int bp_apply(bp_op op, int which, int prec, const void *u, void *w,
              unsigned flags, void *stream);

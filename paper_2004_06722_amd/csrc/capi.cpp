@@ -269,6 +269,21 @@ struct SolveVectors {
 void clear(double *x, int64_t n, hipStream_t s) { fill_f64(x, n, 0.0, s); }
 void clear(float *x, int64_t n, hipStream_t s) { fill_f32(x, n, 0.0f, s); }
 
+// Whether a kernel may add into the caller's array p: the hardware's
+// floating-point atomics need ordinary memory of the operator's own device. In
+// pinned host or managed memory, in a fine-grained allocation or on another
+// device an addition can be lost, and results go there by plain stores from a
+// buffer of the operator's (the question costs 0.1 us a call).
+bool takes_atomics(const bp_op_s *op, const void *p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && !a.isManaged && a.device == op->device &&
+         a.allocationFlags == hipDeviceMallocDefault;
+}
+
 // w = A x0, which the CG initialisation subtracts from b; the device scalars are
 // uploaded first. A guess that is zero everywhere needs no operator: a pass
 // over x0 finds out (sc->x0_zero), and the launches then return at entry (at
@@ -961,13 +976,20 @@ int bp_apply(bp_op op, int which, int prec, const void *u, void *w, unsigned fla
     BP_HIP(hipGetLastError());
     return BP_OK;
   }
-  if (which == BP_MASS && op->tr_pair)
-    ;  // overwrites w
-  else if (f32)
-    fill_f32((float *)w, nv, 0.0f, s);
+  const bool adds = !(which == BP_MASS && op->tr_pair);  // else w is overwritten
+  void *const wo = !adds || takes_atomics(op, w) ? w : f32 ? (void *)op->w32 : (void *)op->w;
+  if (adds && f32)
+    clear((float *)wo, nv, s);
+  else if (adds)
+    clear((double *)wo, nv, s);
+  rc = launch_apply(op, which, f32, caller_map(op), u, wo, masked, nullptr, nullptr, s);
+  if (rc || wo == w) return rc;
+  if (f32)
+    permute_out(op->ncomp, op->nglobal, nullptr, (const float *)wo, (float *)w, s);
   else
-    fill_f64((double *)w, nv, 0.0, s);
-  return launch_apply(op, which, f32, caller_map(op), u, w, masked, nullptr, nullptr, s);
+    permute_out(op->ncomp, op->nglobal, nullptr, (const double *)wo, (double *)w, s);
+  BP_HIP(hipGetLastError());
+  return BP_OK;
 }
 
 int bp_apply_local(bp_op op, int which, int prec, const void *uL, void *wL, void *stream) {
@@ -989,8 +1011,13 @@ int bp_diag(bp_op op, int which, double *d, unsigned flags, void *stream) {
   if (!d) return set_error(BP_ERR_ARG, "bp_diag: NULL output");
   if (flags & ~BP_MASKED) return set_error(BP_ERR_ARG, "bp_diag: unknown flag");
   hipStream_t s = (hipStream_t)stream;
-  fill_f64(d, op->nglobal, 0.0, s);
-  return launch_diag(op, which, caller_map(op), d, (flags & BP_MASKED) != 0, s);
+  double *const dd = takes_atomics(op, d) ? d : op->tmp;
+  fill_f64(dd, op->nglobal, 0.0, s);
+  rc = launch_diag(op, which, caller_map(op), dd, (flags & BP_MASKED) != 0, s);
+  if (rc || dd == d) return rc;
+  permute_out(1, op->nglobal, nullptr, (const double *)dd, d, s);
+  BP_HIP(hipGetLastError());
+  return BP_OK;
 }
 
 int bp_pcg_solve(bp_op op, int which, const double *b, double *x, double rtol, int maxit,
@@ -1180,10 +1207,11 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
     operator_energies(nc, op->part, vec_blocks(n), op->sc, s);
   } else {
     difference(u, u_target, op->r, nv, s);
-    double *Md = grad ? grad : op->w;
+    double *const Md = grad && (op->tr_pair || takes_atomics(op, grad)) ? grad : op->w;
     fill_f64(Md, nv, 0.0, s);
     rc = launch_apply(op, BP_MASS, false, caller_map(op), op->r, Md, false, pa, nullptr, s);
     if (rc) return rc;
+    if (grad && Md != grad) permute_out(nc, n, nullptr, (const double *)Md, grad, s);
     operator_energies(nc, pa, apply_rows(op, BP_MASS), op->sc, s);
   }
   BP_HIP(hipGetLastError());

@@ -183,7 +183,7 @@ void sr_update(int nc, int64_t n, T *x, T *u, T *w, T *p, T *sv, const T *dinv, 
 // vectors [nc][n] between the caller's node order and the internal one,
 // both as gathers: in, dst[c][v] = src[c][perm[v]] (perm[v] = the caller's
 // id of internal node v); out, dst[c][g] = src[c][iperm[g]] (iperm[g] = the
-// internal id of the caller's node g); nothing is done if *skip
+// internal id of the caller's node g; NULL: g itself); nothing is done if *skip
 template <typename T>
 void permute_in(int nc, int64_t n, const int32_t *perm, const T *src, T *dst, hipStream_t s,
                 const int *skip = nullptr);

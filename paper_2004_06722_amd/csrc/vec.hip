@@ -1387,7 +1387,7 @@ __global__ __launch_bounds__(kVecThreads) void k_map_internal(const int32_t *__r
 }
 
 // Between the caller's node order and the internal one, per component, as a
-// gather (contiguous stores): dst[c][v] = src[c][map[v]].
+// gather (contiguous stores): dst[c][v] = src[c][map[v]] (src[c][v] without map).
 template <typename T>
 __global__ __launch_bounds__(kVecThreads) void k_permute(int64_t n, const int32_t *__restrict__ map,
                                                          const T *__restrict__ src,
@@ -1397,7 +1397,7 @@ __global__ __launch_bounds__(kVecThreads) void k_permute(int64_t n, const int32_
   const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
   if (v >= n) return;
   const int64_t c = (int64_t)blockIdx.y * n;
-  dst[c + v] = src[c + map[v]];
+  dst[c + v] = src[c + (map ? map[v] : v)];
 }
 
 }  // namespace
@@ -1417,6 +1417,8 @@ template void permute_in<double>(int, int64_t, const int32_t *, const double *, 
                                  hipStream_t, const int *);
 template void permute_out<double>(int, int64_t, const int32_t *, const double *, double *,
                                   hipStream_t);
+template void permute_out<float>(int, int64_t, const int32_t *, const float *, float *,
+                                 hipStream_t);
 
 void map_internal(const int32_t *idx_c, const int32_t *iperm, int32_t *idx, int64_t count,
                   hipStream_t s) {
