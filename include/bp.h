@@ -278,7 +278,8 @@ int bp_pcg_solve_mixed(bp_op op, const double *b, double *x, double outer_rtol,
  * quadrature point: the derivative of lam^T A(kappa) u with respect to the
  * coefficient (section 4 eq. (ip1) with mu = kappa; section 5 eq. (bk5x)),
  * summed over the ncomp components. lam, u: device double [ncomp][nglobal]
- * (masked on Dirichlet nodes); g: device double [nelem][q^3], overwritten.
+ * (masked on Dirichlet nodes); g: device double [nelem][q^3], overwritten (it
+ * may share memory with lam or u).
  * Collocated GLL operators with p <= 8; others return BP_ERR_ARG.
  */
 int bp_grad_kappa(bp_op op, const double *lam, const double *u, double *g,

@@ -6,6 +6,7 @@
 #include <cstring>
 #include <string>
 #include <climits>
+#include <utility>
 #include <vector>
 
 #include <mutex>
@@ -255,6 +256,12 @@ int download_scalars(bp_op op, hipStream_t s) { return download_scalars(op, op->
 // assembles w by adding Q^T w_L (gather_local) and needs w cleared.
 int64_t stored_rows(const bp_op_s *op, int which) {
   return which == BP_MASS && op->tr_pair ? 0 : op->n_owned;
+}
+
+// Whether two arrays share a byte.
+bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + nb && y < x + na;
 }
 
 // b, x0 and x of a solve. With perm, b and x0 are in the caller's order and x is
@@ -968,22 +975,27 @@ int bp_apply(bp_op op, int which, int prec, const void *u, void *w, unsigned fla
   hipStream_t s = (hipStream_t)stream;
   const int64_t nv = op->nglobal * op->ncomp;
   const bool f32 = prec == BP_FP32, masked = (flags & BP_MASKED) != 0;
-  if (which == BP_MASS && op->colloc) {
+  const bool diagonal = which == BP_MASS && op->colloc;
+  const bool adds = !diagonal && !(which == BP_MASS && op->tr_pair);  // else w is overwritten
+  // a w that the additions or the reads of u forbid: through the operator's own
+  const size_t bytes = (size_t)nv * (f32 ? sizeof(float) : sizeof(double));
+  const bool aside = overlap(u, bytes, w, bytes) || (adds && !takes_atomics(op, w));
+  void *const wo = !aside ? w : f32 ? (void *)op->w32 : (void *)op->w;
+  if (diagonal) {
     if (f32)
-      mass_diagonal(op->ncomp, op->nglobal, op->md, (const float *)u, (float *)w, masked, s);
+      mass_diagonal(op->ncomp, op->nglobal, op->md, (const float *)u, (float *)wo, masked, s);
     else
-      mass_diagonal(op->ncomp, op->nglobal, op->md, (const double *)u, (double *)w, masked, s);
+      mass_diagonal(op->ncomp, op->nglobal, op->md, (const double *)u, (double *)wo, masked, s);
     BP_HIP(hipGetLastError());
-    return BP_OK;
+  } else {
+    if (adds && f32)
+      clear((float *)wo, nv, s);
+    else if (adds)
+      clear((double *)wo, nv, s);
+    rc = launch_apply(op, which, f32, caller_map(op), u, wo, masked, nullptr, nullptr, s);
+    if (rc) return rc;
   }
-  const bool adds = !(which == BP_MASS && op->tr_pair);  // else w is overwritten
-  void *const wo = !adds || takes_atomics(op, w) ? w : f32 ? (void *)op->w32 : (void *)op->w;
-  if (adds && f32)
-    clear((float *)wo, nv, s);
-  else if (adds)
-    clear((double *)wo, nv, s);
-  rc = launch_apply(op, which, f32, caller_map(op), u, wo, masked, nullptr, nullptr, s);
-  if (rc || wo == w) return rc;
+  if (!aside) return BP_OK;
   if (f32)
     permute_out(op->ncomp, op->nglobal, nullptr, (const float *)wo, (float *)w, s);
   else
@@ -1185,6 +1197,15 @@ int bp_grad_kappa(bp_op op, const double *lam, const double *u, double *g, void 
   if (rc) return rc;
   if (!lam || !u || !g) return set_error(BP_ERR_ARG, "bp_grad_kappa: NULL pointer");
   hipStream_t s = (hipStream_t)stream;
+  // work-groups write g while others still read lam and u: inputs that g
+  // overlaps are read from copies
+  const size_t in = (size_t)op->nglobal * op->ncomp * sizeof(double);
+  const size_t out = (size_t)op->nelem * op->q * op->q * op->q * sizeof(double);
+  for (auto [v, copy] : {std::pair(&lam, op->r), std::pair(&u, op->pv)})
+    if (overlap(*v, in, g, out)) {
+      permute_out(op->ncomp, op->nglobal, nullptr, *v, copy, s);
+      *v = copy;
+    }
   return launch_grad_kappa(op, lam, u, g, s);
 }
 
@@ -1203,7 +1224,11 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
   // element energies d_L^T B_L d_L per work-group and component
   double *pa = op->part + (vec_blocks(n) + kStage2Rows) * 3 * nc;
   if (op->colloc) {
-    misfit_diagonal(nc, n, op->md, u, u_target, grad, op->part, s);
+    const size_t bytes = (size_t)nv * sizeof(double);
+    const bool aside =
+        grad && (overlap(grad, bytes, u, bytes) || overlap(grad, bytes, u_target, bytes));
+    misfit_diagonal(nc, n, op->md, u, u_target, aside ? op->w : grad, op->part, s);
+    if (aside) permute_out(nc, n, nullptr, (const double *)op->w, grad, s);
     operator_energies(nc, op->part, vec_blocks(n), op->sc, s);
   } else {
     difference(u, u_target, op->r, nv, s);
