@@ -265,7 +265,8 @@ bool overlap(const void *a, size_t na, const void *b, size_t nb) {
 }
 
 // b, x0 and x of a solve. With perm, b and x0 are in the caller's order and x is
-// the solve's own copy, made by the initialisation; otherwise x0 is x.
+// the solve's own copy, made for the operator on x0, or by the initialisation
+// where x0 is zero; otherwise x0 is x.
 template <typename T>
 struct SolveVectors {
   const T *b, *x0;

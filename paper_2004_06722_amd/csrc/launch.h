@@ -80,7 +80,7 @@ void invert_diag(const double *d, double *dinv, float *dinv32, int64_t n, hipStr
 
 // CG steps; part holds per-block partial sums, sc the device scalars.
 // Where perm is given, b and x0 are in the caller's order, and x0 is copied
-// into x.
+// into x if sc->x0_zero is set (otherwise x holds it).
 template <typename T>
 void cg_init(int nc, int64_t n, const T *b, const T *x0, T *x, const int32_t *perm, T *r, T *w,
              T *p, const T *dinv, double *part, DevScalars *sc, hipStream_t s);

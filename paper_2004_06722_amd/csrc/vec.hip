@@ -197,9 +197,10 @@ __device__ __forceinline__ void block_partial1(double v, double *part, int width
 
 // r = b - w (w holds A x0; nothing to subtract where the initial guess is zero
 // everywhere, sc->x0_zero), w = 0, p = z = dinv r; partials r.z, r.r, b.b.
-// With perm, b and x0 are in the caller's order: they are gathered here, and
+// With perm, b and x0 are in the caller's order: b is gathered here, and a zero
 // x0 is copied into x, the solve's own (one pass; as a permutation of each
-// before it 2 x 0.5 ms at n = 9e7). Entries of b on Dirichlet nodes are treated
+// before it 2 x 0.5 ms at n = 9e7; a guess that the operator was applied to is in
+// x already). Entries of b on Dirichlet nodes are treated
 // as zero. The iteration keeps the preconditioned residual z = dinv r (stored
 // in `r`) rather than r: the residual update then advances z and the direction
 // update reads z alone, ten vector words per DOF and iteration instead of
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(kVecThreads) void k_cg_init(
   double rz = 0.0, rr = 0.0, bb = 0.0;
   if (v < n) {
     const int64_t f = comp * n + v, g = perm ? comp * n + perm[v] : f;
-    if (perm) x[f] = x0[g];
+    if (perm && zero) x[f] = x0[g];  // else there already, for the operator
     T wv = T(0);
     if (!zero) {
       wv = w[f];
@@ -1199,7 +1200,7 @@ __global__ __launch_bounds__(kVecThreads) void k_sr_init(
   double ru = 0.0, rr = 0.0, bb = 0.0;
   if (v < n) {
     const int64_t f = comp * n + v, g = perm ? comp * n + perm[v] : f;
-    if (perm) x[f] = x0[g];
+    if (perm && zero) x[f] = x0[g];  // else there already, for the operator
     double wv = 0.0;
     if (!zero) {
       wv = w[f];
