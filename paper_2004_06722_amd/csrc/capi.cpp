@@ -695,11 +695,14 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   const bool renum = !(flags & BP_SETUP_CALLER_ORDER) &&
                      interior_first_order(p1, nelem, nglobal, elem_dofs, new_of_old, old_of_new,
                                           &n_owned);
-  // gather map in the caller's ids with the Dirichlet sign encoding
+  // gather map with the Dirichlet sign encoding: in internal ids where the
+  // host needs those (Gauss-Legendre points), otherwise in the caller's
+  const bool internal_ids = renum && quad == BP_QUAD_GL;
   std::vector<int32_t> idx((size_t)(nelem * n3));
   for (int64_t k = 0; k < nelem * n3; ++k) {
-    const int32_t g = (int32_t)elem_dofs[k];
-    idx[k] = dirichlet && dirichlet[g] ? -1 - g : g;
+    const int64_t g = elem_dofs[k];
+    const int32_t v = internal_ids ? new_of_old[(size_t)g] : (int32_t)g;
+    idx[k] = dirichlet && dirichlet[g] ? -1 - v : v;
   }
 
   bp_op op = new bp_op_s();
@@ -742,13 +745,18 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   } while (0)
 
   const int64_t nv = nglobal * ncomp;
-  // the uploads below are waited for once, with the geometric factors (their
-  // host arrays live until the return; an early one frees device memory first,
-  // which waits)
+  // the uploads of the maps are not waited for here: their host arrays live
+  // until the return, and an early one frees device memory first, which waits
   TRY(dmalloc(&op->idx_c, idx.size()));
   op->idx = op->idx_c;
-  TRYHIP(hipMemcpyAsync(op->idx_c, idx.data(), idx.size() * sizeof(int32_t),
-                        hipMemcpyHostToDevice, s));
+  int32_t *given = op->idx_c;
+  if (renum) {
+    op->idx = nullptr;
+    TRY(dmalloc(&op->idx, idx.size()));
+    if (internal_ids) given = op->idx;
+  }
+  TRYHIP(hipMemcpyAsync(given, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice,
+                        s));
   if (renum) {
     op->n_owned = n_owned;
     TRY(dmalloc(&op->perm, old_of_new.size()));
@@ -757,67 +765,52 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
                           hipMemcpyHostToDevice, s));
     TRYHIP(hipMemcpyAsync(op->iperm, new_of_old.data(), new_of_old.size() * sizeof(int32_t),
                           hipMemcpyHostToDevice, s));
-    op->idx = nullptr;
-    TRY(dmalloc(&op->idx, idx.size()));
-    map_internal(op->idx_c, op->iperm, op->idx, nelem * n3, s);
+    if (internal_ids)
+      map_ids(op->idx, op->perm, op->idx_c, nelem * n3, s);
+    else
+      map_ids(op->idx_c, op->iperm, op->idx, nelem * n3, s);
     TRYHIP(hipGetLastError());
     if (op->fp32) TRY(dmalloc(&op->bi, nv));
     TRY(dmalloc(&op->xi, nv));
   }
-  // Gauss-Legendre operators: the transposed gather map (each node's
-  // element-local slots, ascending) for the mass operator's fixed-order
-  // assembly, and its element-local output
+  // Gauss-Legendre operators: the transposed gather map (counting sort of the
+  // element-local slots by node, ascending within a node, which the device turns
+  // into pairs and records) for the mass operator's fixed-order assembly, and its
+  // element-local output (which holds the sorted slots meanwhile)
   const int64_t nl = nelem * n3;
   if (!op->colloc && nl < (int64_t(1) << 31)) {
-    // the internal node of each slot once, and prefetches ahead of the writes
-    // into the pairs and the records: with a random map each is a cache miss
-    constexpr int64_t kAhead = 32, kAheadList = 12;
-    std::vector<int32_t> node((size_t)nl);
-    if (renum)
-      for (int64_t k = 0; k < nl; ++k) {
-        if (k + kAhead < nl) __builtin_prefetch(&new_of_old[(size_t)elem_dofs[k + kAhead]]);
-        node[k] = new_of_old[(size_t)elem_dofs[k]];
-      }
-    else
-      for (int64_t k = 0; k < nl; ++k) node[k] = (int32_t)elem_dofs[k];
-    std::vector<int2> pair((size_t)nglobal, make_int2(0, 0));  // first .x counts
-    for (int64_t k = 0; k < nl; ++k) {
-      if (k + kAhead < nl) __builtin_prefetch(&pair[node[k + kAhead]], 1);
-      ++pair[node[k]].x;
+    auto node = [&](int64_t k) -> size_t { return (size_t)(idx[k] >= 0 ? idx[k] : -1 - idx[k]); };
+    // off[v + 1]: the slots of node v, then where they start, then where they
+    // end; behind them, where the records of each work-group's nodes start
+    std::vector<int32_t> off((size_t)(nglobal + 1 + vec_blocks(nglobal)), 0), pos((size_t)nl);
+    int32_t *const rec = &off[(size_t)nglobal + 1];
+    for (int64_t k = 0; k < nl; ++k) ++off[node(k) + 1];
+    int32_t slots = 0, records = 0;
+    for (int64_t v = 0; v < nglobal; ++v) {
+      const int32_t count = off[(size_t)v + 1];
+      off[(size_t)v + 1] = slots;
+      if (v % kVecThreads == 0) rec[v / kVecThreads] = records;
+      slots += count;
+      if (count > 2) records += count / 4 + (count % 4 != 0);
     }
-    int64_t rec = 0;
-    for (int2 &t : pair) {
-      const int32_t count = t.x;
-      t = make_int2(-1, count > 2 ? (int32_t)(-2 - rec) : -1);
-      if (count > 2) rec += count / 4 + (count % 4 != 0);
-    }
-    // never empty: absent records read list[0]
-    std::vector<int4> list((size_t)std::max<int64_t>(rec, 1), make_int4(0, 0, 0, 0));
-    int32_t *flat = &list[0].x;
-    for (int64_t k = 0; k < nl; ++k) {
-      if (k + kAhead < nl) __builtin_prefetch(&pair[node[k + kAhead]], 1);
-      if (k + kAheadList < nl) {
-        const int32_t y = pair[node[k + kAheadList]].y;
-        if (y < -1) __builtin_prefetch(&list[-2 - y], 1);
-      }
-      int2 &t = pair[node[k]];
-      if (t.x < 0) {
-        t.x = (int32_t)k;
-      } else if (t.y < -1) {
-        int32_t *r = flat + 4 * (int64_t)(-2 - t.y);
-        r[++r[0]] = (int32_t)k;
-      } else {
-        t.y = (int32_t)k;
-      }
-    }
-    TRY(dmalloc(&op->tr_pair, pair.size()));
-    TRY(dmalloc(&op->tr_list, list.size()));
+    for (int64_t k = 0; k < nl; ++k) pos[(size_t)off[node(k) + 1]++] = (int32_t)k;
     TRY(dmalloc(&op->wl, nl * ncomp));
-    TRYHIP(hipMemcpyAsync(op->tr_pair, pair.data(), pair.size() * sizeof(int2),
-                          hipMemcpyHostToDevice, s));
-    TRYHIP(hipMemcpyAsync(op->tr_list, list.data(), list.size() * sizeof(int4),
-                          hipMemcpyHostToDevice, s));
-    TRYHIP(hipStreamSynchronize(s));
+    TRY(dmalloc(&op->tr_pair, nglobal));
+    TRY(dmalloc(&op->tr_list, std::max(records, 1)));  // absent records read the first
+    int32_t *off_d = nullptr, *const pos_d = reinterpret_cast<int32_t *>(op->wl);
+    TRY(dmalloc(&off_d, off.size()));
+    hipError_t e = hipMemcpyAsync(off_d, off.data(), off.size() * sizeof(int32_t),
+                                  hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(pos_d, pos.data(), pos.size() * sizeof(int32_t), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) {
+      slot_records(nglobal, off_d, off_d + nglobal + 1, pos_d, op->tr_pair, op->tr_list, s);
+      e = hipGetLastError();
+    }
+    const hipError_t es = hipStreamSynchronize(s);
+    dfree(off_d);
+    TRYHIP(e);
+    TRYHIP(es);
   }
   TRY(upload_basis(op, s));
 

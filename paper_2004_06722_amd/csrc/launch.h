@@ -157,6 +157,11 @@ template <typename T>
 void cg_update_rxp(int64_t n, T *x, T *p, T *z, T *w, const T *dinv, double *part,
                    DevScalars *sc, hipStream_t s, bool check, bool first, int64_t n_own);
 
+// pair and list of bp_op_s from the sorted slots: those of node v are
+// pos[off[v]], ..., pos[off[v + 1] - 1], the records of nodes 256 b, ... start at
+// list[rec[b]]
+void slot_records(int64_t n, const int32_t *off, const int32_t *rec, const int32_t *pos,
+                  int2 *pair, int4 *list, hipStream_t s);
 // transposed gather Q^T w_L: w[c][g] = sum of wl[c][.] over the slots of node
 // v = iperm[g] or g (pair and list as in bp_op_s), ascending (wl is [nc][nl]);
 // skipped while *done (done may be NULL)
@@ -189,9 +194,8 @@ void permute_in(int nc, int64_t n, const int32_t *perm, const T *src, T *dst, hi
                 const int *skip = nullptr);
 template <typename T>
 void permute_out(int nc, int64_t n, const int32_t *iperm, const T *src, T *dst, hipStream_t s);
-// the gather map in internal ids: idx = idx_c through iperm, Dirichlet signs kept
-void map_internal(const int32_t *idx_c, const int32_t *iperm, int32_t *idx, int64_t count,
-                  hipStream_t s);
+// a gather map in the other node order: out[k] = map[in[k]], Dirichlet signs kept
+void map_ids(const int32_t *in, const int32_t *map, int32_t *out, int64_t count, hipStream_t s);
 void sr_fin(bool first, int nc, double *pv, int64_t nbv, double *pa, int64_t nba,
             DevScalars *sc, hipStream_t s);
 

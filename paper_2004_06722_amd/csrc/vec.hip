@@ -1375,16 +1375,47 @@ __global__ __launch_bounds__(kVecThreads) void k_scale_mass(const double *__rest
   }
 }
 
-// idx = idx_c in internal ids (the Dirichlet sign kept)
-__global__ __launch_bounds__(kVecThreads) void k_map_internal(const int32_t *__restrict__ idx_c,
-                                                              const int32_t *__restrict__ iperm,
-                                                              int32_t *__restrict__ idx,
-                                                              int64_t count) {
+// out = in through map (the Dirichlet sign kept)
+__global__ __launch_bounds__(kVecThreads) void k_map_ids(const int32_t *__restrict__ in,
+                                                         const int32_t *__restrict__ map,
+                                                         int32_t *__restrict__ out,
+                                                         int64_t count) {
   for (int64_t k = (int64_t)blockIdx.x * kVecThreads + threadIdx.x; k < count;
        k += (int64_t)gridDim.x * kVecThreads) {
-    const int32_t g = idx_c[k];
-    idx[k] = g >= 0 ? iperm[g] : -1 - iperm[-1 - g];
+    const int32_t g = in[k];
+    out[k] = g >= 0 ? map[g] : -1 - map[-1 - g];
   }
+}
+
+// The pair and the record of each node (gather_node) from its sorted slots, the
+// records of a work-group's nodes one after the other from list[rec[block]]; the
+// first int4 of the list is read for nodes without a record and never empty.
+__global__ __launch_bounds__(kVecThreads) void k_slot_records(
+    int64_t n, const int32_t *__restrict__ off, const int32_t *__restrict__ rec,
+    const int32_t *__restrict__ pos, int2 *__restrict__ pair, int4 *__restrict__ list) {
+  const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
+  const int32_t o = v < n ? off[v] : 0, count = v < n ? off[v + 1] - o : 0;
+  // int4s of this node's record, then of all up to it
+  const int32_t own = count > 2 ? count / 4 + (count % 4 != 0) : 0;
+  __shared__ int32_t sum[kVecThreads];
+  int32_t upto = own;
+  for (int h = 1; h < kVecThreads; h *= 2) {
+    sum[threadIdx.x] = upto;
+    __syncthreads();
+    if ((int)threadIdx.x >= h) upto += sum[threadIdx.x - h];
+    __syncthreads();
+  }
+  if (v >= n) return;
+  int2 t = make_int2(count > 0 ? pos[o] : -1, count > 1 ? pos[o + 1] : -1);
+  if (count > 2) {
+    const int32_t first = rec[blockIdx.x] + upto - own;
+    t.y = -2 - first;
+    int32_t *r = &list[first].x;
+    r[0] = count - 1;
+    for (int32_t i = 1; i < count; ++i) r[i] = pos[o + i];
+    for (int32_t i = count; i % 4 != 0; ++i) r[i] = 0;
+  }
+  pair[v] = t;
 }
 
 // Between the caller's node order and the internal one, per component, as a
@@ -1421,10 +1452,16 @@ template void permute_out<double>(int, int64_t, const int32_t *, const double *,
 template void permute_out<float>(int, int64_t, const int32_t *, const float *, float *,
                                  hipStream_t);
 
-void map_internal(const int32_t *idx_c, const int32_t *iperm, int32_t *idx, int64_t count,
-                  hipStream_t s) {
-  hipLaunchKernelGGL(k_map_internal, dim3(grid_blocks(count)), dim3(kVecThreads), 0, s, idx_c,
-                     iperm, idx, count);
+void map_ids(const int32_t *in, const int32_t *map, int32_t *out, int64_t count, hipStream_t s) {
+  hipLaunchKernelGGL(k_map_ids, dim3(grid_blocks(count)), dim3(kVecThreads), 0, s, in, map, out,
+                     count);
+}
+
+void slot_records(int64_t n, const int32_t *off, const int32_t *rec, const int32_t *pos,
+                  int2 *pair, int4 *list, hipStream_t s) {
+  fill_f32((float *)list, 4, 0.0f, s);
+  hipLaunchKernelGGL(k_slot_records, dim3(vec_blocks(n)), dim3(kVecThreads), 0, s, n, off, rec,
+                     pos, pair, list);
 }
 
 int64_t vec_blocks(int64_t n) {
