@@ -137,11 +137,11 @@ struct bp_op_s {
   // internal node order (interior_first_order): perm[v] = the caller's id of
   // internal node v (NULL: the caller's order); internal nodes [0, n_owned)
   // are element-interior, each written by its element with a plain store;
-  // xi: x of a solve in the internal order; bi: b of a mixed solve
+  // xi: x of a solve in the internal order
   int32_t *perm = nullptr;
   int32_t *iperm = nullptr;  // iperm[g] = the internal id of the caller's node g
   int64_t n_owned = 0;
-  double *bi = nullptr, *xi = nullptr;
+  double *xi = nullptr;
   double *wl = nullptr;
   float *wl32 = nullptr;
   std::vector<hipEvent_t> apply_ev;  // pairs around operator launches

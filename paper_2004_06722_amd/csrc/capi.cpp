@@ -86,7 +86,6 @@ void release(bp_op op) {
   dfree(op->tr_list);
   dfree(op->perm);
   dfree(op->iperm);
-  dfree(op->bi);
   dfree(op->xi);
   dfree(op->wl);
   dfree(op->wl32);
@@ -770,7 +769,6 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
     else
       map_ids(op->idx_c, op->iperm, op->idx, nelem * n3, s);
     TRYHIP(hipGetLastError());
-    if (op->fp32) TRY(dmalloc(&op->bi, nv));
     TRY(dmalloc(&op->xi, nv));
   }
   // Gauss-Legendre operators: the transposed gather map (counting sort of the
@@ -1130,9 +1128,10 @@ int bp_pcg_solve_mixed(bp_op op, const double *b, double *x_out, double outer_rt
   // the events were created by bp_setup: the solve allocates nothing
   hipEvent_t t0 = op->evm0, t1 = op->evm1;
   if (op->perm) {
-    permute_in<double>(nc, n, op->perm, b, op->bi, s);
+    // pv, the direction of the FP64 solves, holds b: the inner solves have p32
+    permute_in<double>(nc, n, op->perm, b, op->pv, s);
     permute_in<double>(nc, n, op->perm, x, op->xi, s);
-    b = op->bi;
+    b = op->pv;
     x = op->xi;
   }
   BP_HIP(hipEventRecord(t0, s));
