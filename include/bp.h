@@ -339,17 +339,20 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
  *     the standard recurrences (FP64 solves and FP32 inner solves), where the
  *     partial-sum tables are short enough for every work-group to reduce them
  *     itself, each in one fixed order (bit-identical in all work-groups):
- *     1: rows of 256 nodes up to 1024 rows, of 1024 nodes beyond (up to 1024
- *     rows, about 1e6 nodes, and four components): every work-group of
- *     the residual update computes alpha from the operator's partial sums and
+ *     1: up to 1024 vector rows of 256 nodes (262,144 nodes) and 1024 operator
+ *     work-groups, or, with rows of 1024 nodes, up to four components, 1024 rows
+ *     (1,048,576 nodes) and 4096 work-groups while rows x work-groups x
+ *     components stay at most 2^20: every work-group of the residual update computes alpha from the operator's partial sums and
  *     every work-group of the direction update computes beta and the
  *     convergence test from the residual update's: three launches per
  *     iteration instead of five (the mass on Gauss-Legendre points, which
  *     assembles by a gather in the residual update, keeps five).
  *     2: in addition, for the collocated stiffness operator of one component
- *     up to p = 8, while (vector rows) x (operator work-groups) stays at
- *     most 9M (about 1.2e6 nodes at p = 7): the
- *     operator launch forms the direction p_k = z_k + beta p_{k-1} at the
+ *     up to p = 8, with at most 2400 vector rows (of 256 nodes up to 1024 rows, of
+ *     1024 nodes beyond) and 8192 operator work-groups, rows x work-groups at most
+ *     9 * 2^20, and in FP64 at most 20 rows per thread of a work-group (64 threads
+ *     at p = 1, 2, 3, 7, 128 at p = 4, 256 at p = 5, 6, 8; in FP64 up to about 1.3e6
+ *     nodes at p = 7, 2.4e6 at p = 8, 9e5 at p = 3, 1.3e5 at p = 1): the operator launch forms the direction p_k = z_k + beta p_{k-1} at the
  *     nodes it gathers (beta and the stopping test from the vector kernel's
  *     partial sums) and one vector kernel stores p_k and updates x and the
  *     residual: two launches per iteration. Above those bounds, in FP64 while a

@@ -365,7 +365,7 @@ int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, con
   // two launches per iteration where the operator forms p itself (PZIter);
   // its shorter vector table lets it run on larger meshes than the three
   const bool fused2 = op->cg_fuse == 2 && !mass_wl && apply_pz_supported(op, which) &&
-                      cg_fused2_fits(n, nb_apply);
+                      cg_fused2_fits(n, nb_apply, f32 ? 0 : apply_threads(op));
   // above those bounds the same operator with beta from the finisher and one
   // vector pass for p, x and z: four launches instead of five, in FP64 while
   // the vectors stay below the streaming size (measured at p = 7: 0.3-2%

@@ -12,6 +12,8 @@ int64_t plane_epb(int p1, int q, int which);
 // apply_blocks is the largest over mass and stiffness (partial buffer size)
 int64_t apply_rows(const bp_op_s *op, int which);
 int64_t apply_blocks(const bp_op_s *op);
+// threads of a work-group of the stiffness operator
+int apply_threads(const bp_op_s *op);
 // partial rows that any one operator application may write (buffer sizing)
 int64_t max_partial_rows(const bp_op_s *op);
 // The node order of the vectors a launch reads and writes. Internal: the
@@ -134,11 +136,24 @@ void cg_update_xp_fused(int nc, int64_t n, T *x, T *p, const T *z, const double 
 // reduces pr into the scalars the host reads (r.z, r.r, and the stopping
 // test of the last iterate).
 // The bounds of the two partial tables: every work-group of each launch reads
-// the other's (measured at p = 7: 13-14% gained at E = 2^10, 2^11; up to
-// products of 9M FP32 solves gain 1-10%, FP64 ones 0-4%, against the forms below)
-constexpr int64_t kFused2VecRows = 2400, kFused2ApplyRows = 8192;
+// the other's. Four launches (FP32: five) -> two, 40 iterations in us, inside and
+// outside each bound:
+// - product of the two: FP64 p = 5, E = 26^3 (5.5M) 3856 -> 3638, p = 6, 22^3
+//   (4.9M) 3879 -> 3626, p = 4, 28^3 (6.2M) 3106 -> 3117, 30^3 (9.3M) 3545 -> 3700;
+//   FP32 p = 7, 16^3 (5.8M) 1806 -> 1775, 17^3 (8.3M) 2038 -> 2062, 18^3 (11.7M)
+//   2299 -> 2422;
+// - vector rows: p = 8, 16^3 (2097 rows) 3102 -> 3017; 17^3 (2512) 3635 -> 3454
+//   would gain as well;
+// - operator work-groups: p = 1, 50^3 (7813) 1410 -> 1328, 54^3 (9842) 1578 -> 1630;
+// - vector rows per thread of the operator, FP64 (a work-group of one wave, p = 1, 2,
+//   3, 7, sums them in that many dependent steps): p = 7, 14^3 (15) 1770 -> 1765,
+//   15^3 (18) 2067 -> 2092 (60 iterations in another run 3164-3247 -> 3148-3162),
+//   16^3 (22) 2280 -> 2396, 17^3 (26) 2716 -> 3131; p = 3, 32^3 (14) 2650 -> 2643.
+//   The FP32 kernel gains to 22 a thread (above).
+constexpr int64_t kFused2VecRows = 2400, kFused2ApplyRows = 8192, kFused2ThreadRows = 20;
 constexpr int64_t kFused2Product = int64_t(9) << 20;
-bool cg_fused2_fits(int64_t n, int64_t nb_apply);
+// threads: of the operator's work-groups, in FP64 (0: no bound of rows per thread)
+bool cg_fused2_fits(int64_t n, int64_t nb_apply, int threads);
 bool apply_pz_supported(const bp_op_s *op, int which);
 template <typename T>
 int launch_apply_pz(const bp_op_s *op, const T *p, T *w, bool masked, double *part,

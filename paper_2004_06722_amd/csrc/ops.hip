@@ -19,6 +19,12 @@ int64_t apply_rows(const bp_op_s *op, int which) {
   return (op->nelem + epb - 1) / epb;
 }
 
+int apply_threads(const bp_op_s *op) {
+  const int64_t n = plane_epb(op->p1, op->q, BP_STIFF) * std::max(op->p1, op->q) *
+                    std::max(op->p1, op->q);
+  return (int)((n + 63) / 64 * 64);
+}
+
 int64_t apply_blocks(const bp_op_s *op) {
   const int64_t a = apply_rows(op, BP_MASS), b = apply_rows(op, BP_STIFF);
   return a > b ? a : b;

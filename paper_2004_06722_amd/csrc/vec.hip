@@ -1762,10 +1762,10 @@ int64_t rxp_rows(int64_t n) {
 // Every work-group of each launch reads the other launch's whole partial
 // table: the bound keeps those redundant reads (rows x work-groups) small
 // against what the two dropped launches cost.
-bool cg_fused2_fits(int64_t n, int64_t nb_apply) {
+bool cg_fused2_fits(int64_t n, int64_t nb_apply, int threads) {
   const int64_t nv = rxp_rows(n);
   return nv <= kFused2VecRows && nb_apply <= kFused2ApplyRows &&
-         nv * nb_apply <= kFused2Product;
+         nv * nb_apply <= kFused2Product && (threads == 0 || nv <= kFused2ThreadRows * threads);
 }
 
 bool cg_fused_fits(int nc, int64_t n, int64_t nb_apply) {
