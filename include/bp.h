@@ -352,10 +352,11 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
  *     1024 nodes beyond) and 8192 operator work-groups, rows x work-groups at most
  *     9 * 2^20, and in FP64 at most 20 rows per thread of a work-group (64 threads
  *     at p = 1, 2, 3, 7, 128 at p = 4, 256 at p = 5, 6, 8; in FP64 up to about 1.3e6
- *     nodes at p = 7, 2.4e6 at p = 8, 9e5 at p = 3, 1.3e5 at p = 1): the operator launch forms the direction p_k = z_k + beta p_{k-1} at the
- *     nodes it gathers (beta and the stopping test from the vector kernel's
- *     partial sums) and one vector kernel stores p_k and updates x and the
- *     residual: two launches per iteration. Above those bounds, in FP64 while a
+ *     nodes at p = 7, 2.4e6 at p = 8, 9e5 at p = 3, 1.3e5 at p = 1): the operator
+ *     launch forms the direction p_k = z_k + beta p_{k-1} at the nodes it gathers
+ *     (beta and the stopping test from the vector kernel's partial sums) and one
+ *     vector kernel stores p_k and updates x and the residual: two launches per
+ *     iteration. Above those bounds, in FP64 while a
  *     vector stays below 64 MiB, the same operator takes beta from the
  *     finisher of the previous iteration and the vector kernel sits between
  *     the two finishers: four launches.

@@ -58,7 +58,9 @@ int launch_grad_kappa(const bp_op_s *op, const double *lam, const double *u, dou
 // conversions use a capped grid-stride grid (grid_blocks). Up to
 // kDirectRows pairs of block partial sums go straight to the final fixed-order
 // single-work-group sum (one launch less per reduction on small meshes; eight
-// columns of 16,290 rows took it 28 us);
+// columns of 16,290 rows took it 28 us; one column folded or direct, 40 iterations:
+// 17,576 rows 7603 and 7600 us, 21,952 rows 9399 and 9450, 29,791 rows 12,396 and
+// 12,370);
 // more are first folded to at most kStage2Rows rows, stored right after
 // the partials.
 constexpr int kVecThreads = 256;
@@ -112,9 +114,15 @@ void cg_update_xp(int nc, int64_t n, T *x, T *p, const T *z, DevScalars *sc, hip
 // the tables that every work-group reduces stay short.
 constexpr int64_t kFusedRows = 1024;
 constexpr int kRxpNodes = 4;
-// the wider form: components, and the bounds of its tables (20 iterations,
-// five launches -> three: BP3 p = 7, E = 11^3 772 -> 687 us, three components
-// there 1470 -> 1263 us, p = 11, E = 7^3 three components 1656 -> 1427 us)
+// the wider form: components, and the bounds of its tables. Five launches ->
+// three, 40 iterations in us: at the bounds one component gains 7-8% (BP3 p = 7,
+// E = 14^3, 948 rows, 2055 -> 1897; p = 3, 26^3, product 0.9M, 1914 -> 1770), three 11%
+// (BP4 p = 7, 12^3, 1.04M, 3701 -> 3305), four 15% (BP6 p = 9, 8^3, 0.8M, 2537 ->
+// 2163). Beyond them it still gains, less with the product: BP3 p = 7, 17^3 (2.8M)
+// 3150 -> 2908, p = 3, 32^3 (2.9M) 2970 -> 2854, BP4 p = 7, 13^3 (1.7M) 3833 -> 3428,
+// 15^3 (3.9M) 5478 -> 5199; BP5 p = 7, 20^3 (22M) 3883 -> 3911, FP32 2779 -> 2937, p =
+// 3, 34^3 (10M) 3008 -> 3035. The bounds are the sizes that were tried first, not
+// the last ones that gain.
 constexpr int kFusedWide = 4;
 constexpr int64_t kFused3ApplyRows = 4096, kFused3Product = int64_t(1) << 20;
 int64_t rxp_rows(int64_t n);  // partial rows of the fused vector kernels

@@ -1,5 +1,6 @@
-"""Solves on both sides of the bounds that choose how many launches an iteration
-takes: vector rows per thread of the operator's work-groups (20 in FP64: p = 7
+"""Solves on both sides of the bounds that choose how an iteration is launched.
+How partial tables are folded: above 16384 rows, or 32768 sums. How many launches
+it takes: vector rows per thread of the operator's work-groups (20 in FP64: p = 7
 between E = 15^3 and 16^3; p = 3 with 14, p = 4 with 12). The
 iterates of every form are those of the five launches, normwise to 1e-12."""
 import pytest
@@ -38,3 +39,28 @@ def test_iterates_on_both_sides(p, grid):
                 ref.setdefault(iters, x)
                 err = float(torch.norm(x - ref[iters]) / torch.norm(ref[iters]))
                 assert err <= TOL, (fuse, iters, err)
+
+
+@pytest.mark.parametrize("p,grid,ncomp", [(7, (32, 32, 16), 1), (7, (32, 32, 17), 1),
+                                          (7, (32, 32, 16), 2), (7, (33, 16, 16), 4),
+                                          (7, (32, 16, 16), 4)])
+def test_folded_and_direct_sums_agree(p, grid, ncomp):
+    # one work-group an element at p = 7: operator tables of 16384 and 17408 rows of
+    # one sum, 16384 of two, 8448 and 8192 of four. The two- or four-launch and the
+    # five-launch forms sum tables of other lengths
+    op, b = operator(p, grid, ncomp)
+    with op:
+        ref = None
+        for fuse, sr in ((0, False), (2, False), (0, True)):
+            op.set_option(_lib.BP_OPT_CG_FUSE, fuse)
+            op.set_cg_variant(sr)
+            x, _ = op.pcg_solve(b, maxit=4, fixed_iters=True)
+            torch.cuda.synchronize()
+            ref = x if ref is None else ref
+            assert float(torch.norm(x - ref) / torch.norm(ref)) <= TOL, (fuse, sr)
+            # the residual that the sums give is the true one
+            r = b - op.apply(B.STIFF, x)
+            _, st = op.pcg_solve(b, x=x.clone(), maxit=0)
+            true = float(torch.norm(r) / torch.norm(b)) if ncomp == 1 else float(
+                torch.norm(r[0]) / torch.norm(b[0]))
+            assert abs(st["rel_res"][0] - true) <= 1e-12 * max(true, 1.0)
