@@ -251,8 +251,9 @@ int download_scalars(bp_op op, hipStream_t s) { return download_scalars(op, op->
 
 // Nodes [0, n) whose w the operator for `which` overwrites with plain stores
 // on every application (the element-interior block of the internal order),
-// so the vector updates need not clear them. The Gauss-Legendre mass
-// assembles w by adding Q^T w_L (gather_local) and needs w cleared.
+// so the vector updates need not clear them. (The single-reduction updates
+// clear all of w before the Gauss-Legendre mass overwrites it; the standard ones
+// gather that w themselves.)
 int64_t stored_rows(const bp_op_s *op, int which) {
   return which == BP_MASS && op->tr_pair ? 0 : op->n_owned;
 }
@@ -305,7 +306,7 @@ int apply_guess(bp_op op, DevScalars *sc, int which, const SolveVectors<T> &v, T
   const bool scan = !x0_zero && sizeof(T) == 8 && own_data;
   int rc = upload_scalars(op, sc, rtol, fixed, x0_zero || scan, s);
   if (rc) return rc;
-  clear(w, nv, s);
+  if (!(which == BP_MASS && op->tr_pair)) clear(w, nv, s);  // that mass overwrites w
   if (x0_zero) return BP_OK;
   if (scan) scan_nonzero((const double *)v.x0, nv, sc, s);
   const int *skip = scan ? &sc->x0_zero : nullptr;
@@ -353,7 +354,7 @@ int pcg_run(bp_op op, const CgWork &ws, int which, const SolveVectors<T> &v, con
   const bool check = !fixed;
   const int *done = check ? &sc->done : nullptr;
   // mass on Gauss-Legendre points: the kernel stores w_L and the residual
-  // update gathers w = Q^T w_L itself (w stays zero)
+  // update gathers w = Q^T w_L itself (w is not used)
   const bool mass_wl = which == BP_MASS && op->tr_pair != nullptr;
   const int64_t nl = op->nelem * op->p1 * op->p1 * op->p1;
   const T *wl = reinterpret_cast<const T *>(sizeof(T) == 4 ? (const void *)op->wl32
@@ -1226,7 +1227,7 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
   } else {
     difference(u, u_target, op->r, nv, s);
     double *const Md = grad && (op->tr_pair || takes_atomics(op, grad)) ? grad : op->w;
-    fill_f64(Md, nv, 0.0, s);
+    if (!op->tr_pair) clear(Md, nv, s);  // else overwritten
     rc = launch_apply(op, BP_MASS, false, caller_map(op), op->r, Md, false, pa, nullptr, s);
     if (rc) return rc;
     if (grad && Md != grad) permute_out(nc, n, nullptr, (const double *)Md, grad, s);

@@ -27,14 +27,12 @@ struct NodeMap {
   int own;
 };
 inline NodeMap internal_map(const bp_op_s *op) { return {op->idx, op->n_owned > 0 ? 1 : 0}; }
-inline NodeMap caller_map(const bp_op_s *op) {
-  return {op->idx_c, op->idx_c == op->idx && op->n_owned > 0 ? 1 : 0};
-}
+inline NodeMap caller_map(const bp_op_s *op) { return {op->idx_c, 0}; }
 // w, in the order of m, is clear before (the Gauss-Legendre mass overwrites it)
 int launch_apply(const bp_op_s *op, int which, bool f32, const NodeMap &m, const void *u, void *w,
                  bool masked, double *part, const int *done, hipStream_t s);
 // mass element kernel with element-local output: op->wl (op->wl32 if f32)
-// [ncomp][nelem][p1^3] = B_L (Q u), zero at masked nodes; needs op->tr_off
+// [ncomp][nelem][p1^3] = B_L (Q u), zero at masked nodes; needs op->tr_pair
 // (Gauss-Legendre operators). launch_apply(BP_MASS) runs it and then
 // gather_local; the PCG iteration fuses the gather into the residual update.
 int launch_mass_wl(const bp_op_s *op, bool f32, const NodeMap &m, const void *u, bool masked,
