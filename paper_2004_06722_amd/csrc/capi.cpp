@@ -818,6 +818,8 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   const int64_t ng = nelem * 6 * nq, nb = nelem * nq;
   TRY(dmalloc(&op->G, ng));
   TRY(dmalloc(&op->Bt, nb));
+  TRY(dmalloc(&op->r, nv));
+  TRY(dmalloc(&op->w, nv));
   if (op->colloc) TRY(dmalloc(&op->md, nglobal));
   {
     double *X = nullptr;
@@ -832,6 +834,11 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
     if (!rc && hipMemcpyAsync(bad, &big, sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess)
       rc = set_error(BP_ERR_HIP, "bp_setup: flag upload failed");
     if (!rc) rc = launch_geometry(op, X, op->G, op->Bt, bad, s);
+    if (!rc && op->colloc) {  // r and w hold the two parts of the sums meanwhile
+      assemble_mass(op->idx_c, op->Bt, nelem * n3, nglobal, op->md, op->r, op->w, s);
+      if (hipGetLastError() != hipSuccess)
+        rc = set_error(BP_ERR_HIP, "bp_setup: mass assembly failed");
+    }
     if (!rc && (hipMemcpyAsync(&bad_host, bad, sizeof(int), hipMemcpyDeviceToHost, s) !=
                     hipSuccess ||
                 hipStreamSynchronize(s) != hipSuccess))
@@ -845,15 +852,8 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
   }
   TRY(dmalloc(&op->dinv[0], nglobal));
   TRY(dmalloc(&op->dinv[1], nglobal));
-  TRY(dmalloc(&op->r, nv));
   TRY(dmalloc(&op->pv, nv));
-  TRY(dmalloc(&op->w, nv));
   TRY(dmalloc(&op->tmp, std::max<int64_t>(nv, nglobal)));
-  if (op->colloc) {  // r and w hold the two parts of the sums meanwhile
-    assemble_mass(op->idx_c, op->Bt, nelem * n3, nglobal, op->md, op->r, op->w, s);
-    TRYHIP(hipGetLastError());
-    TRYHIP(hipStreamSynchronize(s));
-  }
   // partial sums of the largest grid, followed by the stage-1 rows
   op->part_len =
       (vec_blocks(nglobal) + kStage2Rows) * 3 * ncomp + (max_partial_rows(op) + kStage2Rows) * ncomp;

@@ -1066,9 +1066,12 @@ __global__ __launch_bounds__(kVecThreads) void k_misfit_diagonal(
 // order of arrival differ in the last ones): the largest term of each node (as
 // bits: positive doubles order as integers), then each term as two integers
 // against that one's exponent E, 2^(E - 30) hi + 2^(E - 61) lo with hi, lo <=
-// 2^31 (a term is off by at most 2^-62 of the largest, and 2^32 of them fit),
-// then the node's sum, rounded once.
+// 2^31 (a term is off by at most 2^-62 of the largest, and nearly 2^32 of them
+// fit below the top bit of hi, which marks a Dirichlet node), then the node's
+// sum, rounded once; negative on Dirichlet nodes. (Terms of a mesh that bp_setup
+// goes on to refuse may be negative or not finite: their sums mean nothing.)
 using u64 = unsigned long long;
+constexpr u64 kMassMark = u64(1) << 63;
 static_assert(sizeof(u64) == sizeof(double), "sums in place of doubles");
 __device__ __forceinline__ int64_t slot_node(int32_t v) { return v >= 0 ? v : -1 - v; }
 
@@ -1087,9 +1090,11 @@ __global__ __launch_bounds__(kVecThreads) void k_mass_add(const int32_t *__restr
                                                           u64 *hi, u64 *lo) {
   for (int64_t k = (int64_t)blockIdx.x * kVecThreads + threadIdx.x; k < count;
        k += (int64_t)gridDim.x * kVecThreads) {
-    const int64_t g = slot_node(idx[k]);
+    const int32_t i = idx[k];
+    const int64_t g = slot_node(i);
     const double v = ldexp(Bt[k], 30 - ilogb(largest[g])), h = floor(v);
     atomicAdd(hi + g, (u64)h);
+    if (i < 0) atomicOr(hi + g, kMassMark);
     atomicAdd(lo + g, (u64)rint(ldexp(v - h, 31)));
   }
 }
@@ -1099,20 +1104,13 @@ __global__ __launch_bounds__(kVecThreads) void k_mass_sum(int64_t n, double *__r
                                                           const u64 *__restrict__ hi,
                                                           const u64 *__restrict__ lo) {
   const int64_t v = (int64_t)blockIdx.x * kVecThreads + threadIdx.x;
-  if (v >= n || md[v] == 0.0 || isinf(md[v])) return;
+  if (v >= n || md[v] == 0.0) return;
   const int e = ilogb(md[v]);
-  md[v] = ldexp((double)hi[v], e - 30) + ldexp((double)lo[v], e - 61);
-}
-
-// md = -|md| on the Dirichlet nodes that the map marks
-__global__ __launch_bounds__(kVecThreads) void k_mark_dirichlet(const int32_t *__restrict__ idx,
-                                                                int64_t count,
-                                                                double *__restrict__ md) {
-  for (int64_t k = (int64_t)blockIdx.x * kVecThreads + threadIdx.x; k < count;
-       k += (int64_t)gridDim.x * kVecThreads) {
-    const int32_t g = idx[k];
-    if (g < 0) md[-1 - g] = -fabs(md[-1 - g]);
-  }
+  const u64 h = hi[v];
+  const double m = isinf(md[v]) ? md[v]
+                                : ldexp((double)(h & ~kMassMark), e - 30) +
+                                      ldexp((double)lo[v], e - 61);
+  md[v] = h & kMassMark ? -m : m;
 }
 
 // d = a - b entry by entry (d may be a)
@@ -1884,7 +1882,6 @@ void assemble_mass(const int32_t *idx, const double *Bt, int64_t count, int64_t 
   hipLaunchKernelGGL(k_mass_largest, g, t, 0, s, idx, Bt, count, reinterpret_cast<u64 *>(md));
   hipLaunchKernelGGL(k_mass_add, g, t, 0, s, idx, Bt, count, md, h, l);
   hipLaunchKernelGGL(k_mass_sum, dim3(vec_blocks(n)), t, 0, s, n, md, h, l);
-  hipLaunchKernelGGL(k_mark_dirichlet, g, t, 0, s, idx, count, md);
 }
 
 void difference(const double *a, const double *b, double *d, int64_t count, hipStream_t s) {
