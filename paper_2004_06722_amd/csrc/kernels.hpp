@@ -505,15 +505,17 @@ __device__ __forceinline__ void stiff_colloc_body(
 //
 // What bounds it: HBM traffic at p1 = 7, 8 and E large; below, the atomic
 // scatter; above, with one thread per node and rows read through LDS (3 + 4 p1
-// accesses per node), the LDS pipe and two waves per SIMD did. So each lane
+// accesses per node), the waits of two waves per SIMD did (p1 = 12 element-local: 416
+// LDS and 1380 vector instructions a wave, now 132 and 982). So each lane
 // takes whole pencils of the element in registers instead, as the
 // Gauss-Legendre kernels do: the column (i, j) along t, the row (j, k) along r,
 // the pencil (i, k) along s, with the even-odd splitting (D^ is
 // centro-antisymmetric), and two LDS tiles hand the pencils over: 15 accesses
 // per node. Loads come in few dependent round trips: the map and the first
 // chunk of G at entry, then u, then the further chunks one ahead of their use.
-// Chunks of 4 planes leave registers for three waves per SIMD at p1 = 9..11,
-// chunks of 2 (p1 >= 12, two waves) for no spills. Loads are branch-free: an
+// With chunks of 4 planes FP64 takes 155, 163 and 170 registers at p1 = 9, 10, 11
+// (three waves per SIMD up to 168, so two at p1 = 11), with chunks of 2 144 to 160 at
+// p1 = 12..15 (three waves) and 171 at p1 = 16 (two). Loads are branch-free: an
 // element slot past the end reads the last element and a Dirichlet node reads
 // its (valid) global entry, both masked. D^ is a compile-time table
 // (rules1d.hpp). The local energy u_L^T A_L u_L is accumulated at the
@@ -531,7 +533,7 @@ __device__ __forceinline__ void stiff_colloc_body(
 // 378, p1 = 10 E = 24^3 214 -> 177, p1 = 12 E = 6120 239 -> 131, p1 = 14
 // E = 3584 290 -> 131, p1 = 16 E = 2352 254 -> 118; element-local p1 = 12 189 -> 112;
 // three components p1 = 8 E = 41x37x29 597 -> 520, p1 = 10 E = 24^3 641 -> 370.
-// At least two waves per SIMD are asked for (it binds from p1 = 12 in FP64).
+// At least two waves per SIMD are asked for; no instance spills.
 // ---------------------------------------------------------------------------
 template <int P1, typename T, bool LOCAL = false, bool HELM = false>
 __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) __attribute__((amdgpu_waves_per_eu(2))) void k_stiff_colloc(
@@ -1311,7 +1313,11 @@ __global__ __launch_bounds__(256) void k_diag(int64_t nelem, int p1, int q, int 
 // stays live; the next field's column is requested while the current one is
 // differentiated. 300 us at p = 5, E = 32^3, eight components, in the caller's
 // node order (one thread per node: 405 us in the internal order, and two
-// permutations of 158 us before it). lam and u are masked on Dirichlet nodes (those read as 0).
+// permutations of 158 us before it). At p1 = 9 it wants 46 registers more than the
+// 256 that leave two waves per SIMD and spills them (180 bytes a lane); one thread
+// per node took 309 and one wave. The whole call there, before and now: E = 16^3, eight
+// components 517 -> 240 us, 12^3, three 97 -> 57, 24^3, one 300 -> 235; p1 = 8, 24^3,
+// three 432 -> 136. lam and u are masked on Dirichlet nodes (those read as 0).
 // ---------------------------------------------------------------------------
 template <int P1>
 __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) __attribute__((amdgpu_waves_per_eu(2))) void k_grad_kappa_colloc(
