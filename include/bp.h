@@ -102,8 +102,10 @@ int bp_rule(int n, int quad, double *x, double *w);
  * still takes and returns vectors in the caller's numbering: the solves
  * permute b and x on entry and exit (one gather pass each) and iterate in the
  * internal order; single applications, diagonals and gradients go through a
- * second gather map in the caller's ids (int32, nelem p1^3). The results are
- * the same up to the rounding order of the assembly sums.
+ * second gather map in the caller's ids (int32, nelem p1^3), or where those are
+ * scattered over memory (an unstructured numbering, found from the map) and the
+ * vectors large, through the internal order as well. The results are the same up
+ * to the rounding order of the assembly sums.
  * With GL quadrature (and nelem p1^3 < 2^31) the operator also holds the
  * transposed gather map (two int32 a node, and a list of at most 2 nelem p1^3
  * int32 for the nodes of more than two slots) and

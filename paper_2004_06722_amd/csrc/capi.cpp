@@ -185,6 +185,9 @@ struct CgWork {
 
 CgWork own_work(bp_op op) { return CgWork{op->part, op->sc}; }
 
+// op->spread of random ids and more (by_internal_order)
+constexpr double kSpreadFar = 2.0;
+
 // Flags of the library's timing events: without the system-scope release of
 // a default event, whose cache writeback and invalidation would slow the
 // timed kernels and those after them.
@@ -256,6 +259,36 @@ int download_scalars(bp_op op, hipStream_t s) { return download_scalars(op, op->
 // gather that w themselves.)
 int64_t stored_rows(const bp_op_s *op, int which) {
   return which == BP_MASS && op->tr_pair ? 0 : op->n_owned;
+}
+
+// Whether a call outside the solves runs in the internal order, between a
+// permutation of its input and one of its result, rather than on the map in the
+// caller's ids. The permutations read and write every line once (and two launches);
+// the map in the caller's ids reads and adds into as many lines per element as the
+// numbering spreads its nodes over. op->spread is that number against a
+// lexicographic numbering's (1; with the nodes ordered by vertices, edges, faces and
+// interiors 1.5 to 1.8; random ids 2.7 to 7). us, caller's ids / internal order:
+// - stiffness FP64, p = 7, E = 28^3: lexicographic 157 / 227, by entity 211 / 222,
+//   random 535 / 421; p = 2, 60^3: 94 / 139, 100 / 143, 269 / 174
+// - FP32: 118 / 148, 195 / 145, 556 / 326; p = 2: 77 / 105, 83 / 107, 295 / 127
+// - Gauss-Legendre mass, p = 7, 24^3: 66 / 133, 84 / 129, 341 / 246
+// - diagonal 179 / 220, 222 / 216, 508 / 319, of the mass 128 / 159, 186 / 156,
+//   481 / 262; gradient 130 / 221, 150 / 220, 593 / 417. The Gauss-Legendre
+//   stiffness diagonal is held by its arithmetic: 515 / 530, 500 / 524, 549 / 596
+// Small vectors stay in the caches, and there the launches count (random ids, p = 5):
+// stiffness FP64 n = 2.3e5 27 / 27, 5.3e5 55 / 42; FP32 1e5 17 / 22, 2.3e5 26 / 23;
+// mass (p = 4) 5.3e5 39 / 34, 2.3e5 21 / 24; diagonal 1e5 16 / 19, 2.3e5 23 / 20;
+// gradient 5.3e5 37 / 35, 2.3e5 12 / 21.
+enum class Route { Stiff, Stiff32, Mass, Diag, DiagMass, Gradient };
+bool by_internal_order(const bp_op_s *op, Route call) {
+  if (!op->perm || (call == Route::Diag && !op->colloc)) return false;
+  const bool diag = call == Route::Diag || call == Route::DiagMass;
+  const double tight = op->p >= 4 ? 1.4 : kSpreadFar;
+  const double far = call == Route::Stiff32 || call == Route::DiagMass ? tight : kSpreadFar;
+  const int64_t least = diag || call == Route::Stiff32 ? 190000
+                        : call == Route::Stiff         ? 300000
+                                                       : 480000;
+  return op->spread > far && op->nglobal * (diag ? 1 : op->ncomp) >= least;
 }
 
 // Whether two arrays share a byte.
@@ -771,6 +804,7 @@ int bp_setup(bp_op *out, int p, int q, int quad, int ncomp, int64_t nelem, int64
       map_ids(op->idx_c, op->iperm, op->idx, nelem * n3, s);
     TRYHIP(hipGetLastError());
     TRY(dmalloc(&op->xi, nv));
+    op->spread = id_spread(p1, nelem, elem_dofs);
   }
   // Gauss-Legendre operators: the transposed gather map (counting sort of the
   // element-local slots by node, ascending within a node, which the device turns
@@ -972,8 +1006,18 @@ int bp_apply(bp_op op, int which, int prec, const void *u, void *w, unsigned fla
   const bool adds = !diagonal && !(which == BP_MASS && op->tr_pair);  // else w is overwritten
   // a w that the additions or the reads of u forbid: through the operator's own
   const size_t bytes = (size_t)nv * (f32 ? sizeof(float) : sizeof(double));
-  const bool aside = overlap(u, bytes, w, bytes) || (adds && !takes_atomics(op, w));
+  const Route call = which == BP_MASS ? Route::Mass : f32 ? Route::Stiff32 : Route::Stiff;
+  const bool permuted = !diagonal && by_internal_order(op, call);
+  const bool aside = permuted || overlap(u, bytes, w, bytes) || (adds && !takes_atomics(op, w));
   void *const wo = !aside ? w : f32 ? (void *)op->w32 : (void *)op->w;
+  const NodeMap map = permuted ? internal_map(op) : caller_map(op);
+  if (permuted && f32) {
+    permute_in(op->ncomp, op->nglobal, op->perm, (const float *)u, op->r32, s);
+    u = op->r32;
+  } else if (permuted) {
+    permute_in(op->ncomp, op->nglobal, op->perm, (const double *)u, op->r, s);
+    u = op->r;
+  }
   if (diagonal) {
     if (f32)
       mass_diagonal(op->ncomp, op->nglobal, op->md, (const float *)u, (float *)wo, masked, s);
@@ -985,14 +1029,15 @@ int bp_apply(bp_op op, int which, int prec, const void *u, void *w, unsigned fla
       clear((float *)wo, nv, s);
     else if (adds)
       clear((double *)wo, nv, s);
-    rc = launch_apply(op, which, f32, caller_map(op), u, wo, masked, nullptr, nullptr, s);
+    rc = launch_apply(op, which, f32, map, u, wo, masked, nullptr, nullptr, s);
     if (rc) return rc;
   }
   if (!aside) return BP_OK;
+  const int32_t *const back = permuted ? op->iperm : nullptr;
   if (f32)
-    permute_out(op->ncomp, op->nglobal, nullptr, (const float *)wo, (float *)w, s);
+    permute_out(op->ncomp, op->nglobal, back, (const float *)wo, (float *)w, s);
   else
-    permute_out(op->ncomp, op->nglobal, nullptr, (const double *)wo, (double *)w, s);
+    permute_out(op->ncomp, op->nglobal, back, (const double *)wo, (double *)w, s);
   BP_HIP(hipGetLastError());
   return BP_OK;
 }
@@ -1016,11 +1061,13 @@ int bp_diag(bp_op op, int which, double *d, unsigned flags, void *stream) {
   if (!d) return set_error(BP_ERR_ARG, "bp_diag: NULL output");
   if (flags & ~BP_MASKED) return set_error(BP_ERR_ARG, "bp_diag: unknown flag");
   hipStream_t s = (hipStream_t)stream;
-  double *const dd = takes_atomics(op, d) ? d : op->tmp;
+  const bool permuted = by_internal_order(op, which == BP_MASS ? Route::DiagMass : Route::Diag);
+  double *const dd = !permuted && takes_atomics(op, d) ? d : op->tmp;
   fill_f64(dd, op->nglobal, 0.0, s);
-  rc = launch_diag(op, which, caller_map(op), dd, (flags & BP_MASKED) != 0, s);
+  rc = launch_diag(op, which, permuted ? internal_map(op) : caller_map(op), dd,
+                   (flags & BP_MASKED) != 0, s);
   if (rc || dd == d) return rc;
-  permute_out(1, op->nglobal, nullptr, (const double *)dd, d, s);
+  permute_out(1, op->nglobal, permuted ? op->iperm : nullptr, (const double *)dd, d, s);
   BP_HIP(hipGetLastError());
   return BP_OK;
 }
@@ -1195,12 +1242,13 @@ int bp_grad_kappa(bp_op op, const double *lam, const double *u, double *g, void 
   // overlaps are read from copies
   const size_t in = (size_t)op->nglobal * op->ncomp * sizeof(double);
   const size_t out = (size_t)op->nelem * op->q * op->q * op->q * sizeof(double);
+  const bool permuted = by_internal_order(op, Route::Gradient);
   for (auto [v, copy] : {std::pair(&lam, op->r), std::pair(&u, op->pv)})
-    if (overlap(*v, in, g, out)) {
-      permute_out(op->ncomp, op->nglobal, nullptr, *v, copy, s);
+    if (permuted || overlap(*v, in, g, out)) {
+      permute_out(op->ncomp, op->nglobal, permuted ? op->perm : nullptr, *v, copy, s);
       *v = copy;
     }
-  return launch_grad_kappa(op, lam, u, g, s);
+  return launch_grad_kappa(op, permuted ? internal_map(op) : caller_map(op), lam, u, g, s);
 }
 
 int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *grad,
@@ -1225,12 +1273,21 @@ int bp_mass_misfit(bp_op op, const double *u, const double *u_target, double *gr
     if (aside) permute_out(nc, n, nullptr, (const double *)op->w, grad, s);
     operator_energies(nc, op->part, vec_blocks(n), op->sc, s);
   } else {
-    difference(u, u_target, op->r, nv, s);
-    double *const Md = grad && (op->tr_pair || takes_atomics(op, grad)) ? grad : op->w;
+    const bool permuted = by_internal_order(op, Route::Mass);
+    if (permuted) {
+      difference(u, u_target, op->pv, nv, s);
+      permute_in<double>(nc, n, op->perm, op->pv, op->r, s);
+    } else {
+      difference(u, u_target, op->r, nv, s);
+    }
+    double *const Md =
+        grad && !permuted && (op->tr_pair || takes_atomics(op, grad)) ? grad : op->w;
     if (!op->tr_pair) clear(Md, nv, s);  // else overwritten
-    rc = launch_apply(op, BP_MASS, false, caller_map(op), op->r, Md, false, pa, nullptr, s);
+    rc = launch_apply(op, BP_MASS, false, permuted ? internal_map(op) : caller_map(op), op->r, Md,
+                      false, pa, nullptr, s);
     if (rc) return rc;
-    if (grad && Md != grad) permute_out(nc, n, nullptr, (const double *)Md, grad, s);
+    if (grad && Md != grad)
+      permute_out(nc, n, permuted ? op->iperm : nullptr, (const double *)Md, grad, s);
     operator_energies(nc, pa, apply_rows(op, BP_MASS), op->sc, s);
   }
   BP_HIP(hipGetLastError());

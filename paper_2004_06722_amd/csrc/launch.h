@@ -19,9 +19,10 @@ int64_t max_partial_rows(const bp_op_s *op);
 // The node order of the vectors a launch reads and writes. Internal: the
 // solves' own, element-interior nodes stored by their element (own). Caller's:
 // the vectors of bp_apply, bp_diag, bp_grad_kappa and bp_mass_misfit as they
-// come, every node added. An operator launch alone is about 10% slower so, but
-// permuting u in and w out is two launches and 2 x 147 us more at p = 8,
-// E = 47,520 (bp_apply 789 -> 562 us; 17.6 -> 12 us at E = 120, p = 5).
+// come, every node added, where the numbering allows it (by_internal_order in
+// capi.cpp). An operator launch alone is about 10% slower so, but permuting u in
+// and w out is two launches and 2 x 147 us more at p = 8, E = 47,520 in a
+// lexicographic order (bp_apply 789 -> 562 us; 17.6 -> 12 us at E = 120, p = 5).
 struct NodeMap {
   const int32_t *idx;
   int own;
@@ -47,8 +48,8 @@ int launch_diag(const bp_op_s *op, int which, const NodeMap &m, double *d, bool 
 // *bad (device, preset to INT_MAX) gets the smallest element with det J <= 0
 int launch_geometry(const bp_op_s *op, const double *X, double *G, double *Bt, int *bad,
                     hipStream_t s);
-int launch_grad_kappa(const bp_op_s *op, const double *lam, const double *u, double *g,
-                      hipStream_t s);
+int launch_grad_kappa(const bp_op_s *op, const NodeMap &m, const double *lam, const double *u,
+                      double *g, hipStream_t s);
 
 // vector kernels (vec.hip); sizes are global nodes n and components nc
 // CG vector kernels give each work-group kVecThreads nodes (vec_blocks; FP32

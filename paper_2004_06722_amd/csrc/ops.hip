@@ -186,11 +186,11 @@ void diag_colloc(const bp_op_s *op, const NodeMap &m, const double *G, const dou
 }
 
 template <int P1>
-void grad_colloc(const bp_op_s *op, const double *lam, const double *u, double *g,
+void grad_colloc(const bp_op_s *op, const NodeMap &m, const double *lam, const double *u, double *g,
                  hipStream_t s) {
   using PL = Plane<P1, P1>;
   hipLaunchKernelGGL((k_grad_kappa_colloc<P1>), dim3(apply_blocks(op)), dim3(PL::THREADS), 0, s,
-                     op->nelem, op->idx_c, op->G, lam, u, g, op->nglobal, op->ncomp);
+                     op->nelem, m.idx, op->G, lam, u, g, op->nglobal, op->ncomp);
 }
 
 }  // namespace
@@ -349,18 +349,18 @@ int launch_geometry(const bp_op_s *op, const double *X, double *G, double *Bt, i
   return BP_OK;
 }
 
-int launch_grad_kappa(const bp_op_s *op, const double *lam, const double *u, double *g,
-                      hipStream_t s) {
+int launch_grad_kappa(const bp_op_s *op, const NodeMap &m, const double *lam, const double *u,
+                      double *g, hipStream_t s) {
   if (!op->colloc) return set_error(BP_ERR_ARG, "bp_grad_kappa: only collocated GLL operators");
   switch (op->p1) {
-    case 2: grad_colloc<2>(op, lam, u, g, s); break;
-    case 3: grad_colloc<3>(op, lam, u, g, s); break;
-    case 4: grad_colloc<4>(op, lam, u, g, s); break;
-    case 5: grad_colloc<5>(op, lam, u, g, s); break;
-    case 6: grad_colloc<6>(op, lam, u, g, s); break;
-    case 7: grad_colloc<7>(op, lam, u, g, s); break;
-    case 8: grad_colloc<8>(op, lam, u, g, s); break;
-    case 9: grad_colloc<9>(op, lam, u, g, s); break;
+    case 2: grad_colloc<2>(op, m, lam, u, g, s); break;
+    case 3: grad_colloc<3>(op, m, lam, u, g, s); break;
+    case 4: grad_colloc<4>(op, m, lam, u, g, s); break;
+    case 5: grad_colloc<5>(op, m, lam, u, g, s); break;
+    case 6: grad_colloc<6>(op, m, lam, u, g, s); break;
+    case 7: grad_colloc<7>(op, m, lam, u, g, s); break;
+    case 8: grad_colloc<8>(op, m, lam, u, g, s); break;
+    case 9: grad_colloc<9>(op, m, lam, u, g, s); break;
     default: return set_error(BP_ERR_ARG, "bp_grad_kappa: compiled for p <= 8");
   }
   BP_HIP(hipGetLastError());

@@ -77,4 +77,18 @@ bool interior_first_order(int p1, int64_t nelem, int64_t nglobal, const int64_t 
   return true;
 }
 
+double id_spread(int p1, int64_t nelem, const int64_t *ed) {
+  const int64_t n3 = (int64_t)p1 * p1 * p1, count = std::min<int64_t>(nelem, 16);
+  std::vector<int64_t> line((size_t)n3);
+  int64_t lines = 0;
+  for (int64_t k = 0; k < count; ++k) {
+    const int64_t *e = ed + (count > 1 ? k * (nelem - 1) / (count - 1) : 0) * n3;
+    for (int64_t l = 0; l < n3; ++l) line[(size_t)l] = e[l] / 16;
+    std::sort(line.begin(), line.end());
+    lines += std::unique(line.begin(), line.end()) - line.begin();
+  }
+  const double rows = p1 * p1 * (1.0 + (p1 - 1) / 16.0);
+  return (double)lines / (rows * (double)count);
+}
+
 }  // namespace bp

@@ -1445,6 +1445,8 @@ void permute_out(int nc, int64_t n, const int32_t *iperm, const T *src, T *dst, 
 }
 template void permute_in<double>(int, int64_t, const int32_t *, const double *, double *,
                                  hipStream_t, const int *);
+template void permute_in<float>(int, int64_t, const int32_t *, const float *, float *, hipStream_t,
+                                const int *);
 template void permute_out<double>(int, int64_t, const int32_t *, const double *, double *,
                                   hipStream_t);
 template void permute_out<float>(int, int64_t, const int32_t *, const float *, float *,
