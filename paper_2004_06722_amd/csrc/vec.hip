@@ -1157,8 +1157,12 @@ __device__ __forceinline__ int64_t natural_point(int64_t qp, int qrev) {
   return (c * qrev + b) * qrev + a;
 }
 
-// One point per thread with its six factors, kappa read once: 127 us at p = 5,
-// E = 32^3 (5.8 TB/s; one factor per thread, kappa read six times: 155 us).
+// One point per thread with its six factors, kappa read once. HBM-bound: 127 us at
+// p = 5, E = 32^3 (5.8 TB/s; one factor per thread, below, 155 us). NT where G does
+// not stay in the caches (us with and without: p = 5, 32^3 115 and 127, 15^3 14.6 and
+// 13.8; p = 13, 12^3 77 and 86; but p = 3 Gauss-Legendre, 48^3 283 and 273, with FP32
+// copies 443 and 379: rows of 125 points, kappa in another order).
+template <bool NT>
 __global__ __launch_bounds__(kVecThreads) void k_scale_geometry(const double *__restrict__ G,
                                                                 const double *__restrict__ kap,
                                                                 double *__restrict__ Gk,
@@ -1170,12 +1174,30 @@ __global__ __launch_bounds__(kVecThreads) void k_scale_geometry(const double *__
   const double k = kap[e * nq + natural_point(qp, qrev)];
   double g[6];
 #pragma unroll
-  for (int m = 0; m < 6; ++m) g[m] = ld_v<true>(G + o + m * (int64_t)nq);
+  for (int m = 0; m < 6; ++m) g[m] = ld_v<NT>(G + o + m * (int64_t)nq);
 #pragma unroll
   for (int m = 0; m < 6; ++m) {
     const double v = k * g[m];
-    st_v<true>(Gk + o + m * (int64_t)nq, v);
+    st_v<NT>(Gk + o + m * (int64_t)nq, v);
     if (Gk32) Gk32[o + m * (int64_t)nq] = (float)v;
+  }
+}
+
+// One factor per thread, in the order they are stored: for elements of few points,
+// whose six rows are parts of lines (us, one point per thread and this: p = 2, 79^3
+// 309 and 269, with FP32 copies 455 and 343, p = 1, 140^3 446 and 438, 653 and 555).
+__global__ __launch_bounds__(kVecThreads) void k_scale_factors(const double *__restrict__ G,
+                                                               const double *__restrict__ kap,
+                                                               double *__restrict__ Gk,
+                                                               float *__restrict__ Gk32,
+                                                               int64_t nelem, int nq, int qrev) {
+  const int64_t total = nelem * 6 * nq;
+  for (int64_t i = (int64_t)blockIdx.x * kVecThreads + threadIdx.x; i < total;
+       i += (int64_t)gridDim.x * kVecThreads) {
+    const int64_t e = i / (6 * (int64_t)nq), qp = i % nq;
+    const double v = kap[e * nq + natural_point(qp, qrev)] * G[i];
+    Gk[i] = v;
+    if (Gk32) Gk32[i] = (float)v;
   }
 }
 
@@ -1506,8 +1528,15 @@ void invert_diag(const double *d, double *dinv, float *dinv32, int64_t n, hipStr
 }
 void scale_geometry(const double *G, const double *kappa, double *Gk, float *Gk32, int qrev,
                     int64_t nelem, int nq, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_geometry, dim3(vec_blocks(nelem * nq)), dim3(kVecThreads), 0, s,
-                     G, kappa, Gk, Gk32, nelem, nq, qrev);
+  const dim3 g(vec_blocks(nelem * nq)), t(kVecThreads);
+  const bool streams = nelem * 6 * nq * (int64_t)sizeof(double) >= 2 * kStreamBytes;
+  if (nq < 64)
+    hipLaunchKernelGGL(k_scale_factors, dim3(grid_blocks(nelem * 6 * nq)), t, 0, s, G, kappa, Gk,
+                       Gk32, nelem, nq, qrev);
+  else if (streams && (!qrev || nq >= 216))
+    hipLaunchKernelGGL(k_scale_geometry<true>, g, t, 0, s, G, kappa, Gk, Gk32, nelem, nq, qrev);
+  else
+    hipLaunchKernelGGL(k_scale_geometry<false>, g, t, 0, s, G, kappa, Gk, Gk32, nelem, nq, qrev);
 }
 
 // after a residual replacement that ended an iteration before its direction
