@@ -268,6 +268,21 @@ __device__ __forceinline__ void eo_apply(const T *__restrict__ tab, const T (&x)
 // loaded while the one before is applied (see below).
 constexpr int colloc_chunk(int p1) { return p1 <= 8 ? p1 : p1 <= 11 ? 4 : 2; }
 
+// Loads of the per-point factors, each read once: nontemporal where NT. At p1 <= 3 an
+// element's rows of G are parts of lines (8 and 27 values) that its lanes come back to
+// plane by plane, and without NT the line is still there: us with and without, p = 1,
+// E = 74^3 and 140^3, element-local 55.6 and 31.3, 354 and 240, in FP32 48 and 17, 311
+// and 120, gradient 57.7 and 30.4, 374 and 237; p = 2, 50^3 51.9 and 35.9, 39.2 and 22.7,
+// 53.7 and 34.6. At p1 = 4 the gradient loses without (97 and 113), and so does the
+// assembled application at p = 1, in large meshes.
+template <bool NT, typename T>
+__device__ __forceinline__ T ld_g(const T *p) {
+  if constexpr (NT)
+    return __builtin_nontemporal_load(p);
+  else
+    return *p;
+}
+
 // Body of the collocated stiffness kernels (described below): with MULTI
 // every component of u and w ([ncomp][cs]) runs through one work-group, the
 // map loaded once; otherwise the one component that u and w point at
@@ -289,7 +304,11 @@ __device__ __forceinline__ void stiff_colloc_body(
   const int slot = act ? t / PL::N : 0;
   const int ij = t % PL::N;
   const int i = ij % P1, j = ij / P1;
-  const int64_t bx = LOCAL ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
+  // p = 1 in FP64 adds every node atomically and gains no reuse from runs of elements
+  // on one XCD: 74^3, three components 157.6 us with them, 149.6 without, 140^3, one
+  // 421.6 and 413.5 (FP32 54.4 and 57)
+  constexpr bool PLAIN = LOCAL || (P1 == 2 && sizeof(T) == 8);
+  const int64_t bx = PLAIN ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
   const int64_t e = bx * PL::EPB + slot;
   if (PL::EPB == 1 && e >= nelem) return;  // uniform over the work-group
   const bool live = act && e < nelem;
@@ -333,7 +352,7 @@ __device__ __forceinline__ void stiff_colloc_body(
 #pragma unroll
       for (int k = ch * KC; k < (ch + 1) * KC && k < P1; ++k)
         g[n][k] = MULTI && NCH > 1 ? Ge[n * N3 + k * PP]
-                                   : __builtin_nontemporal_load(Ge + n * N3 + k * PP);
+                                   : ld_g<!LOCAL || (P1 > 3)>(Ge + n * N3 + k * PP);
   };
   T un[P1];
   if constexpr (LOCAL)  // no map to wait for: u before G
@@ -1357,7 +1376,7 @@ __global__ __launch_bounds__((Plane<P1, P1>::THREADS)) __attribute__((amdgpu_wav
 #pragma unroll
     for (int n = 0; n < 6; ++n)
 #pragma unroll
-      for (int k = 0; k < P1; ++k) g[n][k] = __builtin_nontemporal_load(Ge + n * N3 + k * PP);
+      for (int k = 0; k < P1; ++k) g[n][k] = ld_g<(P1 > 3)>(Ge + n * N3 + k * PP);
   double acc[P1], xn[P1];
 #pragma unroll
   for (int k = 0; k < P1; ++k) {
