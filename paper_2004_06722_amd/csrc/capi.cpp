@@ -276,18 +276,16 @@ int64_t stored_rows(const bp_op_s *op, int which) {
 //   481 / 262; gradient 130 / 221, 150 / 220, 593 / 417. The Gauss-Legendre
 //   stiffness diagonal is held by its arithmetic: 515 / 530, 500 / 524, 549 / 596
 // Small vectors stay in the caches, and there the launches count (random ids, p = 5):
-// stiffness FP64 n = 2.3e5 27 / 27, 5.3e5 55 / 42; FP32 1e5 17 / 22, 2.3e5 26 / 23;
-// mass (p = 4) 5.3e5 39 / 34, 2.3e5 21 / 24; diagonal 1e5 16 / 19, 2.3e5 23 / 20;
-// gradient 5.3e5 37 / 35, 2.3e5 12 / 21.
+// stiffness FP64 n = 2.3e5 27 / 27 (p = 2, 2.1e5 38 / 33), 5.3e5 55 / 42; FP32 1e5
+// 17 / 22, 2.3e5 26 / 23; mass (p = 4) 5.3e5 39 / 34, 2.3e5 21 / 24; diagonal 1e5 16 / 19,
+// 2.3e5 23 / 20; gradient 5.3e5 37 / 35, 2.3e5 12 / 21.
 enum class Route { Stiff, Stiff32, Mass, Diag, DiagMass, Gradient };
 bool by_internal_order(const bp_op_s *op, Route call) {
   if (!op->perm || (call == Route::Diag && !op->colloc)) return false;
   const bool diag = call == Route::Diag || call == Route::DiagMass;
   const double tight = op->p >= 4 ? 1.4 : kSpreadFar;
   const double far = call == Route::Stiff32 || call == Route::DiagMass ? tight : kSpreadFar;
-  const int64_t least = diag || call == Route::Stiff32 ? 190000
-                        : call == Route::Stiff         ? 300000
-                                                       : 480000;
+  const int64_t least = call == Route::Mass || call == Route::Gradient ? 480000 : 190000;
   return op->spread > far && op->nglobal * (diag ? 1 : op->ncomp) >= least;
 }
 
