@@ -272,8 +272,8 @@ int64_t stored_rows(const bp_op_s *op, int which) {
 //   random 535 / 421; p = 2, 60^3: 94 / 139, 100 / 143, 269 / 174
 // - FP32: 118 / 148, 195 / 145, 556 / 326; p = 2: 77 / 105, 83 / 107, 295 / 127
 // - Gauss-Legendre mass, p = 7, 24^3: 66 / 133, 84 / 129, 341 / 246
-// - diagonal 179 / 220, 222 / 216, 508 / 319, of the mass 128 / 159, 186 / 156,
-//   481 / 262; gradient 130 / 221, 150 / 220, 593 / 417. The Gauss-Legendre
+// - diagonal 179 / 220, 222 / 216, 508 / 319, of the mass (p = 7, 24^3) 102 / 131,
+//   137 / 128, 315 / 197; gradient 130 / 221, 150 / 220, 593 / 417. The Gauss-Legendre
 //   stiffness diagonal is held by its arithmetic: 515 / 530, 500 / 524, 549 / 596
 // Small vectors stay in the caches, and there the launches count (random ids, p = 5):
 // stiffness FP64 n = 2.3e5 27 / 27 (p = 2, 2.1e5 38 / 33), 5.3e5 55 / 42; FP32 1e5
@@ -1059,6 +1059,11 @@ int bp_diag(bp_op op, int which, double *d, unsigned flags, void *stream) {
   if (!d) return set_error(BP_ERR_ARG, "bp_diag: NULL output");
   if (flags & ~BP_MASKED) return set_error(BP_ERR_ARG, "bp_diag: unknown flag");
   hipStream_t s = (hipStream_t)stream;
+  if (which == BP_MASS && op->md) {  // assembled at set-up
+    mass_entries(op->nglobal, op->md, d, (flags & BP_MASKED) != 0, s);
+    BP_HIP(hipGetLastError());
+    return BP_OK;
+  }
   const bool permuted = by_internal_order(op, which == BP_MASS ? Route::DiagMass : Route::Diag);
   double *const dd = !permuted && takes_atomics(op, d) ? d : op->tmp;
   fill_f64(dd, op->nglobal, 0.0, s);

@@ -233,14 +233,15 @@ void cg_restart(int nc, int64_t n, T *r, T *p, const T *dinv, double *part,
 // sc->pap[c] = sum over the rows of column c of the operator's energy table
 // part[rows][nc] (fixed order); part + rows nc holds the stage-1 rows
 void operator_energies(int nc, double *part, int64_t rows, DevScalars *sc, hipStream_t s);
-// collocated mass: w = M u with the assembled diagonal md (caller's order), and
-// the misfit's gradient and energy rows [vec_blocks(n)][nc]; assemble_mass sums
+// collocated mass: w = M u with the assembled diagonal md (caller's order), its
+// entries (0 on masked nodes), and the misfit's gradient and energy rows [vec_blocks(n)][nc]; assemble_mass sums
 // that diagonal from Bt over the map's count slots (the same bits whatever the
 // order of arrival; hi and lo: n words of scratch each) and makes it negative on
 // the map's Dirichlet nodes
 template <typename T>
 void mass_diagonal(int nc, int64_t n, const double *md, const T *u, T *w, bool masked,
                    hipStream_t s);
+void mass_entries(int64_t n, const double *md, double *d, bool masked, hipStream_t s);
 void misfit_diagonal(int nc, int64_t n, const double *md, const double *u, const double *ut,
                      double *grad, double *part, hipStream_t s);
 void assemble_mass(const int32_t *idx, const double *Bt, int64_t count, int64_t n, double *md,

@@ -62,3 +62,18 @@ def test_nodes_of_many_slots_and_of_none(ncomp):
             assert rel(w, md * u) <= TOL
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("p,grid", [(1, (3, 2, 5)), (5, (13, 12, 12)), (7, (5, 5, 5))])
+def test_diagonal_is_the_assembled_matrix(p, grid):
+    # bp_diag gives the entries that an application multiplies by, bit for bit, 0
+    # on masked nodes and on those of no element
+    xi, _ = B.rule(p + 1, B.GLL)
+    m = synth.scramble_mesh(synth.brick_mesh(*grid, p, xi, seed=3), 5)
+    bd = np.concatenate([np.asarray(m.boundary, dtype=bool), [False]])
+    with B.Operator(p, p + 1, B.GLL, m.elem_dofs, m.node_xyz, m.nglobal + 1, bd) as op:
+        ones = torch.ones(m.nglobal + 1, dtype=torch.float64, device="cuda")
+        for masked in (False, True):
+            d = op.diag(MASS, masked=masked).cpu().numpy()
+            assert np.array_equal(d, op.apply(MASS, ones, masked=masked).cpu().numpy())
+            assert np.array_equal(d == 0.0, bd & masked | (np.arange(d.size) == m.nglobal))
